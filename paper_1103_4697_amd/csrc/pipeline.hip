@@ -76,8 +76,6 @@ void layout_batch(const std::vector<ResPlan>& plans, BatchLayout& lay) {
   lay.pref_red = off; off = align256(off + 8 * (NJ + 1));
   lay.pref_interp = off; off = align256(off + 8 * (NJ + 1));
   lay.pref_interp_blk = off; off = align256(off + 8 * (NJ + 1));
-  lay.pref_crtd = off; off = align256(off + 8 * (NJ + 1));
-  lay.pref_crtc = off; off = align256(off + 8 * (NJ + 1));
   // one lane per coefficient pays off only when the batch's few-prime coefficients fill the device
   // (a wavefront per CU); otherwise the lanes go over the primes of each coefficient
   int64_t small_coefs = 0;
@@ -85,14 +83,21 @@ void layout_batch(const std::vector<ResPlan>& plans, BatchLayout& lay) {
     if (crt_small_class(plans[lay.dev[j]].k) >= 0) small_coefs += plans[lay.dev[j]].D + 1;
   lay.crt_small_on = small_coefs >= CRT_SMALL_MIN_COEFS;
   for (int j = 0; j < NJ; ++j) {
-    const int cc = lay.crt_small_on ? crt_small_class(plans[lay.dev[j]].k) : -1;
-    if (cc >= 0) lay.n_crts_jobs[cc]++; else lay.n_crtb_jobs++;
+    const int k = plans[lay.dev[j]].k;
+    const int cc = lay.crt_small_on ? crt_small_class(k) : -1;
+    if (cc >= 0) lay.n_crts_jobs[cc]++;
+    else if (k >= CRT_MFMA_MIN) lay.n_crtm_jobs++;
+    else lay.n_crtb_jobs++;
   }
+  // one section each for the jobs of both kinds of the other remaindering
+  const size_t nbm = (size_t)lay.n_crtb_jobs + lay.n_crtm_jobs;
+  lay.pref_crtd = off; lay.pref_crtm_grp = off + 8 * (lay.n_crtb_jobs + 1); off = align256(off + 8 * (nbm + 2));
+  lay.pref_crtc = off; lay.pref_crtm_tile = off + 8 * (lay.n_crtb_jobs + 1); off = align256(off + 8 * (nbm + 2));
   for (int c = 0; c < NCRT_SMALL; ++c) {
     lay.pref_crts[c] = off; off = align256(off + 8 * (lay.n_crts_jobs[c] + 1));
     lay.list_crts[c] = off; off = align256(off + 4 * std::max(lay.n_crts_jobs[c], 1));
   }
-  lay.list_crtb = off; off = align256(off + 4 * std::max(lay.n_crtb_jobs, 1));
+  lay.list_crtb = off; lay.list_crtm = off + 4 * lay.n_crtb_jobs; off = align256(off + 4 * std::max<size_t>(nbm, 1));
   lay.pref_inst = off; off = align256(off + 8 * (NJ + 1));
   lay.pref_iw = off; off = align256(off + 8 * (NJ + 1));
   lay.list_iw = off; off = align256(off + 4 * std::max(NJ, 1));
@@ -139,6 +144,10 @@ void layout_batch(const std::vector<ResPlan>& plans, BatchLayout& lay) {
     const int cc = lay.crt_small_on ? crt_small_class(P.k) : -1;
     if (cc >= 0) {
       lay.nb_crts[cc] += (int64_t)((n1 + 63) / 64);
+    } else if (P.k >= CRT_MFMA_MIN) {
+      lay.nb_crtm_grp += crt_mfma_groups((int)n1);
+      lay.nb_crtm_tile += crt_mfma_tiles((int)n1, P.k);
+      lay.max_k_crtm = std::max(lay.max_k_crtm, P.k);
     } else {
       lay.nb_crtd += (int64_t)((n1 + CRT_COEF_PER_BLOCK - 1) / CRT_COEF_PER_BLOCK);
       lay.nb_crtc += (int64_t)((n1 + CRT_COMB_PER_BLOCK - 1) / CRT_COMB_PER_BLOCK);
@@ -291,9 +300,22 @@ void launch_pipeline(const BatchLayout& lay, uint8_t* ws, hipStream_t s, StageTi
     const int32_t* lb = (const int32_t*)(ws + lay.list_crtb);
     launch_crt_digits(tb, jobs, lb, (const int64_t*)(ws + lay.pref_crtd), lay.n_crtb_jobs, lay.nb_crtd, wsw, s);
     if (tm) tm->mark("crt_digits", 1);
-    launch_crt_combine(tb, jobs, lb, (const int64_t*)(ws + lay.pref_crtc), lay.n_crtb_jobs, lay.nb_crtc, lay.max_k,
+    launch_crt_combine(tb, jobs, lb, (const int64_t*)(ws + lay.pref_crtc), lay.n_crtb_jobs, lay.nb_crtc,
+                       (int)std::min<int64_t>(lay.max_k, CRT_MFMA_MIN - 1),
                        wsw, s);
     if (tm) tm->mark("crt_combine", 1);
+  }
+  if (lay.n_crtm_jobs) {
+    const CrtTables tb = global_crt_tables();
+    const int32_t* lm = (const int32_t*)(ws + lay.list_crtm);
+    const int64_t* pg = (const int64_t*)(ws + lay.pref_crtm_grp);
+    launch_crt_mfma_digits(tb, jobs, lm, pg, lay.n_crtm_jobs, lay.nb_crtm_grp, lay.max_k_crtm, wsw, s);
+    if (tm) tm->mark("crt_mfma_digits", 1);
+    launch_crt_mfma_product(jobs, lm, (const int64_t*)(ws + lay.pref_crtm_tile), lay.n_crtm_jobs, lay.nb_crtm_tile,
+                            wsw, s);
+    if (tm) tm->mark("crt_mfma_product", 1);
+    launch_crt_mfma_carry(tb, jobs, lm, pg, lay.n_crtm_jobs, lay.nb_crtm_grp, lay.max_k_crtm, wsw, s);
+    if (tm) tm->mark("crt_mfma_carry", 1);
   }
 }
 
@@ -338,6 +360,11 @@ void fill_header(const BatchLayout& lay, const std::vector<ResPlan>& plans, cons
   }
   int32_t* lbig = (int32_t*)(h + lay.list_crtb);
   int nbig = 0;
+  int32_t* lmm = (int32_t*)(h + lay.list_crtm);
+  int64_t* pmg = (int64_t*)(h + lay.pref_crtm_grp);
+  int64_t* pmt = (int64_t*)(h + lay.pref_crtm_tile);
+  int nmm = 0;
+  pmg[0] = pmt[0] = 0;
   std::vector<std::pair<int64_t, int>> by_cost[NCLS];  // (work per block, job) per register class
   int64_t* pg = (int64_t*)(h + lay.pref_gen);
   int32_t* lg = (int32_t*)(h + lay.list_gen);
@@ -390,6 +417,11 @@ void fill_header(const BatchLayout& lay, const std::vector<ResPlan>& plans, cons
       ls[cc][ns[cc]] = j;
       ps[cc][ns[cc] + 1] = ps[cc][ns[cc]] + (n1 + 63) / 64;
       ns[cc]++;
+    } else if (P.k >= CRT_MFMA_MIN) {
+      lmm[nmm] = j;
+      pmg[nmm + 1] = pmg[nmm] + crt_mfma_groups((int)n1);
+      pmt[nmm + 1] = pmt[nmm] + crt_mfma_tiles((int)n1, P.k);
+      nmm++;
     } else {
       lbig[nbig] = j;
       pd[nbig + 1] = pd[nbig] + (n1 + CRT_COEF_PER_BLOCK - 1) / CRT_COEF_PER_BLOCK;

@@ -103,6 +103,7 @@ int ensure_device_tables(int device, std::string& err) {
   if (done.count(device)) return SNC_OK;
   const Tables& T = tables();
   hipError_t e = configure_kernels();
+  if (e == hipSuccess) e = configure_crt_mfma();
   if (e == hipSuccess) e = configure_gcd_kernels();
   if (e == hipSuccess) e = configure_ygcd_kernel();
   if (e != hipSuccess) { err = std::string("kernel attributes: ") + hipGetErrorString(e); return SNC_EDEVICE; }
@@ -111,6 +112,7 @@ int ensure_device_tables(int device, std::string& err) {
   upload_tables(T.pc.data(), T.garner.data(), T.wtab.data(), T.ptab.data(), nullptr);
   launch_ifact_init(nullptr);
   launch_crt_small_init(nullptr);
+  launch_crt_mfma_init(global_crt_tables(), nullptr);
   e = hipDeviceSynchronize();
   if (e != hipSuccess) { err = std::string("table upload: ") + hipGetErrorString(e); return SNC_EDEVICE; }
   (void)global_crt_tables();

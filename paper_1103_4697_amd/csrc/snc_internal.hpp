@@ -194,6 +194,23 @@ inline int crt_small_class(int k) {
 void launch_crt_small(int cls, const ResJob* jobs_d, const int32_t* job_list_d, const int64_t* prefix_d, int njobs,
                       int64_t nblocks, uint32_t* ws, hipStream_t s);
 void launch_crt_small_init(hipStream_t s);  // transposed table of P_j mod p_i (once per device)
+// Chinese remaindering on the matrix cores (more than CRT_MFMA_MIN - 1
+// primes): digits and carry over groups of 16 coefficients (prefix of
+// crt_mfma_groups over the launch's jobs), limb sums over tiles (prefix of
+// crt_mfma_tiles); the limb sums use the points and Newton-block regions
+constexpr int CRT_MFMA_MIN = 65;
+int64_t crt_mfma_groups(int n1);
+int64_t crt_mfma_tiles(int n1, int k);
+hipError_t configure_crt_mfma();
+void launch_crt_mfma_init(const CrtTables& tb, hipStream_t s);  // operand tables (once per device)
+void launch_crt_mfma_digits(const CrtTables& tb, const ResJob* jobs_d, const int32_t* job_list_d,
+                            const int64_t* prefix_d, int njobs, int64_t ngroups, int kmax, uint32_t* ws,
+                            hipStream_t s);
+void launch_crt_mfma_product(const ResJob* jobs_d, const int32_t* job_list_d, const int64_t* prefix_d, int njobs,
+                             int64_t ntiles, uint32_t* ws, hipStream_t s);
+void launch_crt_mfma_carry(const CrtTables& tb, const ResJob* jobs_d, const int32_t* job_list_d,
+                           const int64_t* prefix_d, int njobs, int64_t ngroups, int kmax, uint32_t* ws,
+                           hipStream_t s);
 CrtTables global_crt_tables();  // the resident tables of the modulus table (after upload)
 
 // gcd work items are (problem, slot) pairs indexing a device array of GcdDesc
