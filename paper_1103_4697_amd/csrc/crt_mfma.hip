@@ -41,11 +41,9 @@
 #include <hip/hip_runtime.h>
 
 #include "eval_elim.hpp"
+#include "mfma_modp.hpp"
 
 namespace snc {
-
-typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
 
 constexpr int CM_NB = KMAX / 64;   // blocks of primes in the table
 static_assert(KMAX % 64 == 0, "whole blocks");
@@ -59,9 +57,6 @@ __device__ uint32_t g_vinv[KMAX];                       // Montgomery form of V_
 // balanced bytes (each word four signed bytes, sum b_s 256^s) of V_j and P_j
 __device__ uint32_t g_vbal[(size_t)KMAX * LPS];
 __device__ uint32_t g_pbal[(size_t)KMAX * LPS];
-
-// v < 2^31 as four signed bytes
-__device__ __forceinline__ uint32_t balance4(uint32_t v) { return (v + 0x00808080u) ^ 0x00808080u; }
 
 __global__ __launch_bounds__(64) void k_crtm_vinv(CrtTables tb) {
   const int i = blockIdx.x * 64 + threadIdx.x;
@@ -119,18 +114,6 @@ __global__ __launch_bounds__(64) void k_crtm_balance(CrtTables tb) {
 // and on half of the earlier blocks' contraction.
 // ---------------------------------------------------------------------------
 
-// sum_d acc[d] 256^d 2^-32 mod p, canonical, for |acc[d]| < 2^28: the sum is
-// split at 2^24, both parts made positive by multiples of p, and the upper
-// one brought back by k56 = 2^56 mod p
-__device__ __forceinline__ uint32_t fold_bytes(const v4i (&acc)[7], int r, uint32_t k56, const PrimeC& c) {
-  const int64_t lo = (int64_t)acc[0][r] + (int64_t)acc[1][r] * 256 + (int64_t)acc[2][r] * 65536;
-  const int64_t hi = (int64_t)acc[3][r] + (int64_t)acc[4][r] * 256 + (int64_t)acc[5][r] * 65536 +
-                     (int64_t)acc[6][r] * 16777216;
-  const uint32_t h = redc((uint64_t)(hi + ((int64_t)c.p << 24)), c.p, c.pinv);  // < 2^23 + p
-  const uint64_t t = (uint64_t)(lo + ((int64_t)c.p << 17)) + (uint64_t)h * k56;
-  return canon2(redc(t, c.p, c.pinv), c.p);
-}
-
 template <int ROWS>
 __global__ __launch_bounds__(CM_THREADS) void k_crtm_digits(CrtTables tb, const ResJob* jobs, const int32_t* job_list,
                                                             const int64_t* prefix, int njobs, uint32_t* ws) {
@@ -185,11 +168,11 @@ __global__ __launch_bounds__(CM_THREADS) void k_crtm_digits(CrtTables tb, const 
         for (int y = 0; y < 4; ++y)
           acc[x + y] = __builtin_amdgcn_mfma_i32_16x16x64_i8(av[x], bv[y], acc[x + y], 0, 0, 0);
     }
-    const uint32_t k56 = redc((uint64_t)c.r2 << 24, c.p, c.pinv);
+    const uint32_t k56 = fold_const(c);
     uint32_t S[4];
     if (row0 < ROWS) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) S[r] = fold_bytes(acc, r, canon2(k56, c.p), c);
+      for (int r = 0; r < 4; ++r) S[r] = fold_bytes(acc[0][r], acc[1][r], acc[2][r], acc[3][r], acc[4][r], acc[5][r], acc[6][r], k56, c);
       if (half == 1 || s == nf) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) Sp[half][row0 + r][col] = S[r];

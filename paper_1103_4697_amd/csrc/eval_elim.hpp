@@ -51,7 +51,7 @@ __device__ __forceinline__ uint32_t reduce_limbs(const uint32_t* limbs, int nl, 
 }
 
 // ---------------------------------------------------------------------------
-// (2)+(3) Evaluation at x_j = j fused with the univariate resultant mod p.
+// (2)+(3) Evaluation at the points x_j fused with the univariate resultant mod p.
 //
 // One (prime, point) instance per lane: a wavefront holds 64 consecutive
 // points of one prime, so every coefficient residue is uniform across the
@@ -339,7 +339,7 @@ __device__ __forceinline__ void eval_elim_block(int64_t b, const PrimeC* primes,
                                                 const int32_t* job_list, const int64_t* prefix, int njobs,
                                                 const RowDesc* rows, uint32_t* ws, uint32_t* abn_count,
                                                 AbnEntry* abn_list, uint32_t abn_cap, int reduce_in, uint32_t* er,
-                                                int64_t& staged) {
+                                                const uint32_t* points, int64_t& staged) {
   const int jj = find_job(prefix, njobs, b);
   const int jid = job_list[jj];
   const ResJob J = jobs[jid];
@@ -372,7 +372,7 @@ __device__ __forceinline__ void eval_elim_block(int64_t b, const PrimeC* primes,
     r = er;
   }
   XPow X;
-  X.x1 = to_mont((uint32_t)j, c);
+  X.x1 = point_mont(points, pi, j, c);
   X.x2 = mmulc(X.x1, X.x1, c.p, c.pinv);
   X.x3 = mmulc(X.x2, X.x1, c.p, c.pinv);
   X.x4 = mmulc(X.x2, X.x2, c.p, c.pinv);
@@ -436,6 +436,7 @@ __device__ __forceinline__ void eval_elim_block(int64_t b, const PrimeC* primes,
 // blocks to be taken are the cheapest.
 struct EEWork {
   uint32_t* counter;
+  const uint32_t* points;  // table of the evaluation points
   int32_t chunk;
 };
 
@@ -453,7 +454,7 @@ __global__ __launch_bounds__(EE_BLOCK) __attribute__((amdgpu_waves_per_eu(WPE)))
   int64_t staged = -1;
   if (wk.chunk == 0) {
     eval_elim_block<N, LDSROWS>(xcd_block(blockIdx.x, gridDim.x), primes, jobs, job_list, prefix, njobs, rows,
-                                ws, abn_count, abn_list, abn_cap, reduce_in, er, staged);
+                                ws, abn_count, abn_list, abn_cap, reduce_in, er, wk.points, staged);
     return;
   }
   const int64_t nb = prefix[njobs];
@@ -465,7 +466,7 @@ __global__ __launch_bounds__(EE_BLOCK) __attribute__((amdgpu_waves_per_eu(WPE)))
     const int64_t end = (int64_t)base + wk.chunk < nb ? (int64_t)base + wk.chunk : nb;
     for (int64_t b = base; b < end; ++b)
       eval_elim_block<N, LDSROWS>(b, primes, jobs, job_list, prefix, njobs, rows, ws, abn_count, abn_list,
-                                  abn_cap, reduce_in, er, staged);
+                                  abn_cap, reduce_in, er, wk.points, staged);
   }
 }
 
@@ -520,7 +521,7 @@ void launch_eval_elim_cls(const EEVariant& v, uint32_t* counter, const PrimeC* p
   const bool in_lds = eval_elim_in_lds(max_T);
   const size_t lds = in_lds ? (size_t)max_T * sizeof(uint32_t) : 0;
   const int red = reduce_in && in_lds ? 1 : 0;
-  const EEWork wk{counter, persistent ? v.chunk : 0};
+  const EEWork wk{counter, points_table(), persistent ? v.chunk : 0};
   const void* k = in_lds ? ee_kernel_ptr<NN, true>(v.wpe) : ee_kernel_ptr<NN, false>(v.wpe);
   void* args[] = {(void*)&primes, (void*)&jobs_d, (void*)&job_list_d, (void*)&blk_prefix_d, (void*)&njobs,
                   (void*)&rows_d, (void*)&ws, (void*)&abn_count, (void*)&abn_list, (void*)&abn_cap, (void*)&red,

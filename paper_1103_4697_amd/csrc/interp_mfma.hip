@@ -1,0 +1,399 @@
+// Interpolation mod p on the matrix cores (Section 4, "Symbolic Speedups":
+// the images over Z_p at points are combined into coefficients over Z_p).
+//
+// Points.  x_j = q^j mod p, j = 0..D, with q of order above MAX_D mod p.  With
+// phi_m = (q - 1)(q^2 - 1) ... (q^m - 1) the Newton polynomials satisfy
+//   N_k(q^i) = q^C(k,2) phi_i / phi_{i-k},
+//   N_k(x)   = sum_i (-1)^{k-i} q^C(k-i,2) phi_k / (phi_i phi_{k-i}) x^i
+// (the q-binomial theorem), and 1 / sum_m z^m / phi_m = sum_m t_m z^m,
+// t_m = (-1)^m q^C(m,2) / phi_m.  So values v_i become coefficients c_i by two
+// products with the same sequence t, lower and upper triangular Toeplitz, and
+// scalings by tables:
+//   u_i = v_i / phi_i,   b_k = sum_{i <= k} t_{k-i} u_i,
+//   e_k = b_k psi_k,     psi_k = phi_k q^-C(k,2),
+//   c_i = (1 / phi_i) sum_{k >= i} t_{k-i} e_k.
+// (At points 0..D the expansion of the Newton form needs falling factorials
+// that differ from block to block.)
+//
+// Mapping.  A workgroup takes one prime and a group of jobs.  Outputs go in
+// blocks of 64; a row of the matrix product is one (job, block), and step d
+// multiplies the rows' input blocks at distance d by the 64 x 64 Toeplitz
+// block T_d, the same for every row.  T_d is never stored: column n of a tile
+// is output 4 n + kappa (kappa = 0..3), so a lane's 16 contraction entries
+// are consecutive bytes of t that start at a multiple of four plus a shift
+// common to the wavefront.  Five words read from LDS give the operands of all
+// four kappa by byte alignment.
+//
+// Bounds and figures (MI355X).  The sums over the whole degree were 64-bit
+// multiply-adds on the vector unit (one wavefront per (resultant, prime) at
+// 77% of its issue slots, or a workgroup with barriers per block), with the
+// expansion of each Newton block a further sixth.  512 pairs of degrees 8..40
+// (25,000 (resultant, prime) pairs, degree bounds up to 1,600): 1,100 -> 274
+// us, 0.9 P byte products/s, bound by the matrix cores and the LDS reads of
+// the operands about equally.  One pair of degree bound 3,072 with 262 primes:
+// 523 -> 79 us (three row tiles and a sixteenth: a third of the products are
+// on rows that end earlier).  Degree bound 225, 15 pairs, 2,052 primes: 248 ->
+// 116 us; degree bound 552, 35 primes: 13 (two launches) -> 11 us; degree
+// bound 36, 5 primes: 8.4 (two launches) -> 6.7 us, both latency.
+#include <hip/hip_runtime.h>
+
+#include "eval_elim.hpp"
+#include "mfma_modp.hpp"
+
+namespace snc {
+
+constexpr int IM_TROW = (MAX_D + 64) / 64 * 64 + 64;  // bytes of a plane of t per prime (zeros above MAX_D)
+
+__device__ uint32_t g_iphi[(size_t)KMAX * (MAX_D + 1)];  // Montgomery form of 1 / phi_m
+__device__ uint32_t g_psi[(size_t)KMAX * (MAX_D + 1)];   // Montgomery form of psi_m
+__device__ __align__(16) int8_t g_tq[(size_t)KMAX * 4 * IM_TROW];  // bytes of t_m (Montgomery form), four planes
+// points: q^l for l < 64, then q^(64 b) at 64 + b (Montgomery form)
+__device__ uint32_t g_points[(size_t)KMAX * POINT_ROW];
+
+// one prime per thread
+__global__ __launch_bounds__(64) void k_points_init(const PrimeC* primes) {
+  const int pi = blockIdx.x * 64 + threadIdx.x;
+  const PrimeC c = primes[pi];
+  uint32_t* ip = g_iphi + (size_t)pi * (MAX_D + 1);
+  uint32_t* ps = g_psi + (size_t)pi * (MAX_D + 1);
+  int8_t* tq = g_tq + (size_t)pi * 4 * IM_TROW;
+  uint32_t* pt = g_points + (size_t)pi * POINT_ROW;
+  // the least q >= 2 of order above MAX_D; phi_m in psi's row
+  uint32_t q = 0, phi = c.r1, qm = c.r1;
+  for (uint32_t g = 2; q == 0; ++g) {
+    const uint32_t gm = to_mont(g, c);
+    phi = c.r1;
+    qm = c.r1;
+    ps[0] = phi;
+    bool ok = true;
+    for (int m = 1; m <= MAX_D && ok; ++m) {
+      qm = mmulc(qm, gm, c.p, c.pinv);
+      ok = qm != c.r1;
+      phi = mmulc(phi, msub(qm, c.r1, c.p), c.p, c.pinv);
+      ps[m] = phi;
+    }
+    if (ok) q = gm;
+  }
+  const uint32_t iq = minv(q, c);
+  uint32_t inv = minv(phi, c);  // 1 / phi_m, and qm = q^m, from the top down
+  for (int m = MAX_D; m >= 0; --m) {
+    ip[m] = inv;
+    inv = mmulc(inv, msub(qm, c.r1, c.p), c.p, c.pinv);
+    qm = mmulc(qm, iq, c.p, c.pinv);
+  }
+  uint32_t qp = c.r1, iqp = c.r1, qc = c.r1, iqc = c.r1;  // q^m, q^-m, q^C(m,2), q^-C(m,2)
+  for (int m = 0; m <= MAX_D; ++m) {
+    uint32_t t = mmulc(qc, ip[m], c.p, c.pinv);
+    if (m & 1) t = mneg(t, c.p);
+    const uint32_t w = balance4(t);
+    for (int b = 0; b < 4; ++b) tq[(size_t)b * IM_TROW + m] = (int8_t)(w >> (8 * b));
+    ps[m] = mmulc(ps[m], iqc, c.p, c.pinv);
+    if (m < 64) pt[m] = qp;
+    if (m % 64 == 0) pt[64 + m / 64] = qp;
+    qc = mmulc(qc, qp, c.p, c.pinv);
+    iqc = mmulc(iqc, iqp, c.p, c.pinv);
+    qp = mmulc(qp, q, c.p, c.pinv);
+    iqp = mmulc(iqp, iq, c.p, c.pinv);
+  }
+}
+
+constexpr int IM_THREADS = 256;
+constexpr int IM_WAVES = IM_THREADS / 64;
+constexpr int IM_MAXROWS = 192;
+static_assert((MAX_D + 64) / 64 <= IM_MAXROWS, "the rows of one job of the largest degree bound");
+
+// LDS of a group: the planes of t (reversed and ascending, or one after the
+// other where both do not fit; zeros below index 0), then for each job the
+// planes of u and of e
+__host__ __device__ constexpr int im_tplane(int Dp) { return Dp + 144; }
+__host__ __device__ constexpr bool im_both(int Dp) { return Dp <= 4096; }
+static_assert(4 * im_tplane((MAX_D + 64) / 64 * 64) + 8 * ((MAX_D + 64) / 64 * 64) + 8 * 1024 <= 160 * 1024,
+              "the buffers of the largest degree bound fit the LDS of a CU");
+
+// the four bytes planes of four consecutive values
+__device__ __forceinline__ void split_planes(const uint32_t (&w)[4], uint32_t (&pl)[4]) {
+  const uint32_t a = __builtin_amdgcn_perm(w[1], w[0], 0x05010400u);  // bytes 0, 1 of w0, w1: 0a 0b 1a 1b
+  const uint32_t b = __builtin_amdgcn_perm(w[3], w[2], 0x05010400u);
+  const uint32_t d = __builtin_amdgcn_perm(w[1], w[0], 0x07030602u);  // bytes 2, 3
+  const uint32_t e = __builtin_amdgcn_perm(w[3], w[2], 0x07030602u);
+  pl[0] = __builtin_amdgcn_perm(b, a, 0x05040100u);
+  pl[1] = __builtin_amdgcn_perm(b, a, 0x07060302u);
+  pl[2] = __builtin_amdgcn_perm(e, d, 0x05040100u);
+  pl[3] = __builtin_amdgcn_perm(e, d, 0x07060302u);
+}
+
+// bytes sh .. sh + 15 of five words
+template <int SH>
+__device__ __forceinline__ v4i align16(const uint32_t (&d)[5]) {
+  v4i r;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    r[i] = SH == 0 ? (int)d[i] : SH == 4 ? (int)d[i + 1] : (int)__builtin_amdgcn_alignbyte(d[i + 1], d[i], SH & 3);
+  return r;
+}
+
+// One unit: 16 rows, the NK columns kappa = NK H + 0 .. NK - 1 of each n.
+// STAGE 1 reads t reversed (step d goes down in memory), STAGE 2 ascending.
+// a0 / astep: LDS byte offset of the lane's row operand at d = 0 and its
+// change per step; valid for d <= K, zeros from zoff otherwise.  A step's
+// operands are read while the step before multiplies.
+struct ToeplitzOps {
+  v4i a[4];
+  uint32_t t[4][5];
+};
+
+template <int STAGE, int NK, int H>
+__device__ __forceinline__ void toeplitz_unit(v4i (&acc)[NK][7], const uint8_t* sm, int len, int K, int a0, int astep,
+                                              int aplane, int zoff, int b0, int bplane) {
+#pragma unroll
+  for (int x = 0; x < NK; ++x)
+#pragma unroll
+    for (int d = 0; d < 7; ++d) acc[x][d] = v4i{0, 0, 0, 0};
+  constexpr int bstep = STAGE == 1 ? -64 : 64;
+  constexpr int SH0 = (STAGE == 1 ? 3 : 4) - NK * H, SH1 = NK == 2 ? SH0 - 1 : SH0;
+  auto load = [&](ToeplitzOps& o, int d) {
+    const bool ok = d <= K;
+    const int ad = ok ? a0 + d * astep : zoff, ap = ok ? aplane : 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) o.a[q] = *reinterpret_cast<const v4i*>(sm + ad + q * ap);
+#pragma unroll
+    for (int y = 0; y < 4; ++y) {
+      const uint32_t* tw = reinterpret_cast<const uint32_t*>(sm + b0 + d * bstep + y * bplane);
+#pragma unroll
+      for (int i = 0; i < 5; ++i) o.t[y][i] = tw[i];
+    }
+  };
+  auto mul = [&](const ToeplitzOps& o) {
+#pragma unroll
+    for (int y = 0; y < 4; ++y) {
+      const v4i f0 = align16<SH0>(o.t[y]), f1 = align16<SH1>(o.t[y]);
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        acc[0][x + y] = __builtin_amdgcn_mfma_i32_16x16x64_i8(o.a[x], f0, acc[0][x + y], 0, 0, 0);
+        if constexpr (NK == 2)
+          acc[1][x + y] = __builtin_amdgcn_mfma_i32_16x16x64_i8(o.a[x], f1, acc[1][x + y], 0, 0, 0);
+      }
+    }
+  };
+  ToeplitzOps p, q;
+  load(p, 0);
+  for (int d = 0; d < len; d += 2) {
+    load(q, min(d + 1, len - 1));
+    mul(p);
+    if (d + 1 < len) {
+      load(p, min(d + 2, len - 1));
+      mul(q);
+    }
+  }
+}
+
+// LDS of a workgroup and its rows, as the stages see them
+struct InterpLds {
+  uint8_t* sm;
+  const int32_t *row, *n1, *blk, *u;
+  const int64_t* val;
+  int TP, Dp, zoff, t0;  // t0: byte offset of the stage's planes of t
+};
+
+// One stage on one unit: the products, then e = b psi into the job's planes
+// (stage 1) or the coefficients c = b / phi to memory (stage 2).
+template <int STAGE, int NK, int H>
+__device__ __forceinline__ void interp_unit(const InterpLds& S, int tile, int lane, const uint32_t* scale, uint32_t* ws,
+                                            uint32_t k56, const PrimeC& c) {
+  const int n = lane & 15, kg = lane >> 4;
+  const int row = S.row[16 * tile + n];
+  const int jj = row < 0 ? 0 : row >> 16, K = row < 0 ? -1 : row & 0xffff;
+  const int len = __builtin_amdgcn_readfirstlane((S.row[16 * tile] & 0xffff) + 1);
+  const int dp = 64 * S.blk[jj];
+  v4i acc[NK][7];
+  // input blocks K, K - 1, .. of u, or dp / 64 - 1 - K and up of e
+  const int a0 = S.u[jj] + (STAGE == 1 ? 64 * K : 4 * dp + dp - 64 - 64 * K) + 16 * kg;
+  const int b0 = S.t0 + (STAGE == 1 ? S.Dp + 64 : 60) - 4 * n + 16 * kg;
+  toeplitz_unit<STAGE, NK, H>(acc, S.sm, len, K, a0, STAGE == 1 ? -64 : 64, dp, S.zoff, b0, S.TP);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int orow = S.row[16 * tile + 4 * kg + r];
+    if (orow < 0) continue;
+    const int oj = orow >> 16, oK = orow & 0xffff, n1 = S.n1[oj], ob = S.blk[oj];
+    const int k0 = 64 * (STAGE == 1 ? oK : ob - 1 - oK) + 4 * n + NK * H;
+    uint32_t w[NK];
+#pragma unroll
+    for (int e = 0; e < NK; ++e) {
+      const uint32_t b = fold_bytes(acc[e][0][r], acc[e][1][r], acc[e][2][r], acc[e][3][r], acc[e][4][r],
+                                    acc[e][5][r], acc[e][6][r], k56, c);
+      w[e] = k0 + e < n1 ? mmulc(b, scale[k0 + e], c.p, c.pinv) : 0u;
+    }
+    if constexpr (STAGE == 1) {
+      uint8_t* E = S.sm + S.u[oj] + 256 * ob + k0;
+#pragma unroll
+      for (int e = 0; e < NK; ++e) w[e] = balance4(w[e]);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if constexpr (NK == 2)
+          *reinterpret_cast<uint16_t*>(E + q * 64 * ob) =
+              (uint16_t)(((w[0] >> (8 * q)) & 0xffu) | (((w[1] >> (8 * q)) & 0xffu) << 8));
+        else
+          E[q * 64 * ob] = (uint8_t)(w[0] >> (8 * q));
+      }
+    } else {
+      uint32_t* C = ws + S.val[oj];
+#pragma unroll
+      for (int e = 0; e < NK; ++e)
+        if (k0 + e < n1) C[k0 + e] = from_mont(w[e], c);
+    }
+  }
+}
+
+template <int STAGE>
+__device__ __forceinline__ void interp_stage(const InterpLds& S, int ntile, int wave, int lane, const uint32_t* scale,
+                                             uint32_t* ws, uint32_t k56, const PrimeC& c) {
+  if (ntile == 1) {  // one tile: a column class per wavefront
+    switch (wave) {
+      case 0: interp_unit<STAGE, 1, 0>(S, 0, lane, scale, ws, k56, c); break;
+      case 1: interp_unit<STAGE, 1, 1>(S, 0, lane, scale, ws, k56, c); break;
+      case 2: interp_unit<STAGE, 1, 2>(S, 0, lane, scale, ws, k56, c); break;
+      default: interp_unit<STAGE, 1, 3>(S, 0, lane, scale, ws, k56, c); break;
+    }
+    return;
+  }
+  // units (tile, column pair) longest first, dealt to the wavefronts forth and back
+  for (int x = wave, turn = 0; x < 2 * ntile;
+       ++turn, x = turn * IM_WAVES + ((turn & 1) ? IM_WAVES - 1 - wave : wave)) {
+    if (x & 1) interp_unit<STAGE, 2, 1>(S, x >> 1, lane, scale, ws, k56, c);
+    else interp_unit<STAGE, 2, 0>(S, x >> 1, lane, scale, ws, k56, c);
+  }
+}
+
+__global__ __launch_bounds__(IM_THREADS) void k_interp_mfma(const PrimeC* primes, const ResJob* jobs,
+                                                            const int32_t* job_list, const int32_t* gstart,
+                                                            const int64_t* gprefix, int ngroups, uint32_t* ws,
+                                                            uint32_t* zero_word) {
+  extern __shared__ uint4 im_sm[];
+  __shared__ int64_t sPts[IM_JOBS], sVal[IM_JOBS];
+  __shared__ int32_t sN1[IM_JOBS], sBlk[IM_JOBS], sU[IM_JOBS];
+  __shared__ int32_t sRow[IM_MAXROWS + 16];  // job << 16 | block distance K; -1 past the last row
+  if (blockIdx.x == 0 && threadIdx.x == 0) *zero_word = 0u;  // abnormal counter, read by now
+  uint8_t* sm = reinterpret_cast<uint8_t*>(im_sm);
+  const int g = find_job(gprefix, ngroups, blockIdx.x);
+  const int pi = (int)(blockIdx.x - gprefix[g]);
+  const int s0 = gstart[g], nj = gstart[g + 1] - s0;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const PrimeC c = primes[pi];
+  if (tid < nj) {
+    const ResJob& J = jobs[job_list[s0 + tid]];
+    const bool on = J.k > pi;  // jobs of the group with fewer primes sit this one out
+    sN1[tid] = on ? J.D + 1 : 0;
+    sBlk[tid] = on ? (J.D + 64) / 64 : 0;
+    sPts[tid] = J.pts_off + (int64_t)pi * (J.D + 1);
+    sVal[tid] = J.val_off + (int64_t)pi * (J.D + 1);
+  }
+  for (int r = tid; r < IM_MAXROWS + 16; r += IM_THREADS) sRow[r] = -1;
+  __syncthreads();
+  int nrows = 0, mxb = 0;
+  for (int j = 0; j < nj; ++j) { nrows += sBlk[j]; mxb = max(mxb, sBlk[j]); }
+  const int Dp = 64 * mxb, TP = im_tplane(Dp);
+  const bool both = im_both(Dp);  // room for t in both orders
+  const int zoff = (both ? 8 : 4) * TP, ubase = zoff + 16;
+  // rows by K (the number of input blocks before the last one that an output
+  // block reads) from the top, so that a tile's rows need about the same steps
+  for (int x = tid; x < nj * mxb; x += IM_THREADS) {
+    const int j = x / mxb, K = x % mxb;
+    if (K >= sBlk[j]) continue;
+    int pos = 0;
+    for (int i = 0; i < nj; ++i) pos += max(0, sBlk[i] - (K + 1)) + (i < j && sBlk[i] > K ? 1 : 0);
+    sRow[pos] = j << 16 | K;
+  }
+  if (tid < nj) {
+    int off = ubase;
+    for (int i = 0; i < tid; ++i) off += 512 * sBlk[i];
+    sU[tid] = off;
+  }
+  if (tid < 4) reinterpret_cast<uint32_t*>(sm + zoff)[tid] = 0u;
+  const uint32_t* ip = g_iphi + (size_t)pi * (MAX_D + 1);
+  const uint32_t* ps = g_psi + (size_t)pi * (MAX_D + 1);
+  const int8_t* tq = g_tq + (size_t)pi * 4 * IM_TROW;
+  // t reversed: the word at byte y holds t at Dp + 67 - y and the three below
+  for (int y = 4 * tid; y < TP; y += 4 * IM_THREADS) {
+    const int x0 = Dp + 64 - y;
+    const bool in = x0 >= 0 && x0 < IM_TROW;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t w = in ? *reinterpret_cast<const uint32_t*>(tq + (size_t)q * IM_TROW + x0) : 0u;
+      *reinterpret_cast<uint32_t*>(sm + q * TP + y) = __builtin_amdgcn_perm(0u, w, 0x00010203u);
+    }
+  }
+  // t ascending: the word at byte y holds t at y - 64 and the three above
+  auto load_ascending = [&](int at) {
+    for (int y = 4 * tid; y < TP; y += 4 * IM_THREADS) {
+      const int x0 = y - 64;
+      const bool in = x0 >= 0 && x0 < IM_TROW;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        *reinterpret_cast<uint32_t*>(sm + at + q * TP + y) =
+            in ? *reinterpret_cast<const uint32_t*>(tq + (size_t)q * IM_TROW + x0) : 0u;
+    }
+  };
+  if (both) load_ascending(4 * TP);
+  __syncthreads();
+  // u = v / phi
+  for (int j = 0; j < nj; ++j) {
+    const int n1 = sN1[j], dp = 64 * sBlk[j];
+    const uint32_t* V = ws + sPts[j];
+    for (int i = 4 * tid; i < dp; i += 4 * IM_THREADS) {
+      uint32_t w[4], pl[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        w[e] = i + e < n1 ? balance4(mmulc(canon(V[i + e], c.p), ip[i + e], c.p, c.pinv)) : 0u;
+      split_planes(w, pl);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) *reinterpret_cast<uint32_t*>(sm + sU[j] + q * dp + i) = pl[q];
+    }
+  }
+  __syncthreads();
+  const uint32_t k56 = fold_const(c);
+  const int ntile = (nrows + 15) / 16;
+  InterpLds S{sm, sRow, sN1, sBlk, sU, sVal, TP, Dp, zoff, 0};
+  interp_stage<1>(S, ntile, wave, lane, ps, ws, k56, c);
+  __syncthreads();
+  if (!both) {
+    load_ascending(0);
+    __syncthreads();
+  }
+  S.t0 = both ? 4 * TP : 0;
+  interp_stage<2>(S, ntile, wave, lane, ip, ws, k56, c);
+}
+
+size_t interp_mfma_lds(int max_D, int blocks) {
+  const int Dp = (max_D + 64) / 64 * 64;
+  return (im_both(Dp) ? 8 : 4) * (size_t)im_tplane(Dp) + 16 + 512 * (size_t)blocks;
+}
+
+hipError_t configure_interp_mfma() {
+  return hipFuncSetAttribute((const void*)k_interp_mfma, hipFuncAttributeMaxDynamicSharedMemorySize, 152 * 1024);
+}
+
+void launch_points_init(hipStream_t s) {
+  hipLaunchKernelGGL(k_points_init, dim3(KMAX / 64), dim3(64), 0, s, global_crt_tables().primes);
+}
+
+const uint32_t* points_table() {
+  static const uint32_t* cache[64] = {nullptr};
+  int dev = 0;
+  (void)hipGetDevice(&dev);
+  if (dev >= 0 && dev < 64 && cache[dev]) return cache[dev];
+  void* p = nullptr;
+  (void)hipGetSymbolAddress(&p, HIP_SYMBOL(g_points));
+  if (dev >= 0 && dev < 64) cache[dev] = (const uint32_t*)p;
+  return (const uint32_t*)p;
+}
+
+void launch_interp_mfma(const ResJob* jobs_d, const int32_t* job_list_d, const int32_t* gstart_d,
+                        const int64_t* gprefix_d, int ngroups, int64_t nblocks, size_t lds, uint32_t* ws,
+                        uint32_t* zero_word, hipStream_t s) {
+  if (nblocks <= 0) return;
+  hipLaunchKernelGGL(k_interp_mfma, dim3((unsigned)nblocks), dim3(IM_THREADS), lds, s, global_crt_tables().primes,
+                     jobs_d, job_list_d, gstart_d, gprefix_d, ngroups, ws, zero_word);
+}
+
+}  // namespace snc

@@ -147,10 +147,11 @@ __device__ uint32_t res_general(uint32_t* F, int m, uint32_t* G, int n, const Pr
 // MAXY: the largest y-degree of the instances this variant runs (the size
 // of the per-lane value arrays)
 template <int MAXY>
-__device__ void general_instance(const ResJob& J, const RowDesc* rows, uint32_t* ws, int pi, int j) {
+__device__ void general_instance(const ResJob& J, const RowDesc* rows, uint32_t* ws, const uint32_t* points, int pi,
+                                 int j) {
   const PrimeC c = g_primes[pi];
   const uint32_t* r = ws + J.res_off + (int64_t)pi * J.T;
-  const uint32_t X = to_mont((uint32_t)j, c);
+  const uint32_t X = point_mont(points, pi, j, c);
   const RowDesc* ra = rows + J.rows_off;
   const RowDesc* rb = ra + J.rstride;
   uint32_t F[MAXY + 1], G[MAXY + 1];
@@ -167,7 +168,7 @@ __device__ void general_instance(const ResJob& J, const RowDesc* rows, uint32_t*
 // job, prefix sums over the njobs jobs).
 __global__ void k_elim_general(const ResJob* jobs, const RowDesc* rows, uint32_t* ws,
                                const uint32_t* abn_count, const AbnEntry* list, uint32_t cap,
-                               const int64_t* inst_prefix, int njobs) {
+                               const int64_t* inst_prefix, int njobs, const uint32_t* points) {
   const uint32_t cnt = *abn_count;
   if (cnt == 0) return;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -176,7 +177,7 @@ __global__ void k_elim_general(const ResJob* jobs, const RowDesc* rows, uint32_t
     for (int64_t idx = t0; idx < cnt; idx += stride) {
       const AbnEntry e = list[idx];
       const ResJob J = jobs[e.job];
-      general_instance<MAXY_FAST>(J, rows, ws, e.prime, e.point);
+      general_instance<MAXY_FAST>(J, rows, ws, points, e.prime, e.point);
     }
     return;
   }
@@ -187,7 +188,7 @@ __global__ void k_elim_general(const ResJob* jobs, const RowDesc* rows, uint32_t
     const int64_t li = idx - inst_prefix[jj];
     const int pi = (int)(li / (J.D + 1)), j = (int)(li % (J.D + 1));
     if (J.m > MAXY_FAST) continue;  // computed whole by the general kernel, never marked
-    if (ws[J.pts_off + (int64_t)pi * (J.D + 1) + j] == ABN_MARK) general_instance<MAXY_FAST>(J, rows, ws, pi, j);
+    if (ws[J.pts_off + (int64_t)pi * (J.D + 1) + j] == ABN_MARK) general_instance<MAXY_FAST>(J, rows, ws, points, pi, j);
   }
 }
 
@@ -198,18 +199,18 @@ void launch_elim_general(const ResJob* jobs_d, const RowDesc* rows_d, uint32_t* 
   int64_t blocks = ((int64_t)cap + 63) / 64;
   blocks = blocks < 1 ? 1 : blocks > 256 * 16 ? 256 * 16 : blocks;
   hipLaunchKernelGGL(k_elim_general, dim3((unsigned)blocks), dim3(64), 0, s, jobs_d, rows_d, ws, abn_count, abn_list,
-                     cap, inst_prefix_d, njobs);
+                     cap, inst_prefix_d, njobs, points_table());
 }
 
 __global__ void k_elim_general_all(const ResJob* jobs, const int32_t* job_list,
                                    const int64_t* prefix, int njobs, int64_t ninst,
-                                   const RowDesc* rows, uint32_t* ws) {
+                                   const RowDesc* rows, uint32_t* ws, const uint32_t* points) {
   for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < ninst;
        idx += (int64_t)gridDim.x * blockDim.x) {
     const int jj = find_job(prefix, njobs, idx);
     const ResJob J = jobs[job_list[jj]];
     const int64_t li = idx - prefix[jj];
-    general_instance<MAXY_GEN>(J, rows, ws, (int)(li / (J.D + 1)), (int)(li % (J.D + 1)));
+    general_instance<MAXY_GEN>(J, rows, ws, points, (int)(li / (J.D + 1)), (int)(li % (J.D + 1)));
   }
 }
 
@@ -220,7 +221,7 @@ void launch_elim_general_all(const ResJob* jobs_d, const int32_t* job_list_d,
   int64_t blocks = (ninst + 63) / 64;
   if (blocks > 8192) blocks = 8192;
   hipLaunchKernelGGL(k_elim_general_all, dim3((unsigned)blocks), dim3(64), 0, s, jobs_d, job_list_d,
-                     inst_prefix_d, njobs, ninst, rows_d, ws);
+                     inst_prefix_d, njobs, ninst, rows_d, ws, points_table());
 }
 
 // ---------------------------------------------------------------------------
@@ -266,17 +267,16 @@ __global__ void k_ifact_init() {
 void launch_ffact_init(hipStream_t s);
 
 // Montgomery coefficients of x^0 .. x^63 of F_j = (x - 64j)(x - 64j - 1) ... (x - 64j - 63)
-// (x^64 implied) for every prime and the blocks j < IW_NBLK of the one-wavefront interpolation
-constexpr int IW_NBLK = (IW_MAXD + 1) / 64;
-static_assert(64 * IW_NBLK == IW_MAXD + 1, "whole blocks");
-__device__ uint32_t g_fblk[(int64_t)KMAX * IW_NBLK * 64];
+// (x^64 implied) for every prime and the blocks j < FB_NBLK
+constexpr int FB_NBLK = 64;
+__device__ uint32_t g_fblk[(int64_t)KMAX * FB_NBLK * 64];
 
 __device__ __forceinline__ uint32_t lane_shr1(uint32_t v);
 
 // one wavefront per (prime, block): F <- F (x - (64 j + t)) for t = 0..63,
 // coefficient of x^lane in lane (the x^64 term leaves lane 63 and is implied)
 __global__ __launch_bounds__(64) void k_fblk_init() {
-  const int pi = blockIdx.x / IW_NBLK, j = blockIdx.x % IW_NBLK, lane = threadIdx.x;
+  const int pi = blockIdx.x / FB_NBLK, j = blockIdx.x % FB_NBLK, lane = threadIdx.x;
   const PrimeC c = g_primes[pi];
   uint32_t f = lane == 0 ? c.r1 : 0u;
   for (int t = 0; t < 64; ++t) {
@@ -284,12 +284,12 @@ __global__ __launch_bounds__(64) void k_fblk_init() {
     const uint32_t fprev = lane_shr1(f);
     f = canon(redc((uint64_t)nk * f + ((uint64_t)fprev << 32), c.p, c.pinv), c.p);
   }
-  g_fblk[((int64_t)pi * IW_NBLK + j) * 64 + lane] = f;
+  g_fblk[((int64_t)pi * FB_NBLK + j) * 64 + lane] = f;
 }
 
 void launch_ifact_init(hipStream_t s) {
   hipLaunchKernelGGL(k_ifact_init, dim3(KMAX / 64), dim3(64), 0, s);
-  hipLaunchKernelGGL(k_fblk_init, dim3(KMAX * IW_NBLK), dim3(64), 0, s);
+  hipLaunchKernelGGL(k_fblk_init, dim3(KMAX * FB_NBLK), dim3(64), 0, s);
   launch_ffact_init(s);
 }
 
@@ -395,8 +395,8 @@ __global__ __launch_bounds__(INTERP_THREADS) void k_interp(const ResJob* jobs, c
     const int len = min(IB, n1 - b0);
     const uint32_t nk = to_mont(c.p - (uint32_t)(b0 + lane), c);  // -(b0 + lane)
     uint32_t q = lane == 0 ? bcast(a, len - 1) : 0u;
-    const bool ftab = ob < IW_NBLK;  // uniform
-    uint32_t f = ftab ? g_fblk[((int64_t)pi * IW_NBLK + ob) * 64 + lane] : (lane == 0 ? c.r1 : 0u);
+    const bool ftab = ob < FB_NBLK;  // uniform
+    uint32_t f = ftab ? g_fblk[((int64_t)pi * FB_NBLK + ob) * 64 + lane] : (lane == 0 ? c.r1 : 0u);
     for (int s = 0; s < IB; ++s) {
       if (!ftab) {
         const uint32_t fprev = lane_shr1(f);  // F <- F (x - (b0 + s))
@@ -442,265 +442,6 @@ __global__ __launch_bounds__(INTERP_THREADS) void k_interp(const ResJob* jobs, c
     dP = dN;
   }
   for (int t = tid; t < n1; t += INTERP_THREADS) C[t] = from_mont(Pa[IPAD + t], c);
-}
-
-// ---------------------------------------------------------------------------
-// One-wavefront interpolation (batches with many (resultant, prime) pairs and
-// degree bounds up to IW_MAXD): the same Newton convolution, Newton blocks and
-// blockwise expansion as k_interp, by one wavefront per (resultant, prime)
-// with no barriers between wavefronts.  LDS holds only the sliding operand:
-// w_j = (-1)^j / j! for the convolution, then P, updated in place from its top
-// block down (a block's new values depend on its own and the next lower
-// block's old ones).  The uniform operand, 64 words, is staged in LDS too and
-// read four words at a time at one address for the whole wavefront (a
-// broadcast; no vector-unit instruction per word), shared by two output
-// blocks; the Newton blocks Q_j (two Horner steps per iteration) go to the
-// workspace, the F_j come from their table.
-// ---------------------------------------------------------------------------
-// s1 += sum_q U[q] S1[-q], and (TWO) s2 += sum_q U[q] S2[-q], U in LDS
-// (16-byte aligned), sixteen products per reduction (fold16).
-template <bool TWO>
-__device__ __forceinline__ void toeplitz64_w(uint32_t& s1, uint32_t& s2, const uint32_t* U, const uint32_t* S1,
-                                             const uint32_t* S2, const PrimeC& c) {
-#pragma unroll
-  for (int g = 0; g < 64; g += 16) {
-    const uint4* U4 = reinterpret_cast<const uint4*>(U + g);
-    const uint4 ua = U4[0], ub = U4[1], uc = U4[2], ud = U4[3];
-    const uint32_t w16[16] = {ua.x, ua.y, ua.z, ua.w, ub.x, ub.y, ub.z, ub.w,
-                              uc.x, uc.y, uc.z, uc.w, ud.x, ud.y, ud.z, ud.w};
-    uint64_t a1 = 0, a2 = 0;
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const uint64_t w = w16[q];
-      a1 += w * S1[-(g + q)];
-      if constexpr (TWO) a2 += w * S2[-(g + q)];
-    }
-    s1 = fold16(s1, a1, c);
-    if constexpr (TWO) s2 = fold16(s2, a2, c);
-  }
-}
-
-// Two adjacent outputs per lane: with P at word t (t even) and
-// V_j = P[1 - j], so += sum_{q<64} U[q] V_q and se += sum_{q<64} U[q] V_{q+1}:
-// the Toeplitz sums of outputs t + 1 and t.  One read of the two words
-// P[-2i], P[1-2i] = V_{2i+1}, V_{2i} feeds four products, so the sliding
-// operand costs half the LDS bytes of one output per lane; sixteen products
-// per reduction (fold16), the same sums as toeplitz64_w.
-__device__ __forceinline__ void toeplitz64_pair(uint32_t& se, uint32_t& so, const uint32_t* U, const uint32_t* P,
-                                                const PrimeC& c) {
-  const uint2* P2 = reinterpret_cast<const uint2*>(P);  // P2[-i] = (V_{2i+1}, V_{2i})
-  uint2 cur = P2[0];
-#pragma unroll
-  for (int g = 0; g < 64; g += 16) {
-    uint32_t V[18];  // V[k] = V_{g+k}
-    V[0] = cur.y;
-    V[1] = cur.x;
-#pragma unroll
-    for (int i = 1; i <= 8; ++i) {
-      const uint2 x = P2[-(g / 2 + i)];
-      V[2 * i] = x.y;
-      V[2 * i + 1] = x.x;
-    }
-    cur = make_uint2(V[17], V[16]);
-    const uint4* U4 = reinterpret_cast<const uint4*>(U + g);
-    const uint4 ua = U4[0], ub = U4[1], uc = U4[2], ud = U4[3];
-    const uint32_t w16[16] = {ua.x, ua.y, ua.z, ua.w, ub.x, ub.y, ub.z, ub.w,
-                              uc.x, uc.y, uc.z, uc.w, ud.x, ud.y, ud.z, ud.w};
-    uint64_t ao = 0, ae = 0;
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const uint64_t w = w16[q];
-      ao += w * V[q];
-      ae += w * V[q + 1];
-    }
-    so = fold16(so, ao, c);
-    se = fold16(se, ae, c);
-  }
-}
-
-// Newton block -> monomial: Q = sum_{s < len} a_{b0+s} prod_{t < s} (x - (b0 + t)),
-// a_{b0+s} in lane s, by Horner's rule from the top with two steps per
-// iteration:
-//   Q <- (Q (x - c1) + a_k)(x - c2) + a_{k-1}
-//      = Q (x^2 + B x + A) + a_k x + (a_{k-1} - c2 a_k),
-// c1 = b0 + k, c2 = c1 - 1, A = c1 c2, B = -(c1 + c2): per coefficient two
-// products and one reduction, Q[i-1] and Q[i-2] by two lane shifts, instead
-// of two products and two reductions.  Lane it first computes iteration it's
-// constants (Montgomery forms of A and B, the corrections of coefficients 0
-// and 1) into K; a is staged in La.  La: 64 words, K: 4 x 32 words, 16-byte
-// aligned; one wavefront (the barriers order its own LDS accesses).  The sum
-// below REDC stays under 2p^2 + 2p 2^32 + 2^32 p < 2^64, its result under 4p.
-__device__ __forceinline__ uint32_t newton_block2(uint32_t a, int b0, int len, int lane, const PrimeC& c,
-                                                  uint32_t* La, uint32_t* K) {
-  __syncthreads();
-  La[lane] = a;
-  __syncthreads();
-  const int nit = (len - 1) / 2;
-  if (lane < nit) {
-    const int k = len - 2 - 2 * lane;                      // the iteration's first Horner index, >= 1
-    const uint32_t c1 = (uint32_t)(b0 + k), c2 = c1 - 1;  // below 2^13: c1 c2 < p
-    const uint32_t ak = La[k], ak1 = La[k - 1];
-    uint4 v;
-    v.x = to_mont(c1 * c2, c);
-    v.y = to_mont(c.p - c1 - c2, c);
-    v.z = msub(ak1, mmulc(to_mont(c2, c), ak, c.p, c.pinv), c.p);
-    v.w = ak;
-    reinterpret_cast<uint4*>(K)[lane] = v;
-  }
-  __syncthreads();
-  uint32_t q = lane == 0 ? La[len - 1] : 0u;
-  for (int it = 0; it < nit; ++it) {
-    const uint4 v = reinterpret_cast<const uint4*>(K)[it];
-    const uint32_t q1 = lane_shr1(q);
-    const uint32_t q2 = lane_shr1(q1) + (lane == 0 ? v.z : lane == 1 ? v.w : 0u);
-    q = canon(redc((uint64_t)v.x * q + (uint64_t)v.y * q1 + ((uint64_t)q2 << 32), c.p, c.pinv), c.p);
-  }
-  if ((len - 1) & 1) {  // the last step alone, k = 0
-    const uint32_t nk = to_mont(c.p - (uint32_t)b0, c);
-    const uint32_t qprev = lane_shr1(q) + (lane == 0 ? La[0] : 0u);
-    q = canon(redc((uint64_t)nk * q + ((uint64_t)qprev << 32), c.p, c.pinv), c.p);
-  }
-  return q;
-}
-
-// zero words below index 0 of k_interp_w's sliding operand: the paired
-// outputs of the Newton coefficients reach 127 words below an input block
-constexpr int IPAD_W = 128;
-
-__global__ __launch_bounds__(64) void k_interp_w(const ResJob* jobs, const int32_t* job_list, const int64_t* prefix,
-                                                 int njobs, uint32_t* ws, uint32_t* zero_word) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) *zero_word = 0u;  // abnormal counter, read by now
-  extern __shared__ uint4 S4[];  // [IPAD_W + Dp] sliding operand, then [64] uniform operand
-  uint32_t* S = reinterpret_cast<uint32_t*>(S4);
-  const int64_t b = blockIdx.x;
-  const int jj = find_job(prefix, njobs, b);
-  const ResJob J = jobs[job_list[jj]];
-  const int pi = (int)(b - prefix[jj]);
-  const PrimeC c = g_primes[pi];
-  const int n1 = J.D + 1;
-  const int nblk = (n1 + 63) / 64;
-  const int Dp = nblk * 64;
-  const uint32_t* V = ws + J.pts_off + (int64_t)pi * n1;
-  uint32_t* C = ws + J.val_off + (int64_t)pi * n1;
-  uint32_t* Qg = ws + J.nq_off + (int64_t)pi * Dp;
-  const uint32_t* IF = g_ifact + (int64_t)pi * (MAX_D + 1);
-  const uint32_t* FB = g_fblk + (int64_t)pi * IW_NBLK * 64;
-  const int lane = threadIdx.x;
-  uint32_t* U = S + IPAD_W + Dp;  // 16-byte aligned: IPAD_W and Dp are multiples of 64
-  uint32_t* K = U + 64;           // constants of the Newton blocks' iterations (128 words)
-  // the uniform operand of the next Toeplitz sums (one wavefront: the
-  // barriers only order its own LDS accesses)
-  auto stage_u = [&](uint32_t v) {
-    __syncthreads();
-    U[lane] = v;
-    __syncthreads();
-  };
-  for (int t = lane; t < IPAD_W + Dp; t += 64) {
-    const int j = t - IPAD_W;
-    uint32_t w = 0;
-    if (j >= 0 && j < n1) {
-      const uint32_t f = IF[j];
-      w = (j & 1) ? mneg(f, c.p) : f;
-    }
-    S[t] = w;
-  }
-  __syncthreads();
-  // u_{64 ib + lane} = v / (64 ib + lane)! from the loaded pair (v, 1/i!); the
-  // loads of the next input block are issued before the current block's
-  // Toeplitz sums, which hide their latency
-  uint32_t vn = 0, fn = 0;
-  auto load_u = [&](int ib) {
-    const int i = 64 * ib + lane;
-    vn = i < n1 ? V[i] : 0u;
-    fn = i < n1 ? IF[i] : 0u;
-  };
-  auto uval = [&]() { return mmulc(canon(vn, c.p), fn, c.p, c.pinv); };
-  for (int ob = 0; ob < nblk; ob += 2) {
-    const int b0 = ob * 64;
-    const uint32_t* w1 = S + IPAD_W + b0 + lane;
-    uint32_t s1 = 0, s2 = 0;
-    load_u(0);
-    if (ob + 1 < nblk) {
-      // lane l: outputs b0 + 2l and b0 + 2l + 1; the input block ob + 1
-      // meets only the upper output block (the zeros below index 0 give the
-      // lower lanes nothing)
-      const int te = b0 + 2 * lane;
-      uint32_t se = 0, so = 0;
-      for (int ib = 0; ib <= ob + 1; ++ib) {
-        stage_u(uval());
-        if (ib <= ob) load_u(ib + 1);
-        toeplitz64_pair(se, so, U, S + IPAD_W + te - 64 * ib, c);
-      }
-      // back to one output block per lane: b0 + lane and b0 + 64 + lane
-      __syncthreads();
-      reinterpret_cast<uint2*>(K)[lane] = make_uint2(se, so);
-      __syncthreads();
-      s1 = K[lane];
-      s2 = K[64 + lane];
-      Qg[b0 + lane] = newton_block2(s1, b0, 64, lane, c, U, K);
-      Qg[b0 + 64 + lane] = newton_block2(s2, b0 + 64, min(64, n1 - b0 - 64), lane, c, U, K);
-    } else {
-      uint32_t dummy = 0;
-      for (int ib = 0; ib <= ob; ++ib) {
-        stage_u(uval());
-        if (ib < ob) load_u(ib + 1);
-        toeplitz64_w<false>(s1, dummy, U, w1 - 64 * ib, w1, c);
-      }
-      Qg[b0 + lane] = newton_block2(s1, b0, min(64, n1 - b0), lane, c, U, K);
-    }
-  }
-  __syncthreads();
-  // P = Q_{nblk-1}; P <- P F_j + Q_j for j = nblk-2 .. 0, in place from the top block down
-  const int lastb = (nblk - 1) * 64;
-  const int lastlen = n1 - lastb;
-  for (int t = lane; t < IPAD_W + Dp; t += 64) {
-    const int x = t - IPAD_W;
-    S[t] = (x >= 0 && x < lastlen) ? Qg[lastb + x] : 0u;
-  }
-  __syncthreads();
-  int dP = lastlen - 1;
-  for (int j = nblk - 2; j >= 0; --j) {
-    const int dN = dP + 64;
-    const int nob = dN / 64 + 1;
-    stage_u(FB[j * 64 + lane]);
-    const uint32_t qj = Qg[j * 64 + lane];
-    for (int ob = nob - 1; ob >= 0; ob -= 2) {
-      if (ob >= 1) {
-        // blocks ob - 1 and ob, lane l: outputs t = te and te + 1
-        const int te = (ob - 1) * 64 + 2 * lane;
-        uint32_t* pe = S + IPAD_W + te;  // P[t - i] = pe[-i]
-        const uint2 x64 = *reinterpret_cast<const uint2*>(pe - 64);  // x^64 term of F_j
-        uint32_t se = x64.x, so = x64.y;
-        if (ob == 1 && lane < 32) {  // outputs below 64: + Q_j
-          const uint2 q2 = *reinterpret_cast<const uint2*>(Qg + j * 64 + te);
-          se = madd(se, q2.x, c.p);
-          so = madd(so, q2.y, c.p);
-        }
-        toeplitz64_pair(se, so, U, pe, c);
-        __syncthreads();  // every lane's reads of the old blocks before the new values land
-        *reinterpret_cast<uint2*>(pe) = make_uint2(se, so);
-        __syncthreads();
-      } else {
-        const uint32_t* p1 = S + IPAD_W + lane;  // P[t - i] = p1[-i]
-        uint32_t s1 = madd(p1[-64], qj, c.p);    // x^64 term of F_j, + Q_j
-        uint32_t dummy = 0;
-        toeplitz64_w<false>(s1, dummy, U, p1, p1, c);
-        __syncthreads();
-        S[IPAD_W + lane] = s1;
-        __syncthreads();
-      }
-    }
-    dP = dN;
-  }
-  for (int t = lane; t < n1; t += 64) C[t] = from_mont(S[IPAD_W + t], c);
-}
-
-void launch_interp_w(const ResJob* jobs_d, const int32_t* job_list_d, const int64_t* prefix_d, int njobs,
-                     int64_t nblocks, int max_D, uint32_t* ws, uint32_t* zero_word, hipStream_t s) {
-  if (nblocks <= 0) return;
-  const size_t lds = (size_t)(IPAD_W + (max_D + 64) / 64 * 64 + 64 + 128) * sizeof(uint32_t);
-  hipLaunchKernelGGL(k_interp_w, dim3((unsigned)nblocks), dim3(64), lds, s, jobs_d, job_list_d, prefix_d, njobs,
-                     ws, zero_word);
 }
 
 // ---------------------------------------------------------------------------

@@ -75,7 +75,7 @@ void layout_batch(const std::vector<ResPlan>& plans, BatchLayout& lay) {
   lay.rows_off = off; off = align256(off + sizeof(RowDesc) * nrows);
   lay.pref_red = off; off = align256(off + 8 * (NJ + 1));
   lay.pref_interp = off; off = align256(off + 8 * (NJ + 1));
-  lay.pref_interp_blk = off; off = align256(off + 8 * (NJ + 1));
+  lay.start_im = off; off = align256(off + 4 * (NJ + 1));
   // one lane per coefficient pays off only when the batch's few-prime coefficients fill the device
   // (a wavefront per CU); otherwise the lanes go over the primes of each coefficient
   int64_t small_coefs = 0;
@@ -99,8 +99,7 @@ void layout_batch(const std::vector<ResPlan>& plans, BatchLayout& lay) {
   }
   lay.list_crtb = off; lay.list_crtm = off + 4 * lay.n_crtb_jobs; off = align256(off + 4 * std::max<size_t>(nbm, 1));
   lay.pref_inst = off; off = align256(off + 8 * (NJ + 1));
-  lay.pref_iw = off; off = align256(off + 8 * (NJ + 1));
-  lay.list_iw = off; off = align256(off + 4 * std::max(NJ, 1));
+  lay.list_im = off; off = align256(off + 4 * std::max(NJ, 1));
   for (int j = 0; j < NJ; ++j) {
     const ResPlan& P = plans[lay.dev[j]];
     if (P.cls >= 0) lay.n_ee_jobs[P.cls]++; else lay.n_gen_jobs++;
@@ -139,8 +138,6 @@ void layout_batch(const std::vector<ResPlan>& plans, BatchLayout& lay) {
     J.dig_off = (int64_t)w; w += align_words(n1 * P.k);
     J.acc_off = (int64_t)w;  // unused: the combine step keeps its accumulators in LDS
     lay.nb_red += (int64_t)P.k * ((P.T + 255) / 256);
-    lay.nb_interp += P.k;
-    lay.nb_interp_blk += (int64_t)P.k * ((n1 + 63) / 64);
     const int cc = lay.crt_small_on ? crt_small_class(P.k) : -1;
     if (cc >= 0) {
       lay.nb_crts[cc] += (int64_t)((n1 + 63) / 64);
@@ -161,11 +158,33 @@ void layout_batch(const std::vector<ResPlan>& plans, BatchLayout& lay) {
     lay.total_inst += (int64_t)P.k * n1;
     lay.max_D = std::max(lay.max_D, P.D);
   }
-  lay.interp_blk = NJ > 0 && interp_blk_fits(lay.max_D, lay.max_k);
-  // many (resultant, prime) pairs: one wavefront each, no barriers between wavefronts
+  // Interpolation groups: rows of several jobs fill the 16-row operand tiles,
+  // one job per workgroup keeps more workgroups in flight; jobs share one
+  // while IM_MIN_BLOCKS workgroups remain (and the group's LDS lets three
+  // share a CU).
   int64_t npairs = 0;
   for (const ResJob& J : lay.jobs) npairs += J.k;
-  lay.interp_w = NJ > 0 && !lay.interp_blk && lay.max_D <= IW_MAXD && npairs >= IW_MIN_PAIRS;
+  const int per = (int)std::min<int64_t>(IM_JOBS, std::max<int64_t>(1, npairs / IM_MIN_BLOCKS));
+  lay.im_order.resize(NJ);
+  for (int j = 0; j < NJ; ++j) lay.im_order[j] = j;
+  std::stable_sort(lay.im_order.begin(), lay.im_order.end(),
+                   [&](int x, int y) { return lay.jobs[x].D > lay.jobs[y].D; });
+  lay.im_start.assign(1, 0);
+  for (int t = 0; t < NJ;) {
+    const int top = lay.jobs[lay.im_order[t]].D;
+    int u = t, blocks = 0, kmax = 0;
+    for (; u < NJ && u - t < per; ++u) {
+      const ResJob& J = lay.jobs[lay.im_order[u]];
+      const int nb = blocks + (J.D + 64) / 64;
+      if (u > t && interp_mfma_lds(top, nb) > IM_LDS) break;
+      blocks = nb;
+      kmax = std::max(kmax, (int)J.k);
+    }
+    lay.im_lds = std::max(lay.im_lds, interp_mfma_lds(top, blocks));
+    lay.nb_interp += kmax;
+    lay.im_start.push_back(u);
+    t = u;
+  }
   // every job on the evaluation kernel's LDS variant: it reduces the inputs itself
   lay.reduce_in_eval = NJ > 0 && lay.n_gen_jobs == 0;
   for (int c = 0; c < NCLS; ++c)
@@ -261,13 +280,9 @@ void launch_pipeline(const BatchLayout& lay, uint8_t* ws, hipStream_t s, StageTi
   launch_elim_general(jobs, rows, wsw, abn_count, abn_list, lay.abn_cap, (const int64_t*)(ws + lay.pref_inst), NJ,
                       s);
   if (tm) tm->mark("elim_general", 1);
-  if (lay.interp_blk)
-    launch_interp_blk(jobs, (const int64_t*)(ws + lay.pref_interp_blk), NJ, lay.nb_interp_blk, wsw, abn_count, s);
-  else if (lay.interp_w)
-    launch_interp_w(jobs, (const int32_t*)(ws + lay.list_iw), (const int64_t*)(ws + lay.pref_iw), NJ, lay.nb_interp,
-                    lay.max_D, wsw, abn_count, s);
-  else
-    launch_interp(jobs, (const int64_t*)(ws + lay.pref_interp), NJ, lay.nb_interp, lay.max_D, wsw, abn_count, s);
+  launch_interp_mfma(jobs, (const int32_t*)(ws + lay.list_im), (const int32_t*)(ws + lay.start_im),
+                     (const int64_t*)(ws + lay.pref_interp), (int)lay.im_start.size() - 1, lay.nb_interp, lay.im_lds,
+                     wsw, abn_count, s);
   if (tm) tm->mark("interp", 1);
   }
   if (part == PIPE_TO_INTERP) return;
@@ -337,8 +352,6 @@ void fill_header(const BatchLayout& lay, const std::vector<ResPlan>& plans, cons
   RowDesc* rows = (RowDesc*)(h + lay.rows_off);
   uint32_t* coef = (uint32_t*)(h + lay.coef_off);
   int64_t* pr = (int64_t*)(h + lay.pref_red);
-  int64_t* pi = (int64_t*)(h + lay.pref_interp);
-  int64_t* pib = (int64_t*)(h + lay.pref_interp_blk);
   int64_t* pd = (int64_t*)(h + lay.pref_crtd);
   int64_t* pc = (int64_t*)(h + lay.pref_crtc);
   int64_t* pn = (int64_t*)(h + lay.pref_inst);
@@ -370,7 +383,7 @@ void fill_header(const BatchLayout& lay, const std::vector<ResPlan>& plans, cons
   int32_t* lg = (int32_t*)(h + lay.list_gen);
   int ng = 0;
   pg[0] = 0;
-  pr[0] = pi[0] = pib[0] = pd[0] = pc[0] = pn[0] = 0;
+  pr[0] = pd[0] = pc[0] = pn[0] = 0;
   size_t cw = 0;
   for (int j = 0; j < NJ; ++j) {
     const int idx = lay.dev[j];
@@ -410,8 +423,6 @@ void fill_header(const BatchLayout& lay, const std::vector<ResPlan>& plans, cons
     cw += (size_t)P.T * P.nl;
     const int64_t n1 = P.D + 1;
     pr[j + 1] = pr[j] + (int64_t)P.k * ((P.T + 255) / 256);
-    pi[j + 1] = pi[j] + P.k;
-    pib[j + 1] = pib[j] + (int64_t)P.k * ((P.D + 1 + 63) / 64);
     const int cc = lay.crt_small_on ? crt_small_class(P.k) : -1;
     if (cc >= 0) {
       ls[cc][ns[cc]] = j;
@@ -437,18 +448,16 @@ void fill_header(const BatchLayout& lay, const std::vector<ResPlan>& plans, cons
       ng++;
     }
   }
-  // the one-wavefront interpolation's jobs by degree bound, largest first (the
-  // longest wavefronts start first)
+  // the interpolation's job order, groups and their prime counts
   {
-    std::vector<int> ord(NJ);
-    for (int j = 0; j < NJ; ++j) ord[j] = j;
-    std::stable_sort(ord.begin(), ord.end(), [&](int x, int y) { return lay.jobs[x].D > lay.jobs[y].D; });
-    int32_t* li = (int32_t*)(h + lay.list_iw);
-    int64_t* pw = (int64_t*)(h + lay.pref_iw);
-    pw[0] = 0;
-    for (int t = 0; t < NJ; ++t) {
-      li[t] = ord[t];
-      pw[t + 1] = pw[t] + lay.jobs[ord[t]].k;
+    std::memcpy(h + lay.list_im, lay.im_order.data(), 4 * (size_t)NJ);
+    std::memcpy(h + lay.start_im, lay.im_start.data(), 4 * lay.im_start.size());
+    int64_t* pg2 = (int64_t*)(h + lay.pref_interp);
+    pg2[0] = 0;
+    for (size_t g = 0; g + 1 < lay.im_start.size(); ++g) {
+      int kmax = 0;
+      for (int t = lay.im_start[g]; t < lay.im_start[g + 1]; ++t) kmax = std::max(kmax, (int)lay.jobs[lay.im_order[t]].k);
+      pg2[g + 1] = pg2[g] + kmax;
     }
   }
   // a class's jobs most expensive first: a persistent launch hands out the

@@ -104,6 +104,7 @@ int ensure_device_tables(int device, std::string& err) {
   const Tables& T = tables();
   hipError_t e = configure_kernels();
   if (e == hipSuccess) e = configure_crt_mfma();
+  if (e == hipSuccess) e = configure_interp_mfma();
   if (e == hipSuccess) e = configure_gcd_kernels();
   if (e == hipSuccess) e = configure_ygcd_kernel();
   if (e != hipSuccess) { err = std::string("kernel attributes: ") + hipGetErrorString(e); return SNC_EDEVICE; }
@@ -113,9 +114,11 @@ int ensure_device_tables(int device, std::string& err) {
   launch_ifact_init(nullptr);
   launch_crt_small_init(nullptr);
   launch_crt_mfma_init(global_crt_tables(), nullptr);
+  launch_points_init(nullptr);
   e = hipDeviceSynchronize();
   if (e != hipSuccess) { err = std::string("table upload: ") + hipGetErrorString(e); return SNC_EDEVICE; }
   (void)global_crt_tables();
+  (void)points_table();
   done.insert(device);
   return SNC_OK;
 }

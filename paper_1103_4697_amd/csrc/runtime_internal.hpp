@@ -52,11 +52,12 @@ struct BatchLayout {
   std::vector<ResJob> jobs;          // device job descriptors (offsets filled)
   size_t jobs_off = 0, rows_off = 0, coef_off = 0;        // bytes
   size_t pref_red = 0, pref_interp = 0, pref_crtd = 0, pref_crtc = 0, pref_gen = 0;  // bytes
-  size_t pref_interp_blk = 0;        // bytes: block prefix of the block-parallel interpolation
   size_t pref_inst = 0;              // bytes: instance prefix k (D+1) over the jobs
-  bool interp_blk = false;           // every job fits the block-parallel interpolation
-  bool interp_w = false;             // one-wavefront interpolation (many (resultant, prime) pairs)
-  size_t pref_iw = 0, list_iw = 0;   // bytes: its job list (degree bound descending) and block prefix
+  // interpolation: jobs by degree bound, largest first, cut into groups that
+  // share a workgroup per prime; bytes of the list, the groups' first entries
+  // and the prefix of their prime counts (pref_interp)
+  std::vector<int32_t> im_order, im_start;
+  size_t list_im = 0, start_im = 0, im_lds = 0;
   bool reduce_in_eval = false;       // the evaluation kernel reduces the inputs (no reduction launch)
   size_t pref_ee[NCLS] = {0}, list_ee[NCLS] = {0}, list_gen = 0;                   // bytes
   // Chinese remaindering: the small-prime classes (one lane per coefficient)
@@ -78,7 +79,7 @@ struct BatchLayout {
   size_t out_off = 0, out_words = 0;                       // bytes / words
   size_t sq_off = 0, sq_words = 0;  // bytes / words: gcd(R, R') descriptors, work items, e and d
   size_t total_bytes = 0;
-  int64_t nb_red = 0, nb_interp = 0, nb_crtd = 0, nb_crtc = 0, n_gen_inst = 0, nb_interp_blk = 0;
+  int64_t nb_red = 0, nb_interp = 0, nb_crtd = 0, nb_crtc = 0, n_gen_inst = 0;
   int64_t nb_ee[NCLS] = {0};
   int n_ee_jobs[NCLS] = {0}, n_gen_jobs = 0, n_rows = 0, max_D = 0, max_k = 0;
   int max_T_ee[NCLS] = {0};  // largest residue count per prime among a class's jobs

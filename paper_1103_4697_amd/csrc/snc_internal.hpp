@@ -25,7 +25,7 @@ constexpr int GCD_THREADS = 256;
 struct ResJob {
   int32_t m, n;        // y-degrees of A and B over Z[x], m >= 1, m >= n >= 0
   int32_t sign;        // 1: operands were swapped and m*n is odd (result negated)
-  int32_t D;           // evaluation points x_j = j, j = 0..D
+  int32_t D;           // evaluation points x_0..x_D
   int32_t k;           // primes 0..k-1 of the table
   int32_t T;           // residues per prime (coefficients of f and g)
   int32_t L;           // output limbs per coefficient
@@ -129,12 +129,28 @@ inline bool interp_blk_fits(int max_D, int max_k) { return max_D + 1 <= 64 * IFF
 void launch_interp_blk(const ResJob* jobs_d, const int64_t* blk_prefix_d, int njobs, int64_t nblocks, uint32_t* ws,
                        uint32_t* zero_word, hipStream_t s);
 void launch_zero_u32(uint32_t* p, int64_t n, hipStream_t s);
-// one-wavefront interpolation per (resultant, prime): degree bounds up to IW_MAXD, for batches with at
-// least IW_MIN_PAIRS (resultant, prime) pairs; jobs from job_list_d (prefix: k per job)
-constexpr int IW_MAXD = 4095;
-constexpr int64_t IW_MIN_PAIRS = 4096;
-void launch_interp_w(const ResJob* jobs_d, const int32_t* job_list_d, const int64_t* prefix_d, int njobs,
-                     int64_t nblocks, int max_D, uint32_t* ws, uint32_t* zero_word, hipStream_t s);
+// Evaluation points of the resultants: x_j = q^j mod p, q = q(p) of order
+// above MAX_D.  Row p of the table: q^l for l < 64, then q^(64 b) at 64 + b.
+constexpr int POINT_ROW = 256;
+static_assert(64 + MAX_D / 64 < POINT_ROW, "a row holds the block powers of the largest degree bound");
+__device__ __forceinline__ uint32_t point_mont(const uint32_t* points, int pi, int j, const PrimeC& c) {
+  const uint32_t* r = points + (int64_t)pi * POINT_ROW;
+  const uint32_t t = mmul(r[64 + (j >> 6)], r[j & 63], c.p, c.pinv);
+  return canon2(t, c.p);
+}
+void launch_points_init(hipStream_t s);  // points and interpolation tables (once per device)
+const uint32_t* points_table();          // of the current device
+// Interpolation at those points: a workgroup per prime of a group of jobs
+// (job_list_d[gstart_d[g]] .. of group g, prefix: the largest prime count of
+// each group).  lds: the largest group's interp_mfma_lds.
+constexpr int IM_JOBS = 16;                    // jobs of a group
+constexpr size_t IM_LDS = 48 * 1024;           // LDS a group of more than one job may take
+constexpr int64_t IM_MIN_BLOCKS = 1024;        // workgroups wanted before jobs share one
+size_t interp_mfma_lds(int max_D, int blocks); // largest degree bound, 64-point blocks of all jobs
+hipError_t configure_interp_mfma();
+void launch_interp_mfma(const ResJob* jobs_d, const int32_t* job_list_d, const int32_t* gstart_d,
+                        const int64_t* gprefix_d, int ngroups, int64_t nblocks, size_t lds, uint32_t* ws,
+                        uint32_t* zero_word, hipStream_t s);
 // zero_word (may be null) is set to zero by the same launch
 void launch_reduce(const ResJob* jobs_d, const int64_t* blk_prefix_d, int njobs, int64_t nblocks,
                    const uint32_t* ws, uint32_t* res_base, uint32_t* zero_word, hipStream_t s);
@@ -154,7 +170,7 @@ constexpr int EE_WPE_MAX = 4;
 // Revision of the evaluation kernels' code and of the tuner's choice rule,
 // part of the autotuner's cache file name: a changed kernel is tuned again
 // instead of taking stale choices.
-constexpr int EE_KERNEL_REV = 5;
+constexpr int EE_KERNEL_REV = 6;
 // workgroups of a variant resident on the whole device (0 if the query fails)
 int eval_elim_grid(int cls, int wpe, int max_T);
 // private (spill) bytes per lane of a variant's kernel (-1 if the query fails)
