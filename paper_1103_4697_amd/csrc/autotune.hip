@@ -136,8 +136,6 @@ int choose_eval_variants(snc_ctx* c, BatchLayout& lay, uint8_t* ws, hipStream_t 
   uint32_t* wsw = (uint32_t*)ws;
   const ResJob* jobs = (const ResJob*)(ws + lay.jobs_off);
   const RowDesc* rows = (const RowDesc*)(ws + lay.rows_off);
-  uint32_t* abn_count = (uint32_t*)(ws + lay.abn_count_off);
-  AbnEntry* abn_list = (AbnEntry*)(ws + lay.abn_list_off);
   uint32_t* counters = (uint32_t*)(ws + lay.ee_counter_off);
   std::lock_guard<std::mutex> lk(g_mu);
   load_cache(tag);
@@ -161,8 +159,7 @@ int choose_eval_variants(snc_ctx* c, BatchLayout& lay, uint8_t* ws, hipStream_t 
         TUNECHK(hipEventCreate(&e1));
       }
       if (!lay.reduce_in_eval && !reduced) {  // residues for the variants that read them
-        launch_reduce(jobs, (const int64_t*)(ws + lay.pref_red), (int)lay.jobs.size(), lay.nb_red, wsw, wsw,
-                      abn_count, s);
+        launch_reduce(jobs, (const int64_t*)(ws + lay.pref_red), (int)lay.jobs.size(), lay.nb_red, wsw, wsw, s);
         reduced = true;
       }
       float best = -1.f, def = -1.f;
@@ -179,12 +176,11 @@ int choose_eval_variants(snc_ctx* c, BatchLayout& lay, uint8_t* ws, hipStream_t 
           }
           float ms_best = -1.f;
           for (int rep_i = 0; rep_i < 2; ++rep_i) {
-            launch_zero_u32(abn_count, 1, s);
             launch_zero_u32(counters + cls, 1, s);
             TUNECHK(hipEventRecord(e0, s));
             launch_eval_elim(cls, cand, counters + cls, jobs, (const int32_t*)(ws + lay.list_ee[cls]),
                              (const int64_t*)(ws + lay.pref_ee[cls]), lay.n_ee_jobs[cls], lay.nb_ee[cls],
-                             lay.max_T_ee[cls], rows, wsw, abn_count, abn_list, lay.abn_cap, lay.reduce_in_eval, s);
+                             lay.max_T_ee[cls], rows, wsw, lay.reduce_in_eval, s);
             TUNECHK(hipGetLastError());
             TUNECHK(hipEventRecord(e1, s));
             TUNECHK(hipEventSynchronize(e1));
@@ -240,7 +236,6 @@ int choose_eval_variants(snc_ctx* c, BatchLayout& lay, uint8_t* ws, hipStream_t 
     c->tune_report.push_back(rep);
   }
   if (reduced || measured) {
-    launch_zero_u32(abn_count, 1, s);  // the runs start from an empty abnormal list
     if (hipStreamSynchronize(s) != hipSuccess) { c->err = "autotune: synchronize failed"; st = SNC_EDEVICE; }
   }
 done:

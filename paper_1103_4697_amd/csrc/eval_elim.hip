@@ -9,8 +9,7 @@ namespace snc {
   extern template int eval_elim_scratch_cls<NN>(int, int);                                                   \
   extern template void launch_eval_elim_cls<NN>(const EEVariant&, uint32_t*, const PrimeC*, const ResJob*,   \
                                                 const int32_t*, const int64_t*, int, int64_t, int,            \
-                                                const RowDesc*, uint32_t*, uint32_t*, AbnEntry*, uint32_t,    \
-                                                bool, hipStream_t);
+                                                const RowDesc*, uint32_t*, bool, hipStream_t);
 SNC_EXTERN_CLASS(8)
 SNC_EXTERN_CLASS(16)
 SNC_EXTERN_CLASS(32)
@@ -52,12 +51,11 @@ int eval_elim_scratch(int cls, int wpe, int max_T) {
 
 void launch_eval_elim(int cls, const EEVariant& v, uint32_t* counter, const ResJob* jobs_d,
                       const int32_t* job_list_d, const int64_t* blk_prefix_d, int njobs, int64_t nblocks,
-                      int max_T, const RowDesc* rows_d, uint32_t* ws, uint32_t* abn_count, AbnEntry* abn_list,
-                      uint32_t abn_cap, bool reduce_in, hipStream_t s) {
+                      int max_T, const RowDesc* rows_d, uint32_t* ws, bool reduce_in, hipStream_t s) {
   const PrimeC* primes = global_crt_tables().primes;
 #define SNC_EE(NN)                                                                                            \
   launch_eval_elim_cls<NN>(v, counter, primes, jobs_d, job_list_d, blk_prefix_d, njobs, nblocks, max_T, rows_d, \
-                           ws, abn_count, abn_list, abn_cap, reduce_in, s)
+                           ws, reduce_in, s)
   switch (kClassCap[cls]) {
     case 8: SNC_EE(8); break;
     case 16: SNC_EE(16); break;

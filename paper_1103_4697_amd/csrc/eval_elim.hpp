@@ -69,7 +69,7 @@ __device__ __forceinline__ uint32_t reduce_limbs(const uint32_t* limbs, int nl, 
 // denominator that is inverted once at the end.  The last step is
 // res(X, c) = c^{deg X}.  A lane whose leading coefficients vanish at its
 // point (formal degree not attained, or a remainder of lower degree) is
-// queued for the general elimination below; the schedule stays uniform.
+// marked for the general elimination; the schedule stays uniform.
 // ---------------------------------------------------------------------------
 // one row q (0..3) of a row group
 __device__ __forceinline__ uint32_t horner_grouped(const uint32_t* r, const RowDesc& d, int q, uint32_t X,
@@ -337,8 +337,7 @@ __device__ __forceinline__ void elim_phases(uint32_t (&A)[N + 1], uint32_t (&B)[
 template <int N, bool LDSROWS>
 __device__ __forceinline__ void eval_elim_block(int64_t b, const PrimeC* primes, const ResJob* jobs,
                                                 const int32_t* job_list, const int64_t* prefix, int njobs,
-                                                const RowDesc* rows, uint32_t* ws, uint32_t* abn_count,
-                                                AbnEntry* abn_list, uint32_t abn_cap, int reduce_in, uint32_t* er,
+                                                const RowDesc* rows, uint32_t* ws, int reduce_in, uint32_t* er,
                                                 const uint32_t* points, int64_t& staged) {
   const int jj = find_job(prefix, njobs, b);
   const int jid = job_list[jj];
@@ -420,12 +419,9 @@ __device__ __forceinline__ void eval_elim_block(int64_t b, const PrimeC* primes,
   if (sg) res = mneg(res, c.p);
   if (!live) return;
   // a zero remainder with a divisor of positive degree: res = 0; an
-  // abnormal instance leaves a marker (never a residue) for the general pass
+  // abnormal instance leaves a marker (never a residue), which the
+  // interpolation replaces by the general elimination's value
   ws[J.pts_off + (int64_t)pi * (J.D + 1) + j] = st == EL_NORMAL ? res : st == EL_ZERO ? 0u : ABN_MARK;
-  if (st == EL_ABN) {
-    uint32_t idx = atomicAdd(abn_count, 1u);
-    if (idx < abn_cap) abn_list[idx] = AbnEntry{jid, pi, j, 0};
-  }
 }
 
 // Work distribution of a launch.  chunk == 0: one workgroup per block,
@@ -446,15 +442,14 @@ struct EEWork {
 template <int N, bool LDSROWS, int WPE>
 __global__ __launch_bounds__(EE_BLOCK) __attribute__((amdgpu_waves_per_eu(WPE))) void k_eval_elim(
     const PrimeC* primes, const ResJob* jobs, const int32_t* job_list, const int64_t* prefix, int njobs,
-    const RowDesc* rows, uint32_t* ws, uint32_t* abn_count, AbnEntry* abn_list, uint32_t abn_cap, int reduce_in,
-    EEWork wk) {
+    const RowDesc* rows, uint32_t* ws, int reduce_in, EEWork wk) {
   static_assert(EE_BLOCK == 64, "one wavefront per workgroup (the work counter is broadcast by readfirstlane)");
   extern __shared__ uint4 er4[];  // max T words (LDSROWS)
   uint32_t* er = reinterpret_cast<uint32_t*>(er4);
   int64_t staged = -1;
   if (wk.chunk == 0) {
     eval_elim_block<N, LDSROWS>(xcd_block(blockIdx.x, gridDim.x), primes, jobs, job_list, prefix, njobs, rows,
-                                ws, abn_count, abn_list, abn_cap, reduce_in, er, wk.points, staged);
+                                ws, reduce_in, er, wk.points, staged);
     return;
   }
   const int64_t nb = prefix[njobs];
@@ -465,8 +460,8 @@ __global__ __launch_bounds__(EE_BLOCK) __attribute__((amdgpu_waves_per_eu(WPE)))
     if ((int64_t)base >= nb) break;
     const int64_t end = (int64_t)base + wk.chunk < nb ? (int64_t)base + wk.chunk : nb;
     for (int64_t b = base; b < end; ++b)
-      eval_elim_block<N, LDSROWS>(b, primes, jobs, job_list, prefix, njobs, rows, ws, abn_count, abn_list,
-                                  abn_cap, reduce_in, er, wk.points, staged);
+      eval_elim_block<N, LDSROWS>(b, primes, jobs, job_list, prefix, njobs, rows, ws, reduce_in, er,
+                                  wk.points, staged);
   }
 }
 
@@ -513,8 +508,7 @@ int eval_elim_scratch_cls(int wpe, int max_T) {
 template <int NN>
 void launch_eval_elim_cls(const EEVariant& v, uint32_t* counter, const PrimeC* primes, const ResJob* jobs_d,
                           const int32_t* job_list_d, const int64_t* blk_prefix_d, int njobs, int64_t nblocks,
-                          int max_T, const RowDesc* rows_d, uint32_t* ws, uint32_t* abn_count, AbnEntry* abn_list,
-                          uint32_t abn_cap, bool reduce_in, hipStream_t s) {
+                          int max_T, const RowDesc* rows_d, uint32_t* ws, bool reduce_in, hipStream_t s) {
   if (nblocks <= 0) return;
   const bool persistent = v.chunk > 0 && v.grid > 0;
   const dim3 g((unsigned)(persistent ? (v.grid < nblocks ? v.grid : nblocks) : nblocks));
@@ -524,8 +518,7 @@ void launch_eval_elim_cls(const EEVariant& v, uint32_t* counter, const PrimeC* p
   const EEWork wk{counter, points_table(), persistent ? v.chunk : 0};
   const void* k = in_lds ? ee_kernel_ptr<NN, true>(v.wpe) : ee_kernel_ptr<NN, false>(v.wpe);
   void* args[] = {(void*)&primes, (void*)&jobs_d, (void*)&job_list_d, (void*)&blk_prefix_d, (void*)&njobs,
-                  (void*)&rows_d, (void*)&ws, (void*)&abn_count, (void*)&abn_list, (void*)&abn_cap, (void*)&red,
-                  (void*)&wk};
+                  (void*)&rows_d, (void*)&ws, (void*)&red, (void*)&wk};
   (void)hipLaunchKernel(k, g, dim3(EE_BLOCK), args, lds, s);
 }
 
@@ -535,6 +528,6 @@ void launch_eval_elim_cls(const EEVariant& v, uint32_t* counter, const PrimeC* p
   template int eval_elim_scratch_cls<NN>(int, int);                                                           \
   template void launch_eval_elim_cls<NN>(const EEVariant&, uint32_t*, const PrimeC*, const ResJob*,           \
                                          const int32_t*, const int64_t*, int, int64_t, int, const RowDesc*,    \
-                                         uint32_t*, uint32_t*, AbnEntry*, uint32_t, bool, hipStream_t);
+                                         uint32_t*, bool, hipStream_t);
 
 }  // namespace snc

@@ -1580,7 +1580,7 @@ static int max_rowdeg(const std::vector<UPoly>& R) {
 // then (if the gcd degree e > 0 is the same at every image) W's coefficients
 // 0..e in x by interpolation and Chinese remaindering
 struct YgcdLayout {
-  size_t jr = 0, jobs = 0, pref_red = 0, pref_ip = 0, pref_crt = 0, pref_crt2 = 0, list_crt = 0, zero = 0, e_out = 0;
+  size_t jr = 0, jobs = 0, pref_red = 0, pref_ip = 0, pref_crt = 0, pref_crt2 = 0, list_crt = 0, e_out = 0;
   size_t coef = 0, res = 0, regions = 0, total = 0;
   int64_t n1 = 0, L = 1, job_words = 0;
 };
@@ -1599,7 +1599,6 @@ static void ygcd_layout(int k, int T, int nl, int Dx, int emax, YgcdLayout& Y) {
   Y.pref_crt = off; off = al(off + 8 * (nj + 1));
   Y.pref_crt2 = off; off = al(off + 8 * (nj + 1));
   Y.list_crt = off; off = al(off + 4 * nj);
-  Y.zero = off; off = al(off + 4);
   Y.e_out = off; off = al(off + 4 * (size_t)k * Y.n1);
   Y.coef = off; off = al(off + 4 * (size_t)T * nl);
   Y.res = off; off = al(off + 4 * (size_t)T * k);
@@ -1697,7 +1696,7 @@ static int bivariate_gcd_run(snc_ctx* ctx, const std::vector<UPoly>& A, const st
     std::memcpy(hdr.data() + Y.coef, coef.data(), coef.size() * 4);
     HIPCHK(hipMemcpyAsync(ws, hdr.data(), Y.regions, hipMemcpyHostToDevice, stream));
     launch_reduce((const ResJob*)(ws + Y.jr), (const int64_t*)(ws + Y.pref_red), 1, pr[1], (const uint32_t*)ws,
-                  (uint32_t*)ws, nullptr, stream);
+                  (uint32_t*)ws, stream);
     YGcdArgs ya{};
     ya.primes = tb.primes; ya.res = (const uint32_t*)(ws + Y.res); ya.T = T; ya.k = k; ya.npts = (int)Y.n1;
     ya.mA = mA; ya.dxA = dxA; ya.offA = offA; ya.mB = mB; ya.dxB = dxB; ya.offB = offB;
@@ -1745,9 +1744,8 @@ static int bivariate_gcd_run(snc_ctx* ctx, const std::vector<UPoly>& A, const st
     HIPCHK(hipMemcpyAsync(ws + Y.pref_crt2, pcc.data(), 8 * (nj + 1), hipMemcpyHostToDevice, stream));
     HIPCHK(hipMemcpyAsync(ws + Y.list_crt, lst.data(), 4 * nj, hipMemcpyHostToDevice, stream));
     const ResJob* jd = (const ResJob*)(ws + Y.jobs);
-    uint32_t* zero = (uint32_t*)(ws + Y.zero);
-    if (blk) launch_interp_blk(jd, (const int64_t*)(ws + Y.pref_ip), nj, pip[nj], (uint32_t*)ws, zero, stream);
-    else launch_interp(jd, (const int64_t*)(ws + Y.pref_ip), nj, pip[nj], Dx, (uint32_t*)ws, zero, stream);
+    if (blk) launch_interp_blk(jd, (const int64_t*)(ws + Y.pref_ip), nj, pip[nj], (uint32_t*)ws, stream);
+    else launch_interp(jd, (const int64_t*)(ws + Y.pref_ip), nj, pip[nj], Dx, (uint32_t*)ws, stream);
     if (cc >= 0) {
       launch_crt_small(cc, jd, (const int32_t*)(ws + Y.list_crt), (const int64_t*)(ws + Y.pref_crt), nj, pcr[nj],
                        (uint32_t*)ws, stream);

@@ -38,6 +38,7 @@
 #include <hip/hip_runtime.h>
 
 #include "eval_elim.hpp"
+#include "general_elim.hpp"
 #include "mfma_modp.hpp"
 
 namespace snc {
@@ -100,6 +101,7 @@ __global__ __launch_bounds__(64) void k_points_init(const PrimeC* primes) {
 constexpr int IM_THREADS = 256;
 constexpr int IM_WAVES = IM_THREADS / 64;
 constexpr int IM_MAXROWS = 192;
+constexpr int IM_MARKS = 32;  // abnormal instances of a workgroup that take a wavefront each
 static_assert((MAX_D + 64) / 64 <= IM_MAXROWS, "the rows of one job of the largest degree bound");
 
 // LDS of a group: the planes of t (reversed and ascending, or one after the
@@ -109,18 +111,6 @@ __host__ __device__ constexpr int im_tplane(int Dp) { return Dp + 144; }
 __host__ __device__ constexpr bool im_both(int Dp) { return Dp <= 4096; }
 static_assert(4 * im_tplane((MAX_D + 64) / 64 * 64) + 8 * ((MAX_D + 64) / 64 * 64) + 8 * 1024 <= 160 * 1024,
               "the buffers of the largest degree bound fit the LDS of a CU");
-
-// the four bytes planes of four consecutive values
-__device__ __forceinline__ void split_planes(const uint32_t (&w)[4], uint32_t (&pl)[4]) {
-  const uint32_t a = __builtin_amdgcn_perm(w[1], w[0], 0x05010400u);  // bytes 0, 1 of w0, w1: 0a 0b 1a 1b
-  const uint32_t b = __builtin_amdgcn_perm(w[3], w[2], 0x05010400u);
-  const uint32_t d = __builtin_amdgcn_perm(w[1], w[0], 0x07030602u);  // bytes 2, 3
-  const uint32_t e = __builtin_amdgcn_perm(w[3], w[2], 0x07030602u);
-  pl[0] = __builtin_amdgcn_perm(b, a, 0x05040100u);
-  pl[1] = __builtin_amdgcn_perm(b, a, 0x07060302u);
-  pl[2] = __builtin_amdgcn_perm(e, d, 0x05040100u);
-  pl[3] = __builtin_amdgcn_perm(e, d, 0x07060302u);
-}
 
 // bytes sh .. sh + 15 of five words
 template <int SH>
@@ -266,13 +256,14 @@ __device__ __forceinline__ void interp_stage(const InterpLds& S, int ntile, int 
 
 __global__ __launch_bounds__(IM_THREADS) void k_interp_mfma(const PrimeC* primes, const ResJob* jobs,
                                                             const int32_t* job_list, const int32_t* gstart,
-                                                            const int64_t* gprefix, int ngroups, uint32_t* ws,
-                                                            uint32_t* zero_word) {
+                                                            const int64_t* gprefix, int ngroups, const RowDesc* rows,
+                                                            uint32_t* ws) {
   extern __shared__ uint4 im_sm[];
   __shared__ int64_t sPts[IM_JOBS], sVal[IM_JOBS];
   __shared__ int32_t sN1[IM_JOBS], sBlk[IM_JOBS], sU[IM_JOBS];
   __shared__ int32_t sRow[IM_MAXROWS + 16];  // job << 16 | block distance K; -1 past the last row
-  if (blockIdx.x == 0 && threadIdx.x == 0) *zero_word = 0u;  // abnormal counter, read by now
+  __shared__ int32_t nmark, mark[IM_MARKS];
+  __shared__ uint32_t gen[IM_WAVES][2 * (MAXY_FAST + 1)];
   uint8_t* sm = reinterpret_cast<uint8_t*>(im_sm);
   const int g = find_job(gprefix, ngroups, blockIdx.x);
   const int pi = (int)(blockIdx.x - gprefix[g]);
@@ -289,6 +280,7 @@ __global__ __launch_bounds__(IM_THREADS) void k_interp_mfma(const PrimeC* primes
     sVal[tid] = J.val_off + (int64_t)pi * (J.D + 1);
   }
   for (int r = tid; r < IM_MAXROWS + 16; r += IM_THREADS) sRow[r] = -1;
+  if (tid == 0) nmark = 0;
   __syncthreads();
   int nrows = 0, mxb = 0;
   for (int j = 0; j < nj; ++j) { nrows += sBlk[j]; mxb = max(mxb, sBlk[j]); }
@@ -336,21 +328,45 @@ __global__ __launch_bounds__(IM_THREADS) void k_interp_mfma(const PrimeC* primes
   };
   if (both) load_ascending(4 * TP);
   __syncthreads();
-  // u = v / phi
-  for (int j = 0; j < nj; ++j) {
-    const int n1 = sN1[j], dp = 64 * sBlk[j];
-    const uint32_t* V = ws + sPts[j];
-    for (int i = 4 * tid; i < dp; i += 4 * IM_THREADS) {
-      uint32_t w[4], pl[4];
+  // u = v / phi.  Instances the evaluation marked abnormal are computed here:
+  // a wavefront each while there are few (a lane alone takes ten times as
+  // long), else a lane each (a pair whose remainders skip degrees at every
+  // point marks all of them).
+  auto put_u = [&](int j, int i, uint32_t v) {
+    const uint32_t w = i < sN1[j] ? balance4(mmulc(canon(v, c.p), ip[i], c.p, c.pinv)) : 0u;
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        w[e] = i + e < n1 ? balance4(mmulc(canon(V[i + e], c.p), ip[i + e], c.p, c.pinv)) : 0u;
-      split_planes(w, pl);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) *reinterpret_cast<uint32_t*>(sm + sU[j] + q * dp + i) = pl[q];
+    for (int q = 0; q < 4; ++q) sm[sU[j] + q * 64 * sBlk[j] + i] = (uint8_t)(w >> (8 * q));
+  };
+  auto each_point = [&](auto&& f) {
+    for (int j = 0; j < nj; ++j)
+      for (int i = tid; i < 64 * sBlk[j]; i += IM_THREADS) f(j, i, i < sN1[j] ? ws[sPts[j] + i] : 0u);
+  };
+  each_point([&](int j, int i, uint32_t v) {
+    if (__builtin_expect(v == ABN_MARK, 0)) {
+      const int x = atomicAdd(&nmark, 1);
+      if (x < IM_MARKS) mark[x] = j << 16 | i;
     }
-  }
+    put_u(j, i, v);
+  });
   __syncthreads();
+  if (__builtin_expect(nmark != 0, 0)) {
+    // small degrees: a lane needs two to three times a wavefront's time, not ten, so two rounds at most
+    const int most = jobs[job_list[s0 + (mark[0] >> 16)]].m >= 16 ? IM_MARKS : 2 * IM_WAVES;
+    if (nmark <= most) {
+      for (int x = wave; x < nmark; x += IM_WAVES) {
+        const int j = mark[x] >> 16, i = mark[x] & 0xffff;
+        const uint32_t v = general_instance_wave(jobs + job_list[s0 + j], primes, rows, ws, g_points, pi, i,
+                                                 gen[wave], gen[wave] + MAXY_FAST + 1, lane);
+        if (lane == 0) put_u(j, i, v);
+      }
+    } else {
+      each_point([&](int j, int i, uint32_t v) {
+        if (v == ABN_MARK)
+          put_u(j, i, general_instance<MAXY_FAST>(jobs + job_list[s0 + j], primes, rows, ws, g_points, pi, i));
+      });
+    }
+    __syncthreads();
+  }
   const uint32_t k56 = fold_const(c);
   const int ntile = (nrows + 15) / 16;
   InterpLds S{sm, sRow, sN1, sBlk, sU, sVal, TP, Dp, zoff, 0};
@@ -389,11 +405,11 @@ const uint32_t* points_table() {
 }
 
 void launch_interp_mfma(const ResJob* jobs_d, const int32_t* job_list_d, const int32_t* gstart_d,
-                        const int64_t* gprefix_d, int ngroups, int64_t nblocks, size_t lds, uint32_t* ws,
-                        uint32_t* zero_word, hipStream_t s) {
+                        const int64_t* gprefix_d, int ngroups, int64_t nblocks, size_t lds, const RowDesc* rows_d,
+                        uint32_t* ws, hipStream_t s) {
   if (nblocks <= 0) return;
   hipLaunchKernelGGL(k_interp_mfma, dim3((unsigned)nblocks), dim3(IM_THREADS), lds, s, global_crt_tables().primes,
-                     jobs_d, job_list_d, gstart_d, gprefix_d, ngroups, ws, zero_word);
+                     jobs_d, job_list_d, gstart_d, gprefix_d, ngroups, rows_d, ws);
 }
 
 }  // namespace snc

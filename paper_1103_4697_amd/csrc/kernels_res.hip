@@ -7,6 +7,7 @@
 #include <algorithm>
 
 #include "eval_elim.hpp"
+#include "general_elim.hpp"
 
 namespace snc {
 
@@ -18,7 +19,7 @@ __device__ uint32_t g_garner[KMAX];            // Montgomery form of (P_i mod p_
 __device__ uint32_t g_wtab[KMAX * KMAX];       // [j*KMAX + i] = Montgomery form of P_j mod p_i (j < i)
 __device__ uint32_t g_ptab[(KMAX + 1) * LPS];  // row j: P_j = prod_{l<j} p_l, little-endian limbs
 
-__global__ void k_interp(const ResJob* jobs, const int64_t* prefix, int njobs, uint32_t* ws, uint32_t* zero_word);
+__global__ void k_interp(const ResJob* jobs, const int64_t* prefix, int njobs, uint32_t* ws);
 
 // per-device kernel attributes (called once per device before any launch)
 __global__ void k_crt_combine(CrtTables tb, const ResJob* jobs, const int32_t* job_list, const int64_t* prefix,
@@ -64,9 +65,8 @@ constexpr int RED_THREADS = 256;
 
 __global__ __launch_bounds__(RED_THREADS) void k_reduce(const ResJob* jobs, const int64_t* prefix,
                                                         int njobs, const uint32_t* ws,
-                                                        uint32_t* wsw, uint32_t* zero_word) {
+                                                        uint32_t* wsw) {
   const int64_t b = blockIdx.x;
-  if (b == 0 && threadIdx.x == 0 && zero_word) *zero_word = 0u;  // the abnormal-instance counter
   const int jj = find_job(prefix, njobs, b);
   const ResJob J = jobs[jj];
   const int nb = (J.T + RED_THREADS - 1) / RED_THREADS;
@@ -79,127 +79,10 @@ __global__ __launch_bounds__(RED_THREADS) void k_reduce(const ResJob* jobs, cons
 }
 
 void launch_reduce(const ResJob* jobs_d, const int64_t* blk_prefix_d, int njobs, int64_t nblocks,
-                   const uint32_t* ws, uint32_t* res_base, uint32_t* zero_word, hipStream_t s) {
-  if (nblocks <= 0) {
-    if (zero_word) launch_zero_u32(zero_word, 1, s);
-    return;
-  }
+                   const uint32_t* ws, uint32_t* res_base, hipStream_t s) {
+  if (nblocks <= 0) return;
   hipLaunchKernelGGL(k_reduce, dim3((unsigned)nblocks), dim3(RED_THREADS), 0, s, jobs_d,
-                     blk_prefix_d, njobs, ws, res_base, zero_word);
-}
-
-// ---------------------------------------------------------------------------
-// General elimination for one instance, any degree pattern: formal-degree
-// corrections (res_{m,n} = (-1)^{n(m-m')} g_n^{m-m'} res_{m',n} when f's
-// leading coefficients vanish, = f_m^{n-n'} res_{m,n'} when g's do, 0 when
-// both do), then Euclid with true remainders.  Arrays are bottom-aligned
-// (index = y-degree); runs for the rare abnormal lanes, or for every
-// instance when a y-degree exceeds the register classes.
-// ---------------------------------------------------------------------------
-__device__ uint32_t res_general(uint32_t* F, int m, uint32_t* G, int n, const PrimeC& c) {
-  if (m == 0 && n == 0) return c.r1;
-  if (n == 0) return mpow(G[0], (uint32_t)m, c);
-  if (m == 0) return mpow(F[0], (uint32_t)n, c);
-  int mm = m;
-  while (mm >= 0 && F[mm] == 0) --mm;
-  int nn = n;
-  while (nn >= 0 && G[nn] == 0) --nn;
-  if (mm < 0 || nn < 0) return 0;
-  if (mm < m && nn < n) return 0;
-  uint32_t acc = c.r1;
-  if (mm < m) {
-    acc = mmulc(acc, mpow(G[n], (uint32_t)(m - mm), c), c.p, c.pinv);
-    if ((n * (m - mm)) & 1) acc = mneg(acc, c.p);
-  }
-  if (nn < n) acc = mmulc(acc, mpow(F[m], (uint32_t)(n - nn), c), c.p, c.pinv);
-  uint32_t* Ap = F;
-  uint32_t* Bp = G;
-  int a = mm, b = nn;
-  while (true) {
-    if (a == 0) return mmulc(acc, mpow(Ap[0], (uint32_t)b, c), c.p, c.pinv);
-    if (b == 0) return mmulc(acc, mpow(Bp[0], (uint32_t)a, c), c.p, c.pinv);
-    if (a < b) {
-      uint32_t* t = Ap; Ap = Bp; Bp = t;
-      int ti = a; a = b; b = ti;
-      if ((a * b) & 1) acc = mneg(acc, c.p);
-      continue;
-    }
-    const uint32_t inv = minv(Bp[b], c);
-    int r = a;
-    while (r >= b) {
-      const uint32_t q = mmulc(Ap[r], inv, c.p, c.pinv);
-      if (q) {
-        for (int i = 0; i < b; ++i)
-          Ap[r - b + i] = msub(Ap[r - b + i], mmulc(q, Bp[i], c.p, c.pinv), c.p);
-      }
-      Ap[r] = 0;
-      --r;
-      while (r >= 0 && Ap[r] == 0) --r;
-    }
-    if (r < 0) return 0;
-    acc = mmulc(acc, mpow(Bp[b], (uint32_t)(a - r), c), c.p, c.pinv);
-    if ((a * b) & 1) acc = mneg(acc, c.p);
-    uint32_t* t = Ap; Ap = Bp; Bp = t;  // (A, B) <- (B, R)
-    a = b; b = r;
-  }
-}
-
-// MAXY: the largest y-degree of the instances this variant runs (the size
-// of the per-lane value arrays)
-template <int MAXY>
-__device__ void general_instance(const ResJob& J, const RowDesc* rows, uint32_t* ws, const uint32_t* points, int pi,
-                                 int j) {
-  const PrimeC c = g_primes[pi];
-  const uint32_t* r = ws + J.res_off + (int64_t)pi * J.T;
-  const uint32_t X = point_mont(points, pi, j, c);
-  const RowDesc* ra = rows + J.rows_off;
-  const RowDesc* rb = ra + J.rstride;
-  uint32_t F[MAXY + 1], G[MAXY + 1];
-  for (int t = 0; t <= J.m; ++t) F[J.m - t] = canon(horner_grouped(r, ra[t / ROWGRP], t % ROWGRP, X, c), c.p);
-  for (int t = 0; t <= J.n; ++t) G[J.n - t] = canon(horner_grouped(r, rb[t / ROWGRP], t % ROWGRP, X, c), c.p);
-  uint32_t res = res_general(F, J.m, G, J.n, c);
-  if (J.sign) res = mneg(res, c.p);
-  ws[J.pts_off + (int64_t)pi * (J.D + 1) + j] = res;
-}
-
-// The abnormal instances of the register-resident elimination (y-degrees up
-// to MAXY_FAST): from the list when it held them all, else every instance
-// of the batch whose value carries the marker (inst_prefix: instances per
-// job, prefix sums over the njobs jobs).
-__global__ void k_elim_general(const ResJob* jobs, const RowDesc* rows, uint32_t* ws,
-                               const uint32_t* abn_count, const AbnEntry* list, uint32_t cap,
-                               const int64_t* inst_prefix, int njobs, const uint32_t* points) {
-  const uint32_t cnt = *abn_count;
-  if (cnt == 0) return;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (cnt <= cap) {
-    for (int64_t idx = t0; idx < cnt; idx += stride) {
-      const AbnEntry e = list[idx];
-      const ResJob J = jobs[e.job];
-      general_instance<MAXY_FAST>(J, rows, ws, points, e.prime, e.point);
-    }
-    return;
-  }
-  const int64_t ninst = inst_prefix[njobs];
-  for (int64_t idx = t0; idx < ninst; idx += stride) {
-    const int jj = find_job(inst_prefix, njobs, idx);
-    const ResJob J = jobs[jj];
-    const int64_t li = idx - inst_prefix[jj];
-    const int pi = (int)(li / (J.D + 1)), j = (int)(li % (J.D + 1));
-    if (J.m > MAXY_FAST) continue;  // computed whole by the general kernel, never marked
-    if (ws[J.pts_off + (int64_t)pi * (J.D + 1) + j] == ABN_MARK) general_instance<MAXY_FAST>(J, rows, ws, points, pi, j);
-  }
-}
-
-void launch_elim_general(const ResJob* jobs_d, const RowDesc* rows_d, uint32_t* ws,
-                         const uint32_t* abn_count, const AbnEntry* abn_list, uint32_t cap,
-                         const int64_t* inst_prefix_d, int njobs, hipStream_t s) {
-  // enough lanes for a full list, at most 16 wavefronts per CU (grid-stride beyond)
-  int64_t blocks = ((int64_t)cap + 63) / 64;
-  blocks = blocks < 1 ? 1 : blocks > 256 * 16 ? 256 * 16 : blocks;
-  hipLaunchKernelGGL(k_elim_general, dim3((unsigned)blocks), dim3(64), 0, s, jobs_d, rows_d, ws, abn_count, abn_list,
-                     cap, inst_prefix_d, njobs, points_table());
+                     blk_prefix_d, njobs, ws, res_base);
 }
 
 __global__ void k_elim_general_all(const ResJob* jobs, const int32_t* job_list,
@@ -210,7 +93,9 @@ __global__ void k_elim_general_all(const ResJob* jobs, const int32_t* job_list,
     const int jj = find_job(prefix, njobs, idx);
     const ResJob J = jobs[job_list[jj]];
     const int64_t li = idx - prefix[jj];
-    general_instance<MAXY_GEN>(J, rows, ws, points, (int)(li / (J.D + 1)), (int)(li % (J.D + 1)));
+    const int pi = (int)(li / (J.D + 1)), j = (int)(li % (J.D + 1));
+    ws[J.pts_off + (int64_t)pi * (J.D + 1) + j] =
+        general_instance<MAXY_GEN>(jobs + job_list[jj], g_primes, rows, ws, points, pi, j);
   }
 }
 
@@ -348,8 +233,7 @@ __device__ __forceinline__ uint32_t toeplitz64(uint32_t s, const uint32_t* U, co
 }
 
 __global__ __launch_bounds__(INTERP_THREADS) void k_interp(const ResJob* jobs, const int64_t* prefix,
-                                                           int njobs, uint32_t* ws, uint32_t* zero_word) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) *zero_word = 0u;  // abnormal counter, read by now
+                                                           int njobs, uint32_t* ws) {
   extern __shared__ uint4 sm4[];  // sections 16-byte aligned: IPAD and Dp are multiples of 64 words
   uint32_t* sm = reinterpret_cast<uint32_t*>(sm4);
   constexpr int NW = INTERP_THREADS / 64;
@@ -490,8 +374,7 @@ __global__ __launch_bounds__(256) void k_ffact_init() {
 }
 
 __global__ __launch_bounds__(64 * IBT) void k_interp_q(const ResJob* jobs, const int64_t* prefix, int njobs,
-                                                       uint32_t* ws, uint32_t* zero_word) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) *zero_word = 0u;  // abnormal counter, read by now
+                                                       uint32_t* ws) {
   __shared__ __align__(16) uint32_t U[64 * IFF_J];  // v_i / i!
   __shared__ uint32_t Wp[IPAD + 64 * IFF_J];  // zeros, then (-1)^j / j!
   __shared__ uint32_t part[IFF_J][64];        // convolution units of this Newton block
@@ -576,10 +459,9 @@ __global__ __launch_bounds__(64 * IBT) void k_interp_out(const ResJob* jobs, con
 }
 
 void launch_interp_blk(const ResJob* jobs_d, const int64_t* blk_prefix_d, int njobs, int64_t nblocks, uint32_t* ws,
-                       uint32_t* zero_word, hipStream_t s) {
+                       hipStream_t s) {
   if (nblocks <= 0) return;
-  hipLaunchKernelGGL(k_interp_q, dim3((unsigned)nblocks), dim3(64 * IBT), 0, s, jobs_d, blk_prefix_d, njobs, ws,
-                     zero_word);
+  hipLaunchKernelGGL(k_interp_q, dim3((unsigned)nblocks), dim3(64 * IBT), 0, s, jobs_d, blk_prefix_d, njobs, ws);
   hipLaunchKernelGGL(k_interp_out, dim3((unsigned)nblocks), dim3(64 * IBT), 0, s, jobs_d, blk_prefix_d, njobs, ws);
 }
 
@@ -589,10 +471,10 @@ size_t interp_lds_bytes(int max_D) {
 }
 
 void launch_interp(const ResJob* jobs_d, const int64_t* blk_prefix_d, int njobs, int64_t nblocks,
-                   int max_D, uint32_t* ws, uint32_t* zero_word, hipStream_t s) {
+                   int max_D, uint32_t* ws, hipStream_t s) {
   if (nblocks <= 0) return;
   hipLaunchKernelGGL(k_interp, dim3((unsigned)nblocks), dim3(INTERP_THREADS), interp_lds_bytes(max_D), s,
-                     jobs_d, blk_prefix_d, njobs, ws, zero_word);
+                     jobs_d, blk_prefix_d, njobs, ws);
 }
 
 // ---------------------------------------------------------------------------

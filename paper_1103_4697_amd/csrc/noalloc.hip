@@ -11,9 +11,8 @@
 // The array is a module global: each device holds one copy from the first
 // load of the library until the process ends, every call on a device shares
 // it and it keeps the last call's contents.  Nothing read by the pipeline
-// depends on its earlier contents except the abnormal-instance counter,
-// which is cleared (by a kernel) before the launches.  Calls that overlap on
-// one device race on the array; the host part of a call is serialised by a
+// depends on its earlier contents.  Calls that overlap on one device race on
+// the array; the host part of a call is serialised by a
 // mutex, which the call holds until its results are on the host.
 #include <hip/hip_runtime.h>
 
@@ -111,8 +110,6 @@ extern "C" int snc_resultant_y_noalloc(snc_ctx* c, const snc_bipoly* f, const sn
   fill_header(lay, P, F, G, g_header);
   e = hipMemcpyAsync(ws, g_header, lay.header_bytes, hipMemcpyHostToDevice, s);
   if (e != hipSuccess) return fail("upload", e);
-  // the only state a run reads before writing it: cleared by a kernel
-  launch_zero_u32((uint32_t*)(ws + lay.abn_count_off), 1, s);
   launch_pipeline(lay, ws, s, nullptr, PIPE_ALL);
   e = hipGetLastError();
   if (e != hipSuccess) return fail("launch", e);

@@ -98,7 +98,6 @@ void layout_batch(const std::vector<ResPlan>& plans, BatchLayout& lay) {
     lay.list_crts[c] = off; off = align256(off + 4 * std::max(lay.n_crts_jobs[c], 1));
   }
   lay.list_crtb = off; lay.list_crtm = off + 4 * lay.n_crtb_jobs; off = align256(off + 4 * std::max<size_t>(nbm, 1));
-  lay.pref_inst = off; off = align256(off + 8 * (NJ + 1));
   lay.list_im = off; off = align256(off + 4 * std::max(NJ, 1));
   for (int j = 0; j < NJ; ++j) {
     const ResPlan& P = plans[lay.dev[j]];
@@ -155,7 +154,6 @@ void layout_batch(const std::vector<ResPlan>& plans, BatchLayout& lay) {
       lay.max_T_ee[P.cls] = std::max(lay.max_T_ee[P.cls], P.T);
     }
     else lay.n_gen_inst += (int64_t)P.k * n1;
-    lay.total_inst += (int64_t)P.k * n1;
     lay.max_D = std::max(lay.max_D, P.D);
   }
   // Interpolation groups: rows of several jobs fill the 16-row operand tiles,
@@ -189,11 +187,7 @@ void layout_batch(const std::vector<ResPlan>& plans, BatchLayout& lay) {
   lay.reduce_in_eval = NJ > 0 && lay.n_gen_jobs == 0;
   for (int c = 0; c < NCLS; ++c)
     if (lay.n_ee_jobs[c] && !eval_elim_in_lds(lay.max_T_ee[c])) lay.reduce_in_eval = false;
-  lay.abn_count_off = w * 4; w += 64;
   lay.ee_counter_off = w * 4; w += 64;
-  lay.abn_list_off = w * 4;
-  lay.abn_cap = abn_list_cap(lay.total_inst);
-  w += align_words((size_t)lay.abn_cap * (sizeof(AbnEntry) / 4));
   lay.out_off = w * 4;
   size_t ow = 0;
   for (int j = 0; j < NJ; ++j) {
@@ -251,11 +245,8 @@ void launch_pipeline(const BatchLayout& lay, uint8_t* ws, hipStream_t s, StageTi
   const ResJob* jobs = (const ResJob*)(ws + lay.jobs_off);
   const RowDesc* rows = (const RowDesc*)(ws + lay.rows_off);
   const int NJ = (int)lay.jobs.size();
-  uint32_t* abn_count = (uint32_t*)(ws + lay.abn_count_off);
-  AbnEntry* abn_list = (AbnEntry*)(ws + lay.abn_list_off);
   if (part != PIPE_CRT) {
-  // the counter is cleared by the previous run's interpolation (and at preparation)
-  if (!lay.reduce_in_eval) launch_reduce(jobs, (const int64_t*)(ws + lay.pref_red), NJ, lay.nb_red, wsw, wsw, abn_count, s);
+  if (!lay.reduce_in_eval) launch_reduce(jobs, (const int64_t*)(ws + lay.pref_red), NJ, lay.nb_red, wsw, wsw, s);
   if (tm) tm->mark("reduce", lay.reduce_in_eval ? 0 : 1);
   // one stage per register class (names: eval_elim_<width>), then the
   // jobs above the register classes
@@ -269,7 +260,7 @@ void launch_pipeline(const BatchLayout& lay, uint8_t* ws, hipStream_t s, StageTi
     if (!lay.n_ee_jobs[c]) continue;
     launch_eval_elim(c, lay.ee_var[c], ee_counters + c, jobs, (const int32_t*)(ws + lay.list_ee[c]),
                      (const int64_t*)(ws + lay.pref_ee[c]), lay.n_ee_jobs[c], lay.nb_ee[c], lay.max_T_ee[c], rows,
-                     wsw, abn_count, abn_list, lay.abn_cap, lay.reduce_in_eval, s);
+                     wsw, lay.reduce_in_eval, s);
     if (tm) tm->mark(kEEStage[c], 1);
   }
   if (lay.n_gen_jobs) {
@@ -277,12 +268,9 @@ void launch_pipeline(const BatchLayout& lay, uint8_t* ws, hipStream_t s, StageTi
                             lay.n_gen_jobs, lay.n_gen_inst, rows, wsw, s);
     if (tm) tm->mark("eval_elim_general", 1);
   }
-  launch_elim_general(jobs, rows, wsw, abn_count, abn_list, lay.abn_cap, (const int64_t*)(ws + lay.pref_inst), NJ,
-                      s);
-  if (tm) tm->mark("elim_general", 1);
   launch_interp_mfma(jobs, (const int32_t*)(ws + lay.list_im), (const int32_t*)(ws + lay.start_im),
                      (const int64_t*)(ws + lay.pref_interp), (int)lay.im_start.size() - 1, lay.nb_interp, lay.im_lds,
-                     wsw, abn_count, s);
+                     rows, wsw, s);
   if (tm) tm->mark("interp", 1);
   }
   if (part == PIPE_TO_INTERP) return;
@@ -354,7 +342,6 @@ void fill_header(const BatchLayout& lay, const std::vector<ResPlan>& plans, cons
   int64_t* pr = (int64_t*)(h + lay.pref_red);
   int64_t* pd = (int64_t*)(h + lay.pref_crtd);
   int64_t* pc = (int64_t*)(h + lay.pref_crtc);
-  int64_t* pn = (int64_t*)(h + lay.pref_inst);
   int64_t* pe[NCLS];
   int32_t* le[NCLS];
   int ne[NCLS] = {0};
@@ -383,7 +370,7 @@ void fill_header(const BatchLayout& lay, const std::vector<ResPlan>& plans, cons
   int32_t* lg = (int32_t*)(h + lay.list_gen);
   int ng = 0;
   pg[0] = 0;
-  pr[0] = pd[0] = pc[0] = pn[0] = 0;
+  pr[0] = pd[0] = pc[0] = 0;
   size_t cw = 0;
   for (int j = 0; j < NJ; ++j) {
     const int idx = lay.dev[j];
@@ -439,7 +426,6 @@ void fill_header(const BatchLayout& lay, const std::vector<ResPlan>& plans, cons
       pc[nbig + 1] = pc[nbig] + (n1 + CRT_COMB_PER_BLOCK - 1) / CRT_COMB_PER_BLOCK;
       nbig++;
     }
-    pn[j + 1] = pn[j] + (int64_t)P.k * n1;
     if (P.cls >= 0) {
       by_cost[P.cls].push_back({eval_block_cost(P), j});
     } else {
@@ -524,10 +510,6 @@ int prepare_resultants(snc_ctx* c, int n, const snc_bipoly* f, const snc_bipoly*
       // launch variants of the evaluation kernel: measured for a batched graph, looked up otherwise
       const int st = choose_eval_variants(c, pr->lay, pr->ws, stream, use_graph);
       if (st) { destroy_prepared(pr); return st; }
-    }
-    if (e == hipSuccess) {  // the abnormal-instance counter starts at zero; each run's interpolation clears it
-      launch_zero_u32((uint32_t*)(pr->ws + lay.abn_count_off), 1, stream);
-      e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
     if (e != hipSuccess) { c->err = std::string("input upload: ") + hipGetErrorString(e); destroy_prepared(pr); return SNC_EDEVICE; }

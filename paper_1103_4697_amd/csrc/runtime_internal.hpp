@@ -52,7 +52,6 @@ struct BatchLayout {
   std::vector<ResJob> jobs;          // device job descriptors (offsets filled)
   size_t jobs_off = 0, rows_off = 0, coef_off = 0;        // bytes
   size_t pref_red = 0, pref_interp = 0, pref_crtd = 0, pref_crtc = 0, pref_gen = 0;  // bytes
-  size_t pref_inst = 0;              // bytes: instance prefix k (D+1) over the jobs
   // interpolation: jobs by degree bound, largest first, cut into groups that
   // share a workgroup per prime; bytes of the list, the groups' first entries
   // and the prefix of their prime counts (pref_interp)
@@ -74,8 +73,6 @@ struct BatchLayout {
   EEVariant ee_var[NCLS];            // launch variant of each register class (autotuner, or the defaults)
   size_t ee_counter_off = 0;         // bytes: the NCLS work counters of persistent evaluation launches
   size_t header_bytes = 0;
-  size_t abn_count_off = 0, abn_list_off = 0;              // bytes
-  uint32_t abn_cap = 0;
   size_t out_off = 0, out_words = 0;                       // bytes / words
   size_t sq_off = 0, sq_words = 0;  // bytes / words: gcd(R, R') descriptors, work items, e and d
   size_t total_bytes = 0;
@@ -83,7 +80,6 @@ struct BatchLayout {
   int64_t nb_ee[NCLS] = {0};
   int n_ee_jobs[NCLS] = {0}, n_gen_jobs = 0, n_rows = 0, max_D = 0, max_k = 0;
   int max_T_ee[NCLS] = {0};  // largest residue count per prime among a class's jobs
-  int64_t total_inst = 0;
   size_t coef_words = 0;
 };
 

@@ -101,17 +101,9 @@ struct GcdDesc {
 // gcd degree written for a prime dividing both leading coefficients (the prime is not used)
 constexpr int32_t GCD_SLOT_UNUSABLE = -2;
 
-// abnormal (prime, point) instance queued for the general elimination
-struct AbnEntry {
-  int32_t job, prime, point, pad;
-};
-// value left at an abnormal instance's point until the general pass (no residue is >= 2^30)
+// value left at an abnormal instance's point for the interpolation, which
+// computes it by the general elimination (no residue is >= 2^30)
 constexpr uint32_t ABN_MARK = 0xffffffffu;
-// capacity of the abnormal-instance list of a batch of ninst instances
-inline uint32_t abn_list_cap(int64_t ninst) {
-  const int64_t c = ninst / 16 > 4096 ? ninst / 16 : 4096;
-  return (uint32_t)(c < ninst ? c : ninst);
-}
 
 __host__ __device__ inline int lx_of(int k) { return (30 * k + 31) / 32 + 2; }
 
@@ -127,7 +119,7 @@ constexpr int IFF_J = 16;
 constexpr int IFF_K = 256;
 inline bool interp_blk_fits(int max_D, int max_k) { return max_D + 1 <= 64 * IFF_J && max_k <= IFF_K; }
 void launch_interp_blk(const ResJob* jobs_d, const int64_t* blk_prefix_d, int njobs, int64_t nblocks, uint32_t* ws,
-                       uint32_t* zero_word, hipStream_t s);
+                       hipStream_t s);
 void launch_zero_u32(uint32_t* p, int64_t n, hipStream_t s);
 // Evaluation points of the resultants: x_j = q^j mod p, q = q(p) of order
 // above MAX_D.  Row p of the table: q^l for l < 64, then q^(64 b) at 64 + b.
@@ -149,11 +141,10 @@ constexpr int64_t IM_MIN_BLOCKS = 1024;        // workgroups wanted before jobs 
 size_t interp_mfma_lds(int max_D, int blocks); // largest degree bound, 64-point blocks of all jobs
 hipError_t configure_interp_mfma();
 void launch_interp_mfma(const ResJob* jobs_d, const int32_t* job_list_d, const int32_t* gstart_d,
-                        const int64_t* gprefix_d, int ngroups, int64_t nblocks, size_t lds, uint32_t* ws,
-                        uint32_t* zero_word, hipStream_t s);
-// zero_word (may be null) is set to zero by the same launch
+                        const int64_t* gprefix_d, int ngroups, int64_t nblocks, size_t lds, const RowDesc* rows_d,
+                        uint32_t* ws, hipStream_t s);
 void launch_reduce(const ResJob* jobs_d, const int64_t* blk_prefix_d, int njobs, int64_t nblocks,
-                   const uint32_t* ws, uint32_t* res_base, uint32_t* zero_word, hipStream_t s);
+                   const uint32_t* ws, uint32_t* res_base, hipStream_t s);
 // the evaluation kernel stages a prime's residues in LDS up to this size
 constexpr int EE_LDS_MAX = 64 * 1024;
 inline bool eval_elim_in_lds(int max_T) { return (size_t)max_T * sizeof(uint32_t) <= (size_t)EE_LDS_MAX; }
@@ -178,19 +169,13 @@ int eval_elim_scratch(int cls, int wpe, int max_T);
 // reduce_in: the residues are reduced from the input limbs inside the kernel (LDS variant only)
 void launch_eval_elim(int cls, const EEVariant& v, uint32_t* counter, const ResJob* jobs_d,
                       const int32_t* job_list_d, const int64_t* blk_prefix_d, int njobs, int64_t nblocks,
-                      int max_T, const RowDesc* rows_d, uint32_t* ws, uint32_t* abn_count, AbnEntry* abn_list,
-                      uint32_t abn_cap, bool reduce_in, hipStream_t s);
-// abnormal instances: the list when count <= cap, else a scan of every
-// instance for ABN_MARK (inst_prefix: prefix sums of k (D+1) over the jobs)
-void launch_elim_general(const ResJob* jobs_d, const RowDesc* rows_d, uint32_t* ws,
-                         const uint32_t* abn_count, const AbnEntry* abn_list, uint32_t cap,
-                         const int64_t* inst_prefix_d, int njobs, hipStream_t s);
+                      int max_T, const RowDesc* rows_d, uint32_t* ws, bool reduce_in, hipStream_t s);
 void launch_elim_general_all(const ResJob* jobs_d, const int32_t* job_list_d,
                              const int64_t* inst_prefix_d, int njobs, int64_t ninst,
                              const RowDesc* rows_d, uint32_t* ws, hipStream_t s);
-// the interpolation launches also clear zero_word (the abnormal-instance counter)
+// interpolation at the points 0..D (bivariate gcd images)
 void launch_interp(const ResJob* jobs_d, const int64_t* blk_prefix_d, int njobs, int64_t nblocks,
-                   int max_D, uint32_t* ws, uint32_t* zero_word, hipStream_t s);
+                   int max_D, uint32_t* ws, hipStream_t s);
 // job_list_d: the jobs of the launch (block prefix over them), or null for jobs 0..njobs-1
 void launch_crt_digits(const CrtTables& tb, const ResJob* jobs_d, const int32_t* job_list_d, const int64_t* prefix_d,
                        int njobs, int64_t nblocks, uint32_t* ws, hipStream_t s);

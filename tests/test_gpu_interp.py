@@ -56,3 +56,23 @@ def test_groups_of_jobs(njobs, bits):
     for _ in range(3):
         b.run()
         assert b.results() == want
+
+
+@pytest.mark.parametrize("d", [4, 20, 64])
+@pytest.mark.parametrize("roots", [1, 3, 40])
+def test_abnormal_points_beside_normal_ones(d, roots):
+    """lc_y(f) vanishes at the first `roots` evaluation points of the first prime's power sequence
+    (1, q, q^2, .. as integers: q is 2 or 3 for every prime of the table's head), so some points of a prime
+    take the general elimination and the others do not; against y-reversed operands, whose leading
+    coefficients are constants: res(y^m f(1/y), y^n g(1/y)) = (-1)^(mn) res(f, g)."""
+    rnd = random.Random(100 * d + roots)
+    lc = [1]
+    for i in range(min(roots, 12)):  # (x - 2^i): integer roots shared by every prime
+        lc = [int(v) for v in np.convolve(np.array(lc, dtype=object), np.array([-(2 ** i), 1], dtype=object))]
+    m, n = d, max(d - 1, 1)
+    f = [[rnd.randint(1, 99)]] + [[rnd.randint(-99, 99), rnd.randint(-9, 9)] for _ in range(m - 1)] + [lc]
+    g = [[rnd.randint(1, 99)]] + [[rnd.randint(-99, 99)] for _ in range(n - 1)] + [[rnd.randint(1, 99)]]
+    got = snc.resultant_y(f, g)
+    rev = snc.resultant_y(f[::-1], g[::-1])
+    assert got == [(-1) ** (m * n) * c for c in rev]
+    assert got
