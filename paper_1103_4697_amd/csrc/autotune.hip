@@ -123,12 +123,15 @@ int choose_eval_variants(snc_ctx* c, BatchLayout& lay, uint8_t* ws, hipStream_t 
   bool any = false;
   for (int k = 0; k < NCLS; ++k) any |= lay.n_ee_jobs[k] > 0;
   if (!any) return SNC_OK;
-  hipDeviceProp_t prop;
-  if (hipGetDeviceProperties(&prop, c->device) != hipSuccess) {
-    c->err = "autotune: device query failed";
-    return SNC_EDEVICE;
+  if (c->device_tag.empty()) {
+    hipDeviceProp_t prop;
+    if (hipGetDeviceProperties(&prop, c->device) != hipSuccess) {
+      c->err = "autotune: device query failed";
+      return SNC_EDEVICE;
+    }
+    c->device_tag = device_tag(prop);
   }
-  const std::string tag = device_tag(prop);
+  const std::string tag = c->device_tag;
   const auto t0 = std::chrono::steady_clock::now();
   int st = SNC_OK;
   hipEvent_t e0 = nullptr, e1 = nullptr;

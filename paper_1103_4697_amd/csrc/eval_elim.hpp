@@ -489,11 +489,12 @@ int eval_elim_grid_cls(int wpe, int max_T) {
   const bool in_lds = eval_elim_in_lds(max_T);
   const size_t lds = in_lds ? (size_t)max_T * sizeof(uint32_t) : 0;
   const void* k = in_lds ? ee_kernel_ptr<NN, true>(wpe) : ee_kernel_ptr<NN, false>(wpe);
-  int per_cu = 0, dev = 0;
-  hipDeviceProp_t prop;
-  if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return 0;
+  int per_cu = 0, dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    return 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, EE_BLOCK, lds) != hipSuccess) return 0;
-  return per_cu * prop.multiProcessorCount;
+  return per_cu * cus;
 }
 
 // private (spill) bytes per lane of a variant's kernel, -1 if unknown

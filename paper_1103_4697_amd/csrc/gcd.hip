@@ -2373,7 +2373,7 @@ int snc_arrangement_run(snc_arrangement* A, void* d_ws, size_t ws_bytes, void* s
   }
   if (!A->prep) {
     const int st = prepare_resultants(ctx, (int)A->F.size(), A->F.data(), A->G.data(), d_ws, ws_bytes,
-                                      (hipStream_t)stream, /*graph=*/true, &A->prep);
+                                      (hipStream_t)stream, /*graph=*/true, /*one_shot=*/false, &A->prep);
     if (st) return st;
     A->prep_ws = d_ws;
     A->prep_bytes = ws_bytes;

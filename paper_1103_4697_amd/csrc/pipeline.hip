@@ -471,7 +471,7 @@ void fill_header(const BatchLayout& lay, const std::vector<ResPlan>& plans, cons
   } while (0)
 
 int prepare_resultants(snc_ctx* c, int n, const snc_bipoly* f, const snc_bipoly* g, void* d_ws,
-                       size_t ws_bytes, hipStream_t stream, bool use_graph, snc_prepared** outp) {
+                       size_t ws_bytes, hipStream_t stream, bool use_graph, bool one_shot, snc_prepared** outp) {
   *outp = nullptr;
   HIPCHK(hipSetDevice(c->device));
   std::vector<Operand> F(n), G(n);
@@ -496,7 +496,17 @@ int prepare_resultants(snc_ctx* c, int n, const snc_bipoly* f, const snc_bipoly*
     }
     pr->ws = (uint8_t*)d_ws;
     if (c->stage_in(lay.header_bytes)) { c->err = "pinned staging allocation failed"; delete pr; return SNC_EDEVICE; }
-    if (hipHostMalloc(&pr->h_out, std::max<size_t>(lay.out_words * 4, 4), hipHostMallocDefault) != hipSuccess) {
+    // a handle keeps a pinned block of its own; a single call takes the
+    // context's (pinning and unpinning a block cost 200-400 us a call)
+    pr->own_out = !one_shot;
+    bool pinned;
+    if (one_shot) {
+      pinned = c->stage_out(lay.out_words * 4) == SNC_OK;
+      pr->h_out = c->h_out;
+    } else {
+      pinned = hipHostMalloc(&pr->h_out, std::max<size_t>(lay.out_words * 4, 4), hipHostMallocDefault) == hipSuccess;
+    }
+    if (!pinned) {
       pr->h_out = nullptr;
       c->err = "pinned staging allocation failed";
       delete pr;
@@ -511,7 +521,9 @@ int prepare_resultants(snc_ctx* c, int n, const snc_bipoly* f, const snc_bipoly*
       const int st = choose_eval_variants(c, pr->lay, pr->ws, stream, use_graph);
       if (st) { destroy_prepared(pr); return st; }
     }
-    if (e == hipSuccess) e = hipStreamSynchronize(stream);
+    // a single call waits once, for its results; the staging buffer is not
+    // written again before that
+    if (e == hipSuccess && !one_shot) e = hipStreamSynchronize(stream);
     if (e != hipSuccess) { c->err = std::string("input upload: ") + hipGetErrorString(e); destroy_prepared(pr); return SNC_EDEVICE; }
   }
   *outp = pr;
@@ -804,10 +816,12 @@ int run_prepared_fork(snc_prepared* pr, hipStream_t stream, const std::function<
 int run_resultants(snc_ctx* c, int n, const snc_bipoly* f, const snc_bipoly* g, void* d_ws,
                    size_t ws_bytes, hipStream_t stream, snc_upoly* out, bool use_graph) {
   snc_prepared* pr = nullptr;
-  int st = prepare_resultants(c, n, f, g, d_ws, ws_bytes, stream, use_graph, &pr);
-  if (st) return st;
-  st = run_prepared(pr, stream, out);
-  destroy_prepared(pr);
+  int st = prepare_resultants(c, n, f, g, d_ws, ws_bytes, stream, use_graph, true, &pr);
+  if (st == SNC_OK) {
+    st = run_prepared(pr, stream, out);
+    destroy_prepared(pr);
+  }
+  if (st) (void)hipStreamSynchronize(stream);  // nothing in flight reads the staging buffers of a failed call
   return st;
 }
 
@@ -821,7 +835,7 @@ void destroy_prepared(snc_prepared* pr) {
     for (hipEvent_t e : pr->slot_ev[s]) (void)hipEventDestroy(e);
   }
   if (pr->gexec) (void)hipGraphExecDestroy(pr->gexec);
-  if (pr->h_out) (void)hipHostFree(pr->h_out);
+  if (pr->h_out && pr->own_out) (void)hipHostFree(pr->h_out);
   if (pr->h_ed) (void)hipHostFree(pr->h_ed);
   for (hipEvent_t e : pr->d2h_ev) (void)hipEventDestroy(e);
   delete pr;

@@ -136,16 +136,16 @@ static bool coef_is_zero(const uint32_t* c, int nl) {
 // the caller's margin covers); no overflow at any size
 static double coef_log2_abs(const uint32_t* c, int nl) {
   const bool neg = c[nl - 1] >> 31;
-  std::vector<uint32_t> m(c, c + nl);
-  if (neg) {  // magnitude = ~c + 1
-    uint64_t carry = 1;
-    for (int l = 0; l < nl; ++l) { uint64_t t = (uint64_t)(~c[l]) + carry; m[l] = (uint32_t)t; carry = t >> 32; }
-  }
+  // magnitude limb l of a negative value: -c has the bits ~c + 1, whose carry
+  // reaches l when every lower limb is zero
+  int low = 0;
+  while (c[low] == 0) ++low;  // c is non-zero
+  auto mag = [&](int l) { return !neg ? c[l] : l > low ? ~c[l] : l == low ? 0u - c[l] : 0u; };
   int t = nl - 1;
-  while (t > 0 && m[t] == 0) --t;
+  while (t > 0 && mag(t) == 0) --t;
   double v = 0.0;
   int used = 0;
-  for (int l = t; l >= 0 && used < 3; --l, ++used) v = v * 4294967296.0 + (double)m[l];
+  for (int l = t; l >= 0 && used < 3; --l, ++used) v = v * 4294967296.0 + (double)mag(l);
   return std::log2(v + 1.0) + 32.0 * (t + 1 - used);
 }
 
@@ -420,7 +420,7 @@ int snc_resultant_y_batch_plan(int32_t n, const snc_bipoly* f, const snc_bipoly*
 int snc_resultant_y_prepare(snc_ctx* c, int32_t n, const snc_bipoly* f, const snc_bipoly* g,
                             void* d_ws, size_t ws_bytes, void* stream, snc_prepared** out) {
   if (!c || !out || n < 0 || (n > 0 && (!f || !g))) return SNC_EINVAL;
-  return prepare_resultants(c, n, f, g, d_ws, ws_bytes, (hipStream_t)stream, /*graph=*/true, out);
+  return prepare_resultants(c, n, f, g, d_ws, ws_bytes, (hipStream_t)stream, /*graph=*/true, /*one_shot=*/false, out);
 }
 
 int snc_prepared_run(snc_prepared* p, void* stream, snc_upoly* out) {

@@ -110,6 +110,7 @@ struct snc_ctx {
   int gcd_variant = 0;  // Euclid of the square-free check: 0 automatic (one wavefront), 1 one wavefront, 2 blocked
   snc::EEVariant forced[snc::NCLS];  // wpe > 0: variant forced for every launch of that class (0: none)
   std::vector<EETuneReport> tune_report;  // the last batched preparation's choices
+  std::string device_tag;                 // architecture and CU count of the device (autotuner cache key)
   float tune_ms = 0.f;                    // host wall time spent tuning in that preparation
   std::vector<const char*> stage_names;
   std::vector<float> stage_ms;
@@ -149,7 +150,8 @@ struct snc_prepared {
   std::vector<snc::ResPlan> P;
   snc::BatchLayout lay;
   uint8_t* ws = nullptr;
-  void* h_out = nullptr;
+  void* h_out = nullptr;             // pinned copy of the output block
+  bool own_out = true;               // false: the context's staging buffer (a call that ends with its results)
   hipGraphExec_t gexec = nullptr;    // whole pipeline
   std::vector<hipEvent_t> d2h_ev;    // chunks of the result download (large batches)
   // projection step (resultant and gcd(R, R')): the Euclid descriptors are
@@ -190,7 +192,7 @@ void launch_pipeline(const BatchLayout& lay, uint8_t* ws, hipStream_t s, StageTi
 // choices or the defaults; fills lay.ee_var and the context's report
 int choose_eval_variants(snc_ctx* c, BatchLayout& lay, uint8_t* ws, hipStream_t s, bool tune);
 int prepare_resultants(snc_ctx* c, int n, const snc_bipoly* f, const snc_bipoly* g, void* d_ws,
-                       size_t ws_bytes, hipStream_t stream, bool use_graph, snc_prepared** outp);
+                       size_t ws_bytes, hipStream_t stream, bool use_graph, bool one_shot, snc_prepared** outp);
 int run_prepared(snc_prepared* pr, hipStream_t stream, snc_upoly* out);
 // pipelined runs: submit enqueues a run and the download of its results
 // into a free staging slot (SNC_EAGAIN when both hold uncollected runs);
