@@ -35,19 +35,69 @@ __device__ __forceinline__ int find_job(const int64_t* prefix, int njobs, int64_
   return lo;
 }
 
-// signed coefficient of nl two's-complement limbs -> canonical Montgomery residue
-// limb l of the coefficient at limbs[l stride] (limb-major: neighbouring
-// lanes read neighbouring words)
-__device__ __forceinline__ uint32_t reduce_limbs(const uint32_t* limbs, int nl, int64_t stride, const PrimeC& c) {
-  const uint32_t mask = (limbs[(nl - 1) * stride] >> 31) ? 0xffffffffu : 0u;
-  uint32_t acc = 0;
-  for (int l = nl - 1; l >= 0; --l) {
-    uint64_t v = (uint64_t)acc * c.r2 + (uint64_t)(limbs[l * stride] ^ mask) * c.r2;
-    acc = redc(v, c.p, c.pinv);
+// Signed coefficient of nl two's-complement limbs, limb l at
+// limbs[l stride] (limb-major: neighbouring lanes read neighbouring words),
+// reduced mod NP primes to canonical Montgomery residues.  pw: rows of the
+// power table of the primes, uniform across the wavefront: entry l = 2^(32 l)
+// 2^64 mod p (l <= 64), entry POW32_STEP the Montgomery form of 2^2048, which
+// joins blocks of 64 limbs.  Four products of a 32-bit limb and an entry stay
+// below 2^64; their sum times 2^-32 is its high word plus REDC of its low
+// word, and up to sixteen such pairs (below 2^37) are reduced at the end of
+// a block: 1 + 6/4 vector instructions per limb instead of 6 (a Horner step
+// per limb).
+//
+// reduce_limbs4: the same for nl <= 4 limbs already in registers (those past
+// nl zero).
+__device__ __forceinline__ uint32_t reduce_limbs4(const uint32_t (&v)[4], int nl, const PrimeC& c, const uint32_t* pw) {
+  uint64_t a = 0;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) a += (uint64_t)v[u] * pw[u];
+  const uint32_t lo = (uint32_t)a;
+  const uint64_t H = (a >> 32) + __umulhi(lo * c.pinv, c.p) + (lo != 0u ? 1u : 0u);
+  const uint32_t s = canon2(redc((uint64_t)redc(H, c.p, c.pinv) * c.r2, c.p, c.pinv), c.p);
+  const uint32_t top = nl == 1 ? v[0] : nl == 2 ? v[1] : nl == 3 ? v[2] : v[3];
+  const uint32_t e = canon2(redc((uint64_t)pw[nl], c.p, c.pinv), c.p);  // 2^(32 nl), uniform
+  return (top >> 31) ? msub(s, e, c.p) : s;
+}
+
+template <int NP>
+__device__ __forceinline__ void reduce_limbs(uint32_t (&out)[NP], const uint32_t* limbs, int nl, int64_t stride,
+                                             const PrimeC (&c)[NP], const uint32_t* pw) {
+  const bool neg = limbs[(nl - 1) * stride] >> 31;
+  const int top = (nl - 1) / 64;
+  for (int b = top; b >= 0; --b) {
+    const int cnt = min(64, nl - 64 * b);
+    const uint32_t* x = limbs + (int64_t)64 * b * stride;
+    uint64_t H[NP];
+#pragma unroll
+    for (int r = 0; r < NP; ++r) H[r] = 0;
+    for (int l = 0; l < cnt; l += 4) {
+      uint32_t v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = l + u < cnt ? x[(l + u) * stride] : 0u;
+#pragma unroll
+      for (int r = 0; r < NP; ++r) {
+        const uint32_t* p = pw + r * POW32_ROW + l;
+        uint64_t a = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) a += (uint64_t)v[u] * p[u];
+        const uint32_t lo = (uint32_t)a;
+        const uint32_t t = __umulhi(lo * c[r].pinv, c[r].p) + (lo != 0u ? 1u : 0u);  // REDC(lo) <= p
+        H[r] += (a >> 32) + t;
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < NP; ++r) {
+      const uint32_t* p = pw + r * POW32_ROW;
+      uint32_t s = canon2(redc((uint64_t)redc(H[r], c[r].p, c[r].pinv) * c[r].r2, c[r].p, c[r].pinv), c[r].p);
+      if (b == top) {
+        if (neg) s = msub(s, canon2(redc((uint64_t)p[cnt], c[r].p, c[r].pinv), c[r].p), c[r].p);  // - 2^(32 nl)
+        out[r] = s;
+      } else {
+        out[r] = madd(mmulc(out[r], p[POW32_STEP], c[r].p, c[r].pinv), s, c[r].p);
+      }
+    }
   }
-  acc = canon(acc, c.p);
-  if (mask) acc = mneg(madd(acc, c.r1, c.p), c.p);  // -(~x + 1)
-  return acc;
 }
 
 // ---------------------------------------------------------------------------
@@ -338,7 +388,8 @@ template <int N, bool LDSROWS>
 __device__ __forceinline__ void eval_elim_block(int64_t b, const PrimeC* primes, const ResJob* jobs,
                                                 const int32_t* job_list, const int64_t* prefix, int njobs,
                                                 const RowDesc* rows, uint32_t* ws, int reduce_in, uint32_t* er,
-                                                const uint32_t* points, int64_t& staged) {
+                                                const uint32_t* points, const uint32_t* pow32,
+                                                int64_t& staged) {
   const int jj = find_job(prefix, njobs, b);
   const int jid = job_list[jj];
   const ResJob J = jobs[jid];
@@ -356,14 +407,47 @@ __device__ __forceinline__ void eval_elim_block(int64_t b, const PrimeC* primes,
       __syncthreads();    // the previous block's reads of the LDS rows are done
       if (reduce_in) {
         uint32_t* rg = ws + J.res_off + (int64_t)pi * J.T;
+        const uint32_t* pw = pow32 + (int64_t)pi * POW32_ROW;
+        const uint32_t* limbs = ws + J.coef_off;
         const bool store = lb % npb == 0;
-        for (int x = threadIdx.x; x < J.T; x += EE_BLOCK) {
-          const uint32_t v = reduce_limbs(ws + J.coef_off + x, J.nl, J.T, c);
-          er[x] = v;
-          if (store) rg[x] = v;
+        if (J.nl <= 4) {  // four coefficients at a time: a lone wavefront waits once for their limbs
+          for (int x0 = threadIdx.x; x0 < J.T; x0 += 4 * EE_BLOCK) {
+            uint32_t v[4][4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+              for (int l = 0; l < 4; ++l) {
+                const int x = x0 + u * EE_BLOCK;
+                v[u][l] = x < J.T && l < J.nl ? limbs[(int64_t)l * J.T + x] : 0u;
+              }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              const int x = x0 + u * EE_BLOCK;
+              if (x < J.T) {
+                const uint32_t w = reduce_limbs4(v[u], J.nl, c, pw);
+                er[x] = w;
+                if (store) rg[x] = w;
+              }
+            }
+          }
+        } else {
+          for (int x = threadIdx.x; x < J.T; x += EE_BLOCK) {
+            uint32_t w[1];
+            const PrimeC c1[1] = {c};
+            reduce_limbs<1>(w, limbs + x, J.nl, J.T, c1, pw);
+            er[x] = w[0];
+            if (store) rg[x] = w[0];
+          }
         }
       } else {
-        for (int x = threadIdx.x; x < J.T; x += EE_BLOCK) er[x] = r[x];
+        for (int x0 = threadIdx.x; x0 < J.T; x0 += 4 * EE_BLOCK) {
+          uint32_t v[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) v[u] = x0 + u * EE_BLOCK < J.T ? r[x0 + u * EE_BLOCK] : 0u;
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            if (x0 + u * EE_BLOCK < J.T) er[x0 + u * EE_BLOCK] = v[u];
+        }
       }
       __syncthreads();
       staged = key;
@@ -432,7 +516,7 @@ __device__ __forceinline__ void eval_elim_block(int64_t b, const PrimeC* primes,
 // blocks to be taken are the cheapest.
 struct EEWork {
   uint32_t* counter;
-  const uint32_t* points;  // table of the evaluation points
+  const uint32_t *points, *pow32;  // tables of the evaluation points and of the powers of 2^32
   int32_t chunk;
 };
 
@@ -449,7 +533,7 @@ __global__ __launch_bounds__(EE_BLOCK) __attribute__((amdgpu_waves_per_eu(WPE)))
   int64_t staged = -1;
   if (wk.chunk == 0) {
     eval_elim_block<N, LDSROWS>(xcd_block(blockIdx.x, gridDim.x), primes, jobs, job_list, prefix, njobs, rows,
-                                ws, reduce_in, er, wk.points, staged);
+                                ws, reduce_in, er, wk.points, wk.pow32, staged);
     return;
   }
   const int64_t nb = prefix[njobs];
@@ -461,7 +545,7 @@ __global__ __launch_bounds__(EE_BLOCK) __attribute__((amdgpu_waves_per_eu(WPE)))
     const int64_t end = (int64_t)base + wk.chunk < nb ? (int64_t)base + wk.chunk : nb;
     for (int64_t b = base; b < end; ++b)
       eval_elim_block<N, LDSROWS>(b, primes, jobs, job_list, prefix, njobs, rows, ws, reduce_in, er,
-                                  wk.points, staged);
+                                  wk.points, wk.pow32, staged);
   }
 }
 
@@ -516,7 +600,7 @@ void launch_eval_elim_cls(const EEVariant& v, uint32_t* counter, const PrimeC* p
   const bool in_lds = eval_elim_in_lds(max_T);
   const size_t lds = in_lds ? (size_t)max_T * sizeof(uint32_t) : 0;
   const int red = reduce_in && in_lds ? 1 : 0;
-  const EEWork wk{counter, points_table(), persistent ? v.chunk : 0};
+  const EEWork wk{counter, points_table(), pow32_table(), persistent ? v.chunk : 0};
   const void* k = in_lds ? ee_kernel_ptr<NN, true>(v.wpe) : ee_kernel_ptr<NN, false>(v.wpe);
   void* args[] = {(void*)&primes, (void*)&jobs_d, (void*)&job_list_d, (void*)&blk_prefix_d, (void*)&njobs,
                   (void*)&rows_d, (void*)&ws, (void*)&red, (void*)&wk};

@@ -1691,7 +1691,7 @@ static int bivariate_gcd_run(snc_ctx* ctx, const std::vector<UPoly>& A, const st
     jr.coef_off = (int64_t)(Y.coef / 4);
     jr.res_off = (int64_t)(Y.res / 4);
     std::memcpy(hdr.data() + Y.jr, &jr, sizeof jr);
-    const int64_t pr[2] = {0, (int64_t)k * ((T + 255) / 256)};
+    const int64_t pr[2] = {0, reduce_blocks(k, T)};
     std::memcpy(hdr.data() + Y.pref_red, pr, sizeof pr);
     std::memcpy(hdr.data() + Y.coef, coef.data(), coef.size() * 4);
     HIPCHK(hipMemcpyAsync(ws, hdr.data(), Y.regions, hipMemcpyHostToDevice, stream));

@@ -119,6 +119,7 @@ void layout_batch(const std::vector<ResPlan>& plans, BatchLayout& lay) {
   size_t w = off / 4;
   size_t coefw = lay.coef_off / 4;
   int rows = 0;
+  double reduce_again = 0;  // wavefront instructions of reducing a prime's inputs for every block but the first
   for (int j = 0; j < NJ; ++j) {
     const ResPlan& P = plans[lay.dev[j]];
     ResJob& J = lay.jobs[j];
@@ -136,7 +137,8 @@ void layout_batch(const std::vector<ResPlan>& plans, BatchLayout& lay) {
     J.nq_off = (int64_t)w; w += align_words((size_t)P.k * ((n1 + 63) / 64) * 64);
     J.dig_off = (int64_t)w; w += align_words(n1 * P.k);
     J.acc_off = (int64_t)w;  // unused: the combine step keeps its accumulators in LDS
-    lay.nb_red += (int64_t)P.k * ((P.T + 255) / 256);
+    lay.nb_red += reduce_blocks(P.k, P.T);
+    reduce_again += (double)P.k * ((n1 - 1) / EE_BLOCK) * ((P.T + 63) / 64) * (3 * P.nl + 8);
     const int cc = lay.crt_small_on ? crt_small_class(P.k) : -1;
     if (cc >= 0) {
       lay.nb_crts[cc] += (int64_t)((n1 + 63) / 64);
@@ -183,8 +185,12 @@ void layout_batch(const std::vector<ResPlan>& plans, BatchLayout& lay) {
     lay.im_start.push_back(u);
     t = u;
   }
-  // every job on the evaluation kernel's LDS variant: it reduces the inputs itself
-  lay.reduce_in_eval = NJ > 0 && lay.n_gen_jobs == 0;
+  // Every job on the evaluation kernel's LDS variant: it can reduce the
+  // inputs itself, once per 64-point block of a prime.  With long
+  // coefficients the repeats cost more than a launch: past about 4e6 wavefront
+  // instructions (7 us of the whole chip) the reduction runs before it, once
+  // per prime.
+  lay.reduce_in_eval = NJ > 0 && lay.n_gen_jobs == 0 && reduce_again < 4e6;
   for (int c = 0; c < NCLS; ++c)
     if (lay.n_ee_jobs[c] && !eval_elim_in_lds(lay.max_T_ee[c])) lay.reduce_in_eval = false;
   lay.ee_counter_off = w * 4; w += 64;
@@ -409,7 +415,7 @@ void fill_header(const BatchLayout& lay, const std::vector<ResPlan>& plans, cons
     emit(B, ra + P.rstride, P.n);
     cw += (size_t)P.T * P.nl;
     const int64_t n1 = P.D + 1;
-    pr[j + 1] = pr[j] + (int64_t)P.k * ((P.T + 255) / 256);
+    pr[j + 1] = pr[j] + reduce_blocks(P.k, P.T);
     const int cc = lay.crt_small_on ? crt_small_class(P.k) : -1;
     if (cc >= 0) {
       ls[cc][ns[cc]] = j;

@@ -119,6 +119,7 @@ int ensure_device_tables(int device, std::string& err) {
   if (e != hipSuccess) { err = std::string("table upload: ") + hipGetErrorString(e); return SNC_EDEVICE; }
   (void)global_crt_tables();
   (void)points_table();
+  (void)pow32_table();
   done.insert(device);
   return SNC_OK;
 }

@@ -130,6 +130,15 @@ __device__ __forceinline__ uint32_t point_mont(const uint32_t* points, int pi, i
   const uint32_t t = mmul(r[64 + (j >> 6)], r[j & 63], c.p, c.pinv);
   return canon2(t, c.p);
 }
+// Powers of 2^32 for the reduction of multi-limb inputs, a row per prime:
+// entry l <= 64 = 2^(32 l) 2^64 mod p, entry POW32_STEP = Montgomery form of 2^2048
+constexpr int POW32_ROW = 68, POW32_STEP = 65;
+const uint32_t* pow32_table();           // of the current device
+// residues: workgroups of 64 coefficients for RED_PRIMES primes
+constexpr int RED_PRIMES = 8;
+inline int64_t reduce_blocks(int k, int T) {
+  return (int64_t)((k + RED_PRIMES - 1) / RED_PRIMES) * ((T + 63) / 64);
+}
 void launch_points_init(hipStream_t s);  // points and interpolation tables (once per device)
 const uint32_t* points_table();          // of the current device
 // Interpolation at those points: a workgroup per prime of a group of jobs
@@ -161,7 +170,7 @@ constexpr int EE_WPE_MAX = 4;
 // Revision of the evaluation kernels' code and of the tuner's choice rule,
 // part of the autotuner's cache file name: a changed kernel is tuned again
 // instead of taking stale choices.
-constexpr int EE_KERNEL_REV = 6;
+constexpr int EE_KERNEL_REV = 7;
 // workgroups of a variant resident on the whole device (0 if the query fails)
 int eval_elim_grid(int cls, int wpe, int max_T);
 // private (spill) bytes per lane of a variant's kernel (-1 if the query fails)

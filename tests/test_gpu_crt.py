@@ -76,3 +76,19 @@ def test_mixed_sizes_in_one_batch():
     for _ in range(3):
         b.run()
         assert b.results() == want
+
+
+@pytest.mark.parametrize("nl", [1, 2, 3, 4, 5, 63, 64, 65, 128, 130])
+@pytest.mark.parametrize("dx", [2, 300])
+def test_input_reduction_limb_edges(nl, dx):
+    """Coefficients on the limb edges of both signs, reduced inside the evaluation (small degree) and, with
+    many coefficients, points and primes, by the launch before it."""
+    rnd = random.Random(1000 * nl + dx)
+    top = 32 * nl - 1
+    edges = [0, 1, -1, (1 << top) - 1, -(1 << top), 1 << (32 * (nl // 2)), -(1 << (32 * (nl // 2))),
+             (1 << (32 * (nl // 2))) - 1 if nl > 1 else 7]
+
+    def row():
+        return [rnd.choice(edges) if rnd.random() < 0.7 else rnd.getrandbits(top) for _ in range(dx)] + [-(1 << top)]
+    f, g = [row(), row()], [row(), row()]
+    assert snc.resultant_y(f, g) == _want(f, g)
