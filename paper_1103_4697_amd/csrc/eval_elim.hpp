@@ -125,88 +125,132 @@ __device__ __forceinline__ void reduce_limbs(uint32_t (&out)[NP], const uint32_t
 __device__ __forceinline__ uint32_t horner_grouped(const uint32_t* r, const RowDesc& d, int q, uint32_t X,
                                                    const PrimeC& c) {
   uint32_t acc = 0;
-  for (int i = d.len - 1; i >= 0; --i) acc = mhorner(acc, X, r[d.off + ROWGRP * i + q], c.p, c.pinv);
+  for (int i = d.len - 1; i >= 0; --i) acc = mhorner(acc, X, r[d.off + grp_pos(i, d.len) + q], c.p, c.pinv);
   return acc;
 }
 
-// The N+1 rows of one operand evaluated at X, four rows at a time from the
-// interleaved group layout: each 64-byte load holds four coefficients of
-// four independent rows (instruction-level parallelism for a lone
-// wavefront).  A chunk of four coefficients is one step of Horner's rule in
-// x^4 with the powers x, x^2, x^3, x^4 kept per lane:
-//   acc <- acc x^4 + v0 + v1 x + v2 x^2 + v3 x^3,
+// The N+1 rows of one operand at the lane's point, four rows at a time from
+// the interleaved group layout (instruction-level parallelism for a lone
+// wavefront).  Lanes 2i and 2i+1 hold the points x and -x, and
+//   f(+-x) = E(x^2) +- x O(x^2):
+// the even lane evaluates E and the odd one -x O, each half the powers, and
+// one exchange between the two lanes gives both values.  A chunk of four
+// powers of one parity is one step of Horner's rule in z^4, z = x^2, with z,
+// z^2, z^3, z^4 kept per lane:
+//   acc <- acc z^4 + v0 + v1 z + v2 z^2 + v3 z^3,
 // four 64-bit multiply-adds and one reduction, v0 added to its result.  With
 // canonical coefficients and powers and acc < 4p the sum stays below 7 p^2,
-// the reduction below 2.75p and the result below 4p.  Group lengths are padded at the
-// top with zeros, which keep an accumulator at zero.
+// the reduction below 2.75p and the result below 4p.  The last chunk takes
+// its powers times 1 or -x (five multiply-adds, below 8 p^2, reduced below
+// 3p); a length that is 4 mod 8 starts with two powers per parity.  Group
+// lengths are padded at the top with zeros, which keep an accumulator at
+// zero.
 struct alignas(16) HChunk {
   uint4 v[HCHUNK];
 };
-static_assert(HCHUNK == 4, "a chunk is four coefficients");
+static_assert(HCHUNK == 4, "a chunk is four powers");
 
 struct XPow {
-  uint32_t x1, x2, x3, x4;  // Montgomery forms of x, x^2, x^3, x^4, canonical
+  uint32_t z1, z2, z3, z4;      // Montgomery forms of z, z^2, z^3, z^4, canonical
+  uint32_t m0, m1, m2, m3, m4;  // 1, z, .., z^4 times 1 (even lane) or -x (odd lane)
+  uint32_t flip, add;           // value = own + (other ^ flip) + add: own + 2p - other or own + other
 };
 
 __device__ __forceinline__ uint32_t hstep4(uint32_t acc, uint32_t v0, uint32_t v1, uint32_t v2, uint32_t v3,
                                            const XPow& xp, const PrimeC& c) {
-  uint64_t t = (uint64_t)acc * xp.x4;
-  t += (uint64_t)v1 * xp.x1;
-  t += (uint64_t)v2 * xp.x2;
-  t += (uint64_t)v3 * xp.x3;
+  uint64_t t = (uint64_t)acc * xp.z4;
+  t += (uint64_t)v1 * xp.z1;
+  t += (uint64_t)v2 * xp.z2;
+  t += (uint64_t)v3 * xp.z3;
   // v0 is added after the reduction, REDC(t + v0 2^32) = REDC(t) + v0: the
   // addition also moves the result out of the 64-bit register pair
   const uint32_t m = (uint32_t)t * c.pinv;
   return (uint32_t)((t + (uint64_t)m * c.p) >> 32) + v0;
 }
 
-__device__ __forceinline__ void horner_chunk(uint32_t& a0, uint32_t& a1, uint32_t& a2, uint32_t& a3,
-                                             const HChunk& h, const XPow& xp, const PrimeC& c) {
-  a0 = hstep4(a0, h.v[0].x, h.v[1].x, h.v[2].x, h.v[3].x, xp, c);
-  a1 = hstep4(a1, h.v[0].y, h.v[1].y, h.v[2].y, h.v[3].y, xp, c);
-  a2 = hstep4(a2, h.v[0].z, h.v[1].z, h.v[2].z, h.v[3].z, xp, c);
-  a3 = hstep4(a3, h.v[0].w, h.v[1].w, h.v[2].w, h.v[3].w, xp, c);
+// the exchange: own half reduced from t to the row's value at the lane's point, below 4p
+__device__ __forceinline__ uint32_t hswap(uint64_t t, const XPow& xp, const PrimeC& c) {
+  uint32_t own = redc(t, c.p, c.pinv);
+  const uint32_t o2 = own - 2 * c.p;
+  own = o2 < own ? o2 : own;  // [0, 3p) -> [0, 2p)
+  const uint32_t other = (uint32_t)__builtin_amdgcn_mov_dpp((int)own, 0xb1 /* quad_perm 1,0,3,2 */, 0xf, 0xf, true);
+  return own + (other ^ xp.flip) + xp.add;
+}
+
+// the last chunk
+__device__ __forceinline__ uint32_t hlast(uint32_t acc, uint32_t v0, uint32_t v1, uint32_t v2, uint32_t v3,
+                                          const XPow& xp, const PrimeC& c) {
+  uint64_t t = (uint64_t)acc * xp.m4;
+  t += (uint64_t)v0 * xp.m0;
+  t += (uint64_t)v1 * xp.m1;
+  t += (uint64_t)v2 * xp.m2;
+  t += (uint64_t)v3 * xp.m3;
+  return hswap(t, xp, c);
+}
+
+// a row of at most four coefficients: two of the lane's parity
+__device__ __forceinline__ uint32_t hshort(uint32_t v0, uint32_t v1, const XPow& xp, const PrimeC& c) {
+  return hswap((uint64_t)v0 * xp.m0 + (uint64_t)v1 * xp.m1, xp, c);
+}
+
+// the top half chunk of a row: v0 + v1 z
+__device__ __forceinline__ uint32_t htop(uint32_t v0, uint32_t v1, const XPow& xp, const PrimeC& c) {
+  return redc((uint64_t)v1 * xp.z1, c.p, c.pinv) + v0;
+}
+
+template <int NV>
+__device__ __forceinline__ void eval_group(uint32_t (&a)[4], const uint32_t* g, int len, int odd, const XPow& X,
+                                           const PrimeC& c) {
+  const HChunk* q = reinterpret_cast<const HChunk*>(g) + odd;
+  const int nch = len / (2 * HCHUNK);
+  if (len & HCHUNK) {  // uniform
+    const uint4* h = reinterpret_cast<const uint4*>(g + 4 * (len & ~7)) + 2 * odd;
+    const uint4 u = h[0], v = h[1];
+    if (nch == 0) {
+      a[0] = hshort(u.x, v.x, X, c);
+      a[1] = hshort(u.y, v.y, X, c);
+      if constexpr (NV > 2) a[2] = hshort(u.z, v.z, X, c);
+      if constexpr (NV > 2) a[3] = hshort(u.w, v.w, X, c);
+      return;
+    }
+    a[0] = htop(u.x, v.x, X, c);
+    a[1] = htop(u.y, v.y, X, c);
+    if constexpr (NV > 2) a[2] = htop(u.z, v.z, X, c);
+    if constexpr (NV > 2) a[3] = htop(u.w, v.w, X, c);
+  }
+  for (int ch = nch - 1; ch >= 1; --ch) {
+    const HChunk& h = q[2 * ch];
+    a[0] = hstep4(a[0], h.v[0].x, h.v[1].x, h.v[2].x, h.v[3].x, X, c);
+    a[1] = hstep4(a[1], h.v[0].y, h.v[1].y, h.v[2].y, h.v[3].y, X, c);
+    if constexpr (NV > 2) a[2] = hstep4(a[2], h.v[0].z, h.v[1].z, h.v[2].z, h.v[3].z, X, c);
+    if constexpr (NV > 2) a[3] = hstep4(a[3], h.v[0].w, h.v[1].w, h.v[2].w, h.v[3].w, X, c);
+  }
+  const HChunk& h = q[0];
+  a[0] = hlast(a[0], h.v[0].x, h.v[1].x, h.v[2].x, h.v[3].x, X, c);
+  a[1] = hlast(a[1], h.v[0].y, h.v[1].y, h.v[2].y, h.v[3].y, X, c);
+  if constexpr (NV > 2) a[2] = hlast(a[2], h.v[0].z, h.v[1].z, h.v[2].z, h.v[3].z, X, c);
+  if constexpr (NV > 2) a[3] = hlast(a[3], h.v[0].w, h.v[1].w, h.v[2].w, h.v[3].w, X, c);
 }
 
 // deg: the operand's y-degree.  The group that holds row 0 (index deg) is
-// partial unless deg + 1 is a multiple of four; its missing rows would run
-// the full length on zeros (that group has the longest rows of a dense
-// polynomial), so it takes a loop over its rows that exist only.
-template <int N>
-__device__ __forceinline__ void eval_rows(uint32_t (&A)[N + 1], const uint32_t* r, const RowDesc* rd, int deg,
+// partial unless deg + 1 is a multiple of four; with one or two rows it
+// takes half a group (that group has the longest rows of a dense polynomial).
+// A recursion: the register arrays need every index constant, and the groups
+// together are past what a loop is unrolled to.
+template <int N, int T0 = 0>
+__device__ __forceinline__ void eval_rows(uint32_t (&A)[N + 1], const uint32_t* r, const RowDesc* rd, int deg, int odd,
                                           const XPow& X, const PrimeC& c) {
-#pragma unroll
-  for (int t0 = 0; t0 <= N; t0 += ROWGRP) {
-    const RowDesc d = rd[t0 / ROWGRP];
-    const HChunk* q = reinterpret_cast<const HChunk*>(r + d.off);
-    uint32_t a0 = 0, a1 = 0, a2 = 0, a3 = 0;
-    const int nv = deg - t0 + 1;  // rows of the group that exist (uniform)
-    if (nv >= ROWGRP) {
-      for (int ch = d.len / HCHUNK - 1; ch >= 0; --ch) horner_chunk(a0, a1, a2, a3, q[ch], X, c);
-    } else if (nv == 1) {
-      for (int ch = d.len / HCHUNK - 1; ch >= 0; --ch) {
-        const HChunk& h = q[ch];
-        a0 = hstep4(a0, h.v[0].x, h.v[1].x, h.v[2].x, h.v[3].x, X, c);
-      }
-    } else if (nv == 2) {
-      for (int ch = d.len / HCHUNK - 1; ch >= 0; --ch) {
-        const HChunk& h = q[ch];
-        a0 = hstep4(a0, h.v[0].x, h.v[1].x, h.v[2].x, h.v[3].x, X, c);
-        a1 = hstep4(a1, h.v[0].y, h.v[1].y, h.v[2].y, h.v[3].y, X, c);
-      }
-    } else if (nv == 3) {
-      for (int ch = d.len / HCHUNK - 1; ch >= 0; --ch) {
-        const HChunk& h = q[ch];
-        a0 = hstep4(a0, h.v[0].x, h.v[1].x, h.v[2].x, h.v[3].x, X, c);
-        a1 = hstep4(a1, h.v[0].y, h.v[1].y, h.v[2].y, h.v[3].y, X, c);
-        a2 = hstep4(a2, h.v[0].z, h.v[1].z, h.v[2].z, h.v[3].z, X, c);
-      }
-    }
-    A[t0] = a0;
-    if (t0 + 1 <= N) A[t0 + 1] = a1;
-    if (t0 + 2 <= N) A[t0 + 2] = a2;
-    if (t0 + 3 <= N) A[t0 + 3] = a3;
+  const RowDesc d = rd[T0 / ROWGRP];
+  uint32_t a[4] = {0, 0, 0, 0};
+  if (d.len > 0) {  // uniform
+    if (deg - T0 >= 2) eval_group<4>(a, r + d.off, d.len, odd, X, c);
+    else eval_group<2>(a, r + d.off, d.len, odd, X, c);
   }
+  A[T0] = a[0];
+  if constexpr (T0 + 1 <= N) A[T0 + 1] = a[1];
+  if constexpr (T0 + 2 <= N) A[T0 + 2] = a[2];
+  if constexpr (T0 + 3 <= N) A[T0 + 3] = a[3];
+  if constexpr (T0 + ROWGRP <= N) eval_rows<N, T0 + ROWGRP>(A, r, rd, deg, odd, X, c);
 }
 
 // Lane state of the elimination: every remainder so far of its expected
@@ -393,12 +437,14 @@ __device__ __forceinline__ void eval_elim_block(int64_t b, const PrimeC* primes,
   const int jj = find_job(prefix, njobs, b);
   const int jid = job_list[jj];
   const ResJob J = jobs[jid];
-  const int npb = (J.D + EE_BLOCK) / EE_BLOCK;
+  const int npts = npts_of(J.D);
+  const int npb = (npts + EE_BLOCK - 1) / EE_BLOCK;
   const int64_t lb = b - prefix[jj];
   const int pi = (int)(lb / npb);
   const int j0 = (int)(lb % npb) * EE_BLOCK + threadIdx.x;
-  const bool live = j0 <= J.D;  // lanes past the last point still help stage the rows
-  const int j = live ? j0 : J.D;
+  const int odd = threadIdx.x & 1;
+  const bool live = j0 < npts;  // lanes past the last point still help stage the rows
+  const int j = live ? j0 : npts - 2 + odd;  // a pair of lanes stays a pair of points
   const PrimeC c = primes[pi];
   const uint32_t* r = ws + J.res_off + (int64_t)pi * J.T;
   if constexpr (LDSROWS) {
@@ -455,20 +501,28 @@ __device__ __forceinline__ void eval_elim_block(int64_t b, const PrimeC* primes,
     r = er;
   }
   XPow X;
-  X.x1 = point_mont(points, pi, j, c);
-  X.x2 = mmulc(X.x1, X.x1, c.p, c.pinv);
-  X.x3 = mmulc(X.x2, X.x1, c.p, c.pinv);
-  X.x4 = mmulc(X.x2, X.x2, c.p, c.pinv);
+  const uint32_t xj = point_mont(points, pi, j, c);
+  X.z1 = mmulc(xj, xj, c.p, c.pinv);
+  X.z2 = mmulc(X.z1, X.z1, c.p, c.pinv);
+  X.z3 = mmulc(X.z2, X.z1, c.p, c.pinv);
+  X.z4 = mmulc(X.z2, X.z2, c.p, c.pinv);
+  X.m0 = odd ? xj : c.r1;
+  X.m1 = mmulc(X.z1, X.m0, c.p, c.pinv);
+  X.m2 = mmulc(X.z2, X.m0, c.p, c.pinv);
+  X.m3 = mmulc(X.z3, X.m0, c.p, c.pinv);
+  X.m4 = mmulc(X.z4, X.m0, c.p, c.pinv);
+  X.flip = odd ? 0u : ~0u;
+  X.add = odd ? 0u : 2 * c.p + 1;
   // rows are padded to N+1 per operand (length 0 above the degree): no branches
   const RowDesc* ra = rows + J.rows_off;
   const RowDesc* rb = ra + J.rstride;  // J.rstride == N + 1 on this path
   uint32_t A[N + 1], B[N + 1];
-  eval_rows<N>(A, r, ra, J.m, X, c);
-  eval_rows<N>(B, r, rb, J.n, X, c);
+  eval_rows<N>(A, r, ra, J.m, odd, X, c);
+  eval_rows<N>(B, r, rb, J.n, odd, X, c);
 
   // formal degrees attained at this point, else the general elimination
-  A[0] = canon(A[0], c.p);
-  B[0] = canon(B[0], c.p);
+  A[0] = canon4(A[0], c.p);
+  B[0] = canon4(B[0], c.p);
   int st = A[0] != 0 ? EL_NORMAL : EL_ABN;
   if (J.n >= 1 && B[0] == 0) st = EL_ABN;
   uint32_t den = c.r1;
@@ -505,7 +559,7 @@ __device__ __forceinline__ void eval_elim_block(int64_t b, const PrimeC* primes,
   // a zero remainder with a divisor of positive degree: res = 0; an
   // abnormal instance leaves a marker (never a residue), which the
   // interpolation replaces by the general elimination's value
-  ws[J.pts_off + (int64_t)pi * (J.D + 1) + j] = st == EL_NORMAL ? res : st == EL_ZERO ? 0u : ABN_MARK;
+  ws[J.pts_off + (int64_t)pi * npts + j] = st == EL_NORMAL ? res : st == EL_ZERO ? 0u : ABN_MARK;
 }
 
 // Work distribution of a launch.  chunk == 0: one workgroup per block,

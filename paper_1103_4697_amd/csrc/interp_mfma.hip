@@ -1,22 +1,26 @@
 // Interpolation mod p on the matrix cores (Section 4, "Symbolic Speedups":
 // the images over Z_p at points are combined into coefficients over Z_p).
 //
-// Points.  x_j = q^j mod p, j = 0..D, with q of order above MAX_D mod p.  With
-// phi_m = (q - 1)(q^2 - 1) ... (q^m - 1) the Newton polynomials satisfy
-//   N_k(q^i) = q^C(k,2) phi_i / phi_{i-k},
-//   N_k(x)   = sum_i (-1)^{k-i} q^C(k-i,2) phi_k / (phi_i phi_{k-i}) x^i
+// Points.  +-q^i mod p, i = 0..D/2, with Q = q^2 of order above MAX_D / 2 mod
+// p.  P(x) = E(x^2) + x O(x^2), so the pair of values at +-q^i gives E and O
+// at Q^i: two interpolations of half the size at powers of Q.  With
+// phi_m = (Q - 1)(Q^2 - 1) ... (Q^m - 1) the Newton polynomials at those points
+// satisfy
+//   N_k(Q^i) = Q^C(k,2) phi_i / phi_{i-k},
+//   N_k(z)   = sum_i (-1)^{k-i} Q^C(k-i,2) phi_k / (phi_i phi_{k-i}) z^i
 // (the q-binomial theorem), and 1 / sum_m z^m / phi_m = sum_m t_m z^m,
-// t_m = (-1)^m q^C(m,2) / phi_m.  So values v_i become coefficients c_i by two
+// t_m = (-1)^m Q^C(m,2) / phi_m.  So values v_i become coefficients c_i by two
 // products with the same sequence t, lower and upper triangular Toeplitz, and
 // scalings by tables:
 //   u_i = v_i / phi_i,   b_k = sum_{i <= k} t_{k-i} u_i,
-//   e_k = b_k psi_k,     psi_k = phi_k q^-C(k,2),
-//   c_i = (1 / phi_i) sum_{k >= i} t_{k-i} e_k.
-// (At points 0..D the expansion of the Newton form needs falling factorials
-// that differ from block to block.)
+//   e_k = b_k psi_k,     psi_k = phi_k Q^-C(k,2) / 2,
+//   c_i = (1 / phi_i) sum_{k >= i} t_{k-i} e_k,
+// v_i the sum of the pair's values for E and their difference over q^i for O
+// (psi holds the factor 1/2 of both).  At points 0..D the expansion of the
+// Newton form needs falling factorials that differ from block to block.
 //
 // Mapping.  A workgroup takes one prime and a group of jobs.  Outputs go in
-// blocks of 64; a row of the matrix product is one (job, block), and step d
+// blocks of 64; a row of the matrix product is one (job, parity, block), and step d
 // multiplies the rows' input blocks at distance d by the 64 x 64 Toeplitz
 // block T_d, the same for every row.  T_d is never stored: column n of a tile
 // is output 4 n + kappa (kappa = 0..3), so a lane's 16 contraction entries
@@ -43,73 +47,84 @@
 
 namespace snc {
 
-constexpr int IM_TROW = (MAX_D + 64) / 64 * 64 + 64;  // bytes of a plane of t per prime (zeros above MAX_D)
+constexpr int IM_N = MAX_D / 2 + 1;                    // coefficients of one parity, at most
+constexpr int IM_DP = (IM_N + 63) / 64 * 64;           // whole blocks
+constexpr int IM_TROW = IM_DP + 64;                    // bytes of a plane of t per prime (zeros past IM_N)
 
-__device__ uint32_t g_iphi[(size_t)KMAX * (MAX_D + 1)];  // Montgomery form of 1 / phi_m
-__device__ uint32_t g_psi[(size_t)KMAX * (MAX_D + 1)];   // Montgomery form of psi_m
+__device__ uint32_t g_iphi[(size_t)KMAX * IM_N];   // Montgomery form of 1 / phi_m
+__device__ uint32_t g_iphiq[(size_t)KMAX * IM_N];  // Montgomery form of 1 / (phi_m q^m)
+__device__ uint32_t g_psi[(size_t)KMAX * IM_N];    // Montgomery form of psi_m
 __device__ __align__(16) int8_t g_tq[(size_t)KMAX * 4 * IM_TROW];  // bytes of t_m (Montgomery form), four planes
-// points: q^l for l < 64, then q^(64 b) at 64 + b (Montgomery form)
 __device__ uint32_t g_points[(size_t)KMAX * POINT_ROW];
 
 // one prime per thread
 __global__ __launch_bounds__(64) void k_points_init(const PrimeC* primes) {
   const int pi = blockIdx.x * 64 + threadIdx.x;
   const PrimeC c = primes[pi];
-  uint32_t* ip = g_iphi + (size_t)pi * (MAX_D + 1);
-  uint32_t* ps = g_psi + (size_t)pi * (MAX_D + 1);
+  uint32_t* ip = g_iphi + (size_t)pi * IM_N;
+  uint32_t* iq = g_iphiq + (size_t)pi * IM_N;
+  uint32_t* ps = g_psi + (size_t)pi * IM_N;
   int8_t* tq = g_tq + (size_t)pi * 4 * IM_TROW;
   uint32_t* pt = g_points + (size_t)pi * POINT_ROW;
-  // the least q >= 2 of order above MAX_D; phi_m in psi's row
-  uint32_t q = 0, phi = c.r1, qm = c.r1;
+  // the least q >= 2 with q^2 of order above IM_N - 1; phi_m in psi's row
+  uint32_t q = 0, phi = c.r1, Qm = c.r1;
   for (uint32_t g = 2; q == 0; ++g) {
-    const uint32_t gm = to_mont(g, c);
+    const uint32_t gm = to_mont(g, c), Q = mmulc(gm, gm, c.p, c.pinv);
     phi = c.r1;
-    qm = c.r1;
+    Qm = c.r1;
     ps[0] = phi;
     bool ok = true;
-    for (int m = 1; m <= MAX_D && ok; ++m) {
-      qm = mmulc(qm, gm, c.p, c.pinv);
-      ok = qm != c.r1;
-      phi = mmulc(phi, msub(qm, c.r1, c.p), c.p, c.pinv);
+    for (int m = 1; m < IM_N && ok; ++m) {
+      Qm = mmulc(Qm, Q, c.p, c.pinv);
+      ok = Qm != c.r1;
+      phi = mmulc(phi, msub(Qm, c.r1, c.p), c.p, c.pinv);
       ps[m] = phi;
     }
     if (ok) q = gm;
   }
-  const uint32_t iq = minv(q, c);
-  uint32_t inv = minv(phi, c);  // 1 / phi_m, and qm = q^m, from the top down
-  for (int m = MAX_D; m >= 0; --m) {
+  const uint32_t Q = mmulc(q, q, c.p, c.pinv), qi = minv(q, c), Qi = mmulc(qi, qi, c.p, c.pinv);
+  uint32_t inv = minv(phi, c);  // 1 / phi_m, and Qm = Q^m, from the top down
+  for (int m = IM_N - 1; m >= 0; --m) {
     ip[m] = inv;
-    inv = mmulc(inv, msub(qm, c.r1, c.p), c.p, c.pinv);
-    qm = mmulc(qm, iq, c.p, c.pinv);
+    inv = mmulc(inv, msub(Qm, c.r1, c.p), c.p, c.pinv);
+    Qm = mmulc(Qm, Qi, c.p, c.pinv);
   }
-  uint32_t qp = c.r1, iqp = c.r1, qc = c.r1, iqc = c.r1;  // q^m, q^-m, q^C(m,2), q^-C(m,2)
-  for (int m = 0; m <= MAX_D; ++m) {
-    uint32_t t = mmulc(qc, ip[m], c.p, c.pinv);
+  uint32_t qp = c.r1, qip = c.r1;    // q^m, q^-m
+  uint32_t Qp = c.r1, Qip = c.r1;    // Q^m, Q^-m
+  uint32_t Qc = c.r1;                // Q^C(m,2)
+  uint32_t hc = to_mont((c.p + 1) / 2, c);  // Q^-C(m,2) / 2
+  for (int m = 0; m < IM_N; ++m) {
+    uint32_t t = mmulc(Qc, ip[m], c.p, c.pinv);
     if (m & 1) t = mneg(t, c.p);
     const uint32_t w = balance4(t);
     for (int b = 0; b < 4; ++b) tq[(size_t)b * IM_TROW + m] = (int8_t)(w >> (8 * b));
-    ps[m] = mmulc(ps[m], iqc, c.p, c.pinv);
-    if (m < 64) pt[m] = qp;
-    if (m % 64 == 0) pt[64 + m / 64] = qp;
-    qc = mmulc(qc, qp, c.p, c.pinv);
-    iqc = mmulc(iqc, iqp, c.p, c.pinv);
+    ps[m] = mmulc(ps[m], hc, c.p, c.pinv);
+    iq[m] = mmulc(ip[m], qip, c.p, c.pinv);
+    if (m < 32) pt[m] = qp;
+    if (m % 32 == 0) pt[32 + m / 32] = qp;
+    Qc = mmulc(Qc, Qp, c.p, c.pinv);
+    hc = mmulc(hc, Qip, c.p, c.pinv);
+    Qp = mmulc(Qp, Q, c.p, c.pinv);
+    Qip = mmulc(Qip, Qi, c.p, c.pinv);
     qp = mmulc(qp, q, c.p, c.pinv);
-    iqp = mmulc(iqp, iq, c.p, c.pinv);
+    qip = mmulc(qip, qi, c.p, c.pinv);
   }
 }
 
 constexpr int IM_THREADS = 256;
 constexpr int IM_WAVES = IM_THREADS / 64;
 constexpr int IM_MAXROWS = 192;
+constexpr int IM_LOADS = 4;   // pairs of values a thread has in flight
 constexpr int IM_MARKS = 32;  // abnormal instances of a workgroup that take a wavefront each
-static_assert((MAX_D + 64) / 64 <= IM_MAXROWS, "the rows of one job of the largest degree bound");
+static_assert(2 * (IM_DP / 64) <= IM_MAXROWS, "the rows of one job of the largest degree bound");
+constexpr int IM_SEQ = 2 * IM_JOBS;  // sequences of a group: the even and the odd coefficients of each job
 
 // LDS of a group: the planes of t (reversed and ascending, or one after the
-// other where both do not fit; zeros below index 0), then for each job the
-// planes of u and of e
+// other where both do not fit; zeros below index 0), then for each sequence
+// the planes of u and of e
 __host__ __device__ constexpr int im_tplane(int Dp) { return Dp + 144; }
 __host__ __device__ constexpr bool im_both(int Dp) { return Dp <= 4096; }
-static_assert(4 * im_tplane((MAX_D + 64) / 64 * 64) + 8 * ((MAX_D + 64) / 64 * 64) + 8 * 1024 <= 160 * 1024,
+static_assert(4 * im_tplane(IM_DP) + 16 * IM_DP + 8 * 1024 <= 160 * 1024,
               "the buffers of the largest degree bound fit the LDS of a CU");
 
 // bytes sh .. sh + 15 of five words
@@ -226,10 +241,10 @@ __device__ __forceinline__ void interp_unit(const InterpLds& S, int tile, int la
           E[q * 64 * ob] = (uint8_t)(w[0] >> (8 * q));
       }
     } else {
-      uint32_t* C = ws + S.val[oj];
+      uint32_t* C = ws + S.val[oj];  // coefficients of x^(2 k) or x^(2 k + 1)
 #pragma unroll
       for (int e = 0; e < NK; ++e)
-        if (k0 + e < n1) C[k0 + e] = from_mont(w[e], c);
+        if (k0 + e < n1) C[2 * (k0 + e)] = from_mont(w[e], c);
     }
   }
 }
@@ -259,9 +274,10 @@ __global__ __launch_bounds__(IM_THREADS) void k_interp_mfma(const PrimeC* primes
                                                             const int64_t* gprefix, int ngroups, const RowDesc* rows,
                                                             uint32_t* ws) {
   extern __shared__ uint4 im_sm[];
-  __shared__ int64_t sPts[IM_JOBS], sVal[IM_JOBS];
-  __shared__ int32_t sN1[IM_JOBS], sBlk[IM_JOBS], sU[IM_JOBS];
-  __shared__ int32_t sRow[IM_MAXROWS + 16];  // job << 16 | block distance K; -1 past the last row
+  __shared__ int64_t sPts[IM_JOBS], sVal[IM_SEQ];
+  __shared__ int32_t sN1[IM_SEQ], sBlk[IM_SEQ], sU[IM_SEQ];  // sequence 2 j + parity of job j
+  __shared__ int32_t sRow[IM_MAXROWS + 16];  // sequence << 16 | block distance K; -1 past the last row
+  __shared__ int32_t sPair[IM_JOBS + 1];     // pairs of points (whole blocks) before each job
   __shared__ int32_t nmark, mark[IM_MARKS];
   __shared__ uint32_t gen[IM_WAVES][2 * (MAXY_FAST + 1)];
   uint8_t* sm = reinterpret_cast<uint8_t*>(im_sm);
@@ -271,39 +287,69 @@ __global__ __launch_bounds__(IM_THREADS) void k_interp_mfma(const PrimeC* primes
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const PrimeC c = primes[pi];
-  if (tid < nj) {
-    const ResJob& J = jobs[job_list[s0 + tid]];
+  const int ns = 2 * nj;
+  if (tid < ns) {
+    const ResJob& J = jobs[job_list[s0 + (tid >> 1)]];
     const bool on = J.k > pi;  // jobs of the group with fewer primes sit this one out
-    sN1[tid] = on ? J.D + 1 : 0;
-    sBlk[tid] = on ? (J.D + 64) / 64 : 0;
-    sPts[tid] = J.pts_off + (int64_t)pi * (J.D + 1);
-    sVal[tid] = J.val_off + (int64_t)pi * (J.D + 1);
+    const int odd = tid & 1;
+    const int n = !on ? 0 : odd ? (J.D + 1) / 2 : J.D / 2 + 1;
+    sN1[tid] = n;
+    sBlk[tid] = (n + 63) / 64;
+    sVal[tid] = J.val_off + (int64_t)pi * (J.D + 1) + odd;
+    if (!odd) sPts[tid >> 1] = J.pts_off + (int64_t)pi * npts_of(J.D);
   }
   for (int r = tid; r < IM_MAXROWS + 16; r += IM_THREADS) sRow[r] = -1;
   if (tid == 0) nmark = 0;
   __syncthreads();
   int nrows = 0, mxb = 0;
-  for (int j = 0; j < nj; ++j) { nrows += sBlk[j]; mxb = max(mxb, sBlk[j]); }
+  for (int j = 0; j < ns; ++j) { nrows += sBlk[j]; mxb = max(mxb, sBlk[j]); }
   const int Dp = 64 * mxb, TP = im_tplane(Dp);
   const bool both = im_both(Dp);  // room for t in both orders
   const int zoff = (both ? 8 : 4) * TP, ubase = zoff + 16;
   // rows by K (the number of input blocks before the last one that an output
   // block reads) from the top, so that a tile's rows need about the same steps
-  for (int x = tid; x < nj * mxb; x += IM_THREADS) {
+  for (int x = tid; x < ns * mxb; x += IM_THREADS) {
     const int j = x / mxb, K = x % mxb;
     if (K >= sBlk[j]) continue;
     int pos = 0;
-    for (int i = 0; i < nj; ++i) pos += max(0, sBlk[i] - (K + 1)) + (i < j && sBlk[i] > K ? 1 : 0);
+    for (int i = 0; i < ns; ++i) pos += max(0, sBlk[i] - (K + 1)) + (i < j && sBlk[i] > K ? 1 : 0);
     sRow[pos] = j << 16 | K;
   }
-  if (tid < nj) {
+  if (tid < ns) {
     int off = ubase;
     for (int i = 0; i < tid; ++i) off += 512 * sBlk[i];
     sU[tid] = off;
   }
   if (tid < 4) reinterpret_cast<uint32_t*>(sm + zoff)[tid] = 0u;
-  const uint32_t* ip = g_iphi + (size_t)pi * (MAX_D + 1);
-  const uint32_t* ps = g_psi + (size_t)pi * (MAX_D + 1);
+  if (tid <= nj) {
+    int off = 0;
+    for (int i = 0; i < tid; ++i) off += 64 * sBlk[2 * i];
+    sPair[tid] = off;
+  }
+  __syncthreads();
+  // The pairs of values of all jobs, IM_LOADS at a time per thread; the first
+  // are requested before t is staged.
+  uint2 vv[IM_LOADS];
+  int vj[IM_LOADS], vi[IM_LOADS];
+  auto load_pairs = [&](int x0) {
+    int j = 0;
+#pragma unroll
+    for (int u = 0; u < IM_LOADS; ++u) {
+      const int x = x0 + u * IM_THREADS;
+      vj[u] = -1;
+      if (x < sPair[nj]) {
+        while (x >= sPair[j + 1]) ++j;
+        vj[u] = j;
+        vi[u] = x - sPair[j];
+        vv[u] = make_uint2(0u, 0u);
+        if (vi[u] < sN1[2 * j]) vv[u] = *reinterpret_cast<const uint2*>(ws + sPts[j] + 2 * vi[u]);
+      }
+    }
+  };
+  load_pairs(tid);
+  const uint32_t* ip = g_iphi + (size_t)pi * IM_N;
+  const uint32_t* iq = g_iphiq + (size_t)pi * IM_N;
+  const uint32_t* ps = g_psi + (size_t)pi * IM_N;
   const int8_t* tq = g_tq + (size_t)pi * 4 * IM_TROW;
   // t reversed: the word at byte y holds t at Dp + 67 - y and the three below
   for (int y = 4 * tid; y < TP; y += 4 * IM_THREADS) {
@@ -328,25 +374,40 @@ __global__ __launch_bounds__(IM_THREADS) void k_interp_mfma(const PrimeC* primes
   };
   if (both) load_ascending(4 * TP);
   __syncthreads();
-  // u = v / phi.  Instances the evaluation marked abnormal are computed here:
-  // a wavefront each while there are few (a lane alone takes ten times as
-  // long), else a lane each (a pair whose remainders skip degrees at every
-  // point marks all of them).
-  auto put_u = [&](int j, int i, uint32_t v) {
-    const uint32_t w = i < sN1[j] ? balance4(mmulc(canon(v, c.p), ip[i], c.p, c.pinv)) : 0u;
+  // u of both parities from the pairs of values.  Instances the evaluation
+  // marked abnormal are computed here: a wavefront each while there are few (a
+  // lane alone takes up to ten times as long), else a lane each (a pair whose
+  // remainders skip degrees at every point marks all of them).
+  auto put_u = [&](int j, int i, uint32_t v0, uint32_t v1) {
+    v0 = canon(v0, c.p);
+    v1 = canon(v1, c.p);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) sm[sU[j] + q * 64 * sBlk[j] + i] = (uint8_t)(w >> (8 * q));
-  };
-  auto each_point = [&](auto&& f) {
-    for (int j = 0; j < nj; ++j)
-      for (int i = tid; i < 64 * sBlk[j]; i += IM_THREADS) f(j, i, i < sN1[j] ? ws[sPts[j] + i] : 0u);
-  };
-  each_point([&](int j, int i, uint32_t v) {
-    if (__builtin_expect(v == ABN_MARK, 0)) {
-      const int x = atomicAdd(&nmark, 1);
-      if (x < IM_MARKS) mark[x] = j << 16 | i;
+    for (int odd = 0; odd < 2; ++odd) {
+      const int s = 2 * j + odd;
+      if (i >= 64 * sBlk[s]) continue;
+      const uint32_t v = odd ? v0 + c.p - v1 : v0 + v1;  // < 2p
+      const uint32_t w = i < sN1[s] ? balance4(mmulc(v, (odd ? iq : ip)[i], c.p, c.pinv)) : 0u;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) sm[sU[s] + q * 64 * sBlk[s] + i] = (uint8_t)(w >> (8 * q));
     }
-    put_u(j, i, v);
+  };
+  auto each_pair = [&](auto&& f) {
+    for (int x0 = tid; x0 < sPair[nj]; x0 += IM_LOADS * IM_THREADS) {
+      if (x0 != tid) load_pairs(x0);
+#pragma unroll
+      for (int u = 0; u < IM_LOADS; ++u)
+        if (vj[u] >= 0) f(vj[u], vi[u], vv[u].x, vv[u].y);
+    }
+  };
+  each_pair([&](int j, int i, uint32_t v0, uint32_t v1) {
+    if (__builtin_expect(v0 == ABN_MARK || v1 == ABN_MARK, 0)) {
+      for (int e = 0; e < 2; ++e)
+        if ((e ? v1 : v0) == ABN_MARK) {
+          const int x = atomicAdd(&nmark, 1);
+          if (x < IM_MARKS) mark[x] = j << 16 | (2 * i + e);
+        }
+    }
+    put_u(j, i, v0, v1);
   });
   __syncthreads();
   if (__builtin_expect(nmark != 0, 0)) {
@@ -357,12 +418,21 @@ __global__ __launch_bounds__(IM_THREADS) void k_interp_mfma(const PrimeC* primes
         const int j = mark[x] >> 16, i = mark[x] & 0xffff;
         const uint32_t v = general_instance_wave(jobs + job_list[s0 + j], primes, rows, ws, g_points, pi, i,
                                                  gen[wave], gen[wave] + MAXY_FAST + 1, lane);
-        if (lane == 0) put_u(j, i, v);
+        if (lane == 0) ws[sPts[j] + i] = v;
+      }
+      __syncthreads();
+      if (tid < nmark) {
+        const int j = mark[tid] >> 16, i = (mark[tid] & 0xffff) >> 1;
+        put_u(j, i, ws[sPts[j] + 2 * i], ws[sPts[j] + 2 * i + 1]);
       }
     } else {
-      each_point([&](int j, int i, uint32_t v) {
-        if (v == ABN_MARK)
-          put_u(j, i, general_instance<MAXY_FAST>(jobs + job_list[s0 + j], primes, rows, ws, g_points, pi, i));
+      load_pairs(tid);
+      each_pair([&](int j, int i, uint32_t v0, uint32_t v1) {
+        if (v0 != ABN_MARK && v1 != ABN_MARK) return;
+        const ResJob* J = jobs + job_list[s0 + j];
+        if (v0 == ABN_MARK) v0 = general_instance<MAXY_FAST>(J, primes, rows, ws, g_points, pi, 2 * i);
+        if (v1 == ABN_MARK) v1 = general_instance<MAXY_FAST>(J, primes, rows, ws, g_points, pi, 2 * i + 1);
+        put_u(j, i, v0, v1);
       });
     }
     __syncthreads();
@@ -380,8 +450,10 @@ __global__ __launch_bounds__(IM_THREADS) void k_interp_mfma(const PrimeC* primes
   interp_stage<2>(S, ntile, wave, lane, ip, ws, k56, c);
 }
 
+int interp_mfma_blocks(int D) { return (D / 2 + 64) / 64 + ((D + 1) / 2 + 63) / 64; }
+
 size_t interp_mfma_lds(int max_D, int blocks) {
-  const int Dp = (max_D + 64) / 64 * 64;
+  const int Dp = (max_D / 2 + 64) / 64 * 64;
   return (im_both(Dp) ? 8 : 4) * (size_t)im_tplane(Dp) + 16 + 512 * (size_t)blocks;
 }
 

@@ -127,8 +127,9 @@ __global__ void k_elim_general_all(const ResJob* jobs, const int32_t* job_list,
     const int jj = find_job(prefix, njobs, idx);
     const ResJob J = jobs[job_list[jj]];
     const int64_t li = idx - prefix[jj];
-    const int pi = (int)(li / (J.D + 1)), j = (int)(li % (J.D + 1));
-    ws[J.pts_off + (int64_t)pi * (J.D + 1) + j] =
+    const int np = npts_of(J.D);
+    const int pi = (int)(li / np), j = (int)(li % np);
+    ws[J.pts_off + (int64_t)pi * np + j] =
         general_instance<MAXY_GEN>(jobs + job_list[jj], g_primes, rows, ws, points, pi, j);
   }
 }

@@ -81,6 +81,14 @@ __device__ __forceinline__ uint32_t canon(uint32_t x, uint32_t p) {
   return (y < x) ? y : x;
 }
 
+// [0, 4p) -> [0, p)
+__device__ __forceinline__ uint32_t canon4(uint32_t x, uint32_t p) {
+  uint32_t y = x - 2 * p;
+  x = (y < x) ? y : x;
+  y = x - p;
+  return (y < x) ? y : x;
+}
+
 // [0, 2p) -> [0, p)
 __device__ __forceinline__ uint32_t canon2(uint32_t x, uint32_t p) {
   uint32_t y = x - p;
@@ -107,16 +115,18 @@ __device__ __forceinline__ uint32_t from_mont(uint32_t v, const PrimeC& c) {
 }
 
 // x^e (Montgomery, canonical result), e >= 0; e is usually uniform across
-// the wavefront so the loop is scalar control flow.
+// the wavefront so the loop is scalar control flow.  Factors below 2p give
+// products below 4p^2, reduced below p^2 2^-30 + p < 2p, so only the result is
+// made canonical.
 __device__ __forceinline__ uint32_t mpow(uint32_t x, uint32_t e, const PrimeC& c) {
   uint32_t r = c.r1;
   x = canon(x, c.p);
   while (e) {
-    if (e & 1u) r = mmulc(r, x, c.p, c.pinv);
+    if (e & 1u) r = mmul(r, x, c.p, c.pinv);
     e >>= 1;
-    if (e) x = mmulc(x, x, c.p, c.pinv);
+    if (e) x = mmul(x, x, c.p, c.pinv);
   }
-  return r;
+  return canon2(r, c.p);
 }
 
 // inverse by Fermat (x != 0 mod p)

@@ -133,12 +133,13 @@ void layout_batch(const std::vector<ResPlan>& plans, BatchLayout& lay) {
     const size_t n1 = (size_t)P.D + 1;
     J.res_off = (int64_t)w; w += align_words((size_t)P.k * P.T);
     J.val_off = (int64_t)w; w += align_words((size_t)P.k * n1);
-    J.pts_off = (int64_t)w; w += align_words((size_t)P.k * n1);
+    const size_t np = (size_t)npts_of(P.D);
+    J.pts_off = (int64_t)w; w += align_words((size_t)P.k * np);
     J.nq_off = (int64_t)w; w += align_words((size_t)P.k * ((n1 + 63) / 64) * 64);
     J.dig_off = (int64_t)w; w += align_words(n1 * P.k);
     J.acc_off = (int64_t)w;  // unused: the combine step keeps its accumulators in LDS
     lay.nb_red += reduce_blocks(P.k, P.T);
-    reduce_again += (double)P.k * ((n1 - 1) / EE_BLOCK) * ((P.T + 63) / 64) * (3 * P.nl + 8);
+    reduce_again += (double)P.k * ((np - 1) / EE_BLOCK) * ((P.T + 63) / 64) * (3 * P.nl + 8);
     const int cc = lay.crt_small_on ? crt_small_class(P.k) : -1;
     if (cc >= 0) {
       lay.nb_crts[cc] += (int64_t)((n1 + 63) / 64);
@@ -152,10 +153,10 @@ void layout_batch(const std::vector<ResPlan>& plans, BatchLayout& lay) {
     }
     lay.max_k = std::max(lay.max_k, P.k);
     if (P.cls >= 0) {
-      lay.nb_ee[P.cls] += (int64_t)P.k * ((n1 + EE_BLOCK - 1) / EE_BLOCK);
+      lay.nb_ee[P.cls] += (int64_t)P.k * ((np + EE_BLOCK - 1) / EE_BLOCK);
       lay.max_T_ee[P.cls] = std::max(lay.max_T_ee[P.cls], P.T);
     }
-    else lay.n_gen_inst += (int64_t)P.k * n1;
+    else lay.n_gen_inst += (int64_t)P.k * np;
     lay.max_D = std::max(lay.max_D, P.D);
   }
   // Interpolation groups: rows of several jobs fill the 16-row operand tiles,
@@ -175,7 +176,7 @@ void layout_batch(const std::vector<ResPlan>& plans, BatchLayout& lay) {
     int u = t, blocks = 0, kmax = 0;
     for (; u < NJ && u - t < per; ++u) {
       const ResJob& J = lay.jobs[lay.im_order[u]];
-      const int nb = blocks + (J.D + 64) / 64;
+      const int nb = blocks + interp_mfma_blocks(J.D);
       if (u > t && interp_mfma_lds(top, nb) > IM_LDS) break;
       blocks = nb;
       kmax = std::max(kmax, (int)J.k);
@@ -329,12 +330,12 @@ void launch_pipeline(const BatchLayout& lay, uint8_t* ws, hipStream_t s, StageTi
 }
 
 // Essential lane-operations of one evaluation block (64 instances): Horner
-// in x^4 (1.5 per coefficient), the fused remainder steps (5 per entry of
+// on the powers of one parity (0.75 per coefficient), the fused remainder steps (5 per entry of
 // each remainder), the first remainder's elementary steps and the final
 // powers and inversion.
 static int64_t eval_block_cost(const ResPlan& P) {
   const int64_t m = P.m, n = P.n;
-  return 3 * (int64_t)P.T / 2 + 5 * n * (n + 1) / 2 + 4 * n * std::max<int64_t>(m - n - 1, 0) + 300;
+  return 3 * (int64_t)P.T / 4 + 5 * n * (n + 1) / 2 + 4 * n * std::max<int64_t>(m - n - 1, 0) + 300;
 }
 
 // Fill the upload block: job descriptors, row descriptors, block prefixes,
@@ -397,7 +398,7 @@ void fill_header(const BatchLayout& lay, const std::vector<ResPlan>& plans, cons
         rd[g].off = off; rd[g].len = ml;
         for (int kx = 0; kx < ml; ++kx) {
           for (int q = 0; q < ROWGRP; ++q) {
-            uint32_t* dst = coef + cw + (size_t)(off + ROWGRP * kx + q);  // limb l at dst[l T]
+            uint32_t* dst = coef + cw + (size_t)(off + grp_pos(kx, ml) + q);  // limb l at dst[l T]
             const int row = deg - t0 - q;
             if (t0 + q > deg || kx > O.rowdeg[row]) {
               for (int l = 0; l < P.nl; ++l) dst[(size_t)l * P.T] = 0u;
@@ -436,7 +437,7 @@ void fill_header(const BatchLayout& lay, const std::vector<ResPlan>& plans, cons
       by_cost[P.cls].push_back({eval_block_cost(P), j});
     } else {
       lg[ng] = j;
-      pg[ng + 1] = pg[ng] + (int64_t)P.k * n1;
+      pg[ng + 1] = pg[ng] + (int64_t)P.k * npts_of(P.D);
       ng++;
     }
   }
@@ -460,7 +461,7 @@ void fill_header(const BatchLayout& lay, const std::vector<ResPlan>& plans, cons
     for (const auto& e : by_cost[c]) {
       const ResJob& J = lay.jobs[e.second];
       le[c][ne[c]] = e.second;
-      pe[c][ne[c] + 1] = pe[c][ne[c]] + (int64_t)J.k * ((J.D + 1 + EE_BLOCK - 1) / EE_BLOCK);
+      pe[c][ne[c] + 1] = pe[c][ne[c]] + (int64_t)J.k * ((npts_of(J.D) + EE_BLOCK - 1) / EE_BLOCK);
       ne[c]++;
     }
   }

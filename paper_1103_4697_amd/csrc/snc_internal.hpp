@@ -25,7 +25,7 @@ constexpr int GCD_THREADS = 256;
 struct ResJob {
   int32_t m, n;        // y-degrees of A and B over Z[x], m >= 1, m >= n >= 0
   int32_t sign;        // 1: operands were swapped and m*n is odd (result negated)
-  int32_t D;           // evaluation points x_0..x_D
+  int32_t D;           // degree bound
   int32_t k;           // primes 0..k-1 of the table
   int32_t T;           // residues per prime (coefficients of f and g)
   int32_t L;           // output limbs per coefficient
@@ -35,7 +35,7 @@ struct ResJob {
   int64_t coef_off;    // input limbs, limb-major [nl][T] (uint32 index)
   int64_t res_off;     // residues [k][T] (uint32 index)
   int64_t val_off;     // coefficients mod p: [k][D+1]
-  int64_t pts_off;     // values at the points: [k][D+1]
+  int64_t pts_off;     // values at the points: [k][npts_of(D)]
   int64_t nq_off;      // Newton blocks Q_j of the block-parallel interpolation: [k][64 ceil((D+1)/64)]
   int64_t dig_off;     // mixed-radix digits [D+1][k]
   int64_t acc_off;     // CRT accumulator [D+1][LX] with LX = lx_of(k)
@@ -43,9 +43,11 @@ struct ResJob {
 };
 
 // Rows of an operand are stored top-down (row of y^deg first) in groups of
-// four: group g holds rows 4g..4g+3 interleaved coefficient-major, zero-padded
-// to the longest of the four: residue off + 4c + q = coefficient of x^c of row
-// 4g + q.
+// four: group g holds rows 4g..4g+3, zero-padded to the longest of the four.
+// The evaluation takes even and odd powers of x apart (points come in pairs
+// +-x), so a group is a sequence of 64-byte chunks, four powers of one parity
+// by four rows: the coefficient of x^c of row 4g + q is residue
+// off + grp_pos(c, len) + q.
 struct RowDesc {
   int32_t off;  // first residue of the group within a prime's block of T
   int32_t len;  // coefficients per row of the group (0 for an all-zero group)
@@ -61,8 +63,17 @@ __device__ __forceinline__ int64_t xcd_block(int64_t b, int64_t nb) {
 }
 
 constexpr int ROWGRP = 4;
-constexpr int HCHUNK = 4;   // Horner steps per 64-byte scalar load; group lengths are padded to a multiple
+constexpr int HCHUNK = 4;   // powers of one parity per chunk; group lengths are padded to a multiple
 __host__ __device__ inline int padded_group_len(int ml) { return (ml + HCHUNK - 1) / HCHUNK * HCHUNK; }
+// position of x^c in a group of length len: pairs of chunks (even, odd powers)
+// of eight, and for the top four of a length that is 4 mod 8 one chunk with
+// two even powers and two odd ones
+__host__ __device__ inline int grp_pos(int c, int len) {
+  if (c >= (len & ~7)) return 4 * (len & ~7) + 8 * (c & 1) + 4 * ((c >> 1) & 1);
+  return 16 * (2 * (c >> 3) + (c & 1)) + 4 * ((c >> 1) & 3);
+}
+// evaluation points: pairs +-q^i, i = 0..D/2 (one point more than needed when D is even)
+__host__ __device__ inline int npts_of(int D) { return 2 * (D / 2 + 1); }
 
 // Constant tables of a Chinese-remainder reconstruction over primes
 // q_0..q_{k-1}: garner[i] = Montgomery form of (Q_i mod q_i)^-1 and
@@ -121,14 +132,16 @@ inline bool interp_blk_fits(int max_D, int max_k) { return max_D + 1 <= 64 * IFF
 void launch_interp_blk(const ResJob* jobs_d, const int64_t* blk_prefix_d, int njobs, int64_t nblocks, uint32_t* ws,
                        hipStream_t s);
 void launch_zero_u32(uint32_t* p, int64_t n, hipStream_t s);
-// Evaluation points of the resultants: x_j = q^j mod p, q = q(p) of order
-// above MAX_D.  Row p of the table: q^l for l < 64, then q^(64 b) at 64 + b.
+// Evaluation points of the resultants: x_2i = q^i, x_2i+1 = -q^i mod p, q =
+// q(p) with q^2 of order above MAX_D / 2.  Row p of the table: q^l for l < 32,
+// then q^(32 b) at 32 + b.
 constexpr int POINT_ROW = 256;
-static_assert(64 + MAX_D / 64 < POINT_ROW, "a row holds the block powers of the largest degree bound");
+static_assert(32 + MAX_D / 64 < POINT_ROW, "a row holds the block powers of the largest degree bound");
 __device__ __forceinline__ uint32_t point_mont(const uint32_t* points, int pi, int j, const PrimeC& c) {
   const uint32_t* r = points + (int64_t)pi * POINT_ROW;
-  const uint32_t t = mmul(r[64 + (j >> 6)], r[j & 63], c.p, c.pinv);
-  return canon2(t, c.p);
+  const int i = j >> 1;
+  const uint32_t t = canon2(mmul(r[32 + (i >> 5)], r[i & 31], c.p, c.pinv), c.p);
+  return j & 1 ? c.p - t : t;  // a power is never zero
 }
 // Powers of 2^32 for the reduction of multi-limb inputs, a row per prime:
 // entry l <= 64 = 2^(32 l) 2^64 mod p, entry POW32_STEP = Montgomery form of 2^2048
@@ -147,7 +160,8 @@ const uint32_t* points_table();          // of the current device
 constexpr int IM_JOBS = 16;                    // jobs of a group
 constexpr size_t IM_LDS = 48 * 1024;           // LDS a group of more than one job may take
 constexpr int64_t IM_MIN_BLOCKS = 1024;        // workgroups wanted before jobs share one
-size_t interp_mfma_lds(int max_D, int blocks); // largest degree bound, 64-point blocks of all jobs
+size_t interp_mfma_lds(int max_D, int blocks); // largest degree bound, interp_mfma_blocks of all jobs
+int interp_mfma_blocks(int D);                 // 64-coefficient blocks of both parities
 hipError_t configure_interp_mfma();
 void launch_interp_mfma(const ResJob* jobs_d, const int32_t* job_list_d, const int32_t* gstart_d,
                         const int64_t* gprefix_d, int ngroups, int64_t nblocks, size_t lds, const RowDesc* rows_d,
@@ -170,7 +184,7 @@ constexpr int EE_WPE_MAX = 4;
 // Revision of the evaluation kernels' code and of the tuner's choice rule,
 // part of the autotuner's cache file name: a changed kernel is tuned again
 // instead of taking stale choices.
-constexpr int EE_KERNEL_REV = 7;
+constexpr int EE_KERNEL_REV = 8;
 // workgroups of a variant resident on the whole device (0 if the query fails)
 int eval_elim_grid(int cls, int wpe, int max_T);
 // private (spill) bytes per lane of a variant's kernel (-1 if the query fails)

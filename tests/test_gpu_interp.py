@@ -31,7 +31,7 @@ def _want(f, g):
     return r
 
 
-@pytest.mark.parametrize("n1", [2, 63, 64, 65, 127, 128, 129, 1023, 1024, 1025, 2049, 4096, 4097])
+@pytest.mark.parametrize("n1", [1, 2, 63, 64, 65, 127, 128, 129, 130, 255, 257, 1024, 1025, 2047, 2049, 4097, 8191, 8193])
 def test_block_and_tile_edges(n1):
     rnd = random.Random(n1)
     D = n1 - 1
