@@ -16,6 +16,7 @@
 #include <algorithm>
 
 #include "gcd_reg.hpp"
+#include "toeplitz.hpp"
 #include "snc_internal.hpp"
 
 namespace snc {
@@ -158,18 +159,67 @@ __global__ __launch_bounds__(GCD_THREADS) void k_gcd_modp(const GcdDesc* descs, 
   }
 }
 
-template <int E>
-__device__ __forceinline__ void reg_cofactor(uint32_t (&R)[E], const uint32_t (&G)[E], int e, const uint32_t* row,
-                                             int deg, uint32_t* q, uint32_t* sm, int lane, const PrimeC& c) {
-  reg_load_staged<E>(R, row, deg, sm, lane);
-  for (int i = lane; i <= deg; i += 64) q[i] = 0u;
-  const int dR = reg_trim<E>(R, deg, c);
-  for (int t = dR - e; t >= 0; --t) {
-    const uint32_t qt = lead(R[0], c.p);  // coefficient of x^t of the quotient (G is monic)
-    if (lane == 0) q[t] = from_mont(qt, c);
-    reg_step<E>(R, G, c.r1, mneg(qt, c.p), c);
+// ---------------------------------------------------------------------------
+// Exact division by the monic gcd G (degree e), 64 quotient coefficients at a
+// time.  With the coefficients from the top, A_i = sum_{j <= e} G_j Q_{i-j}, a
+// block's right-hand side is A_i less the products with the blocks before it
+// (lane = i, Q uniform, G sliding), and the block itself the product with the
+// first 64 terms of the power series H = 1 / G (lower triangular Toeplitz).
+// Per block e + 64 multiply-adds per lane; one quotient coefficient at a time
+// over the whole dividend took (deg + 1) / 64 updates a coefficient and half
+// of the kernel (degrees 1403 and 1187 with a gcd of degree 37: 1,008 us with it,
+// 422 us now, bound by the Euclid of one wavefront per prime).
+// ---------------------------------------------------------------------------
+// H[64 + i] = h_i for i < 64, zeros below; N[j] = -G_j, zeros above e
+__device__ __forceinline__ void series_inverse(const uint32_t* N, uint32_t* H, int lane, const PrimeC& c) {
+  uint32_t acc = lane == 0 ? c.r1 : 0u;
+  for (int l = 0; l < 63; ++l) {
+    const uint32_t h = (uint32_t)__builtin_amdgcn_readlane((int)acc, l);
+    const uint32_t n = lane > l ? N[lane - l] : 0u;
+    acc = madd(acc, mmulc(h, n, c.p, c.pinv), c.p);
+  }
+  H[lane] = 0u;
+  H[64 + lane] = acc;
+  wave_sync();
+}
+
+// row: residues (Montgomery, canonical), ascending, degree at most deg; q:
+// deg + 1 quotient coefficients (plain); N, H in LDS, Q: LDS for the quotient
+// (whole blocks), R: 64 words, both 16-byte aligned
+__device__ __forceinline__ void wave_divide(const uint32_t* row, int deg, int e, const uint32_t* N, const uint32_t* H,
+                                            uint32_t* Q, uint32_t* R, uint32_t* q, int lane, const PrimeC& c) {
+  int d = deg;  // degree mod p (a leading coefficient may vanish)
+  while (d >= e && row[d] == 0) --d;
+  const int nq = d - e + 1;
+  for (int i = nq + lane; i <= deg; i += 64) q[i] = 0u;
+  uint32_t next = d - lane >= 0 ? row[d - lane] : 0u;
+  for (int b0 = 0; b0 < nq; b0 += 64) {
+    uint32_t s = next;
+    next = d - b0 - 64 - lane >= 0 ? row[d - b0 - 64 - lane] : 0u;
+    const int mm = min(e, b0);
+    for (int m = 0; m < mm; m += 16) {  // products m + 1 .. m + 16; N is zero above e
+      const uint4* U = reinterpret_cast<const uint4*>(Q + b0 - m - 16);
+      const uint4 ua = U[3], ub = U[2], uc = U[1], ud = U[0];
+      const uint32_t w[16] = {ua.w, ua.z, ua.y, ua.x, ub.w, ub.z, ub.y, ub.x,
+                              uc.w, uc.z, uc.y, uc.x, ud.w, ud.z, ud.y, ud.x};
+      uint64_t a = 0;
+#pragma unroll
+      for (int u = 0; u < 16; ++u) a += (uint64_t)w[u] * N[lane + m + 1 + u];
+      s = fold16(s, a, c);
+    }
+    R[lane] = s;
+    wave_sync();
+    const uint32_t t = toeplitz64(0u, R, H + 64 + lane, c);
+    Q[b0 + lane] = t;
+    if (b0 + lane < nq) q[d - e - b0 - lane] = from_mont(t, c);
+    wave_sync();
   }
 }
+
+// LDS words: two remainders of 64 E for the Euclid; in the division the
+// quotient in the first 64 E, then -G with zeros past it, H and the right-hand side
+__host__ __device__ constexpr int div_off(int E) { return 64 * E; }
+__host__ __device__ constexpr int gcd_reg_lds(int E) { return 2 * 64 * E + 192 + 128 + 64; }
 
 template <int E>
 __global__ __launch_bounds__(64) void k_gcd_modp_reg(const GcdDesc* descs, const int32_t* items,
@@ -183,8 +233,9 @@ __global__ __launch_bounds__(64) void k_gcd_modp_reg(const GcdDesc* descs, const
   const int T = G.da + G.db + 2;
   const uint32_t* ra = ws + G.res_off + (int64_t)slot * T;
   const uint32_t* rb = ra + G.da + 1;
-  extern __shared__ uint32_t sm[];  // 2 * 64 * E words
-  uint32_t X[E], Y[E], Gm[E];
+  extern __shared__ uint4 sm4[];  // gcd_reg_lds(E) words
+  uint32_t* sm = reinterpret_cast<uint32_t*>(sm4);
+  uint32_t X[E], Y[E];
   if (G.fused) {  // given residues of a (plain), b = a': element i of b is (da - i) times element i of a
     reg_load_staged<E>(X, G.vals + (int64_t)slot * G.vstride, G.da, sm, lane);
 #pragma unroll
@@ -212,22 +263,28 @@ __global__ __launch_bounds__(64) void k_gcd_modp_reg(const GcdDesc* descs, const
   const int e = euclid_levels<E>(X, dX, Y, dY, sm, lane, c);
   if (lane == 0) ((int32_t*)(ws + G.e_off))[slot] = e;
   if (e == 0) return;  // a usable prime with a constant gcd ends the problem on the host: no rows needed
+  // the gcd made monic, from the top in sm[0..e]
   __syncthreads();
-  reg_fetch<E>(Gm, sm, e, lane);
-  const uint32_t inv = minv(lead(Gm[0], c.p), c);
-#pragma unroll
-  for (int s = 0; s < E; ++s) Gm[s] = mmulc(Gm[s], inv, c.p, c.pinv);
+  const uint32_t inv = minv(canon4(sm[0], c.p), c);
   uint32_t* w = ws + G.w_off + (int64_t)slot * G.wl;
+  uint32_t* N = sm + div_off(E);
   for (int i = lane; i < G.wl; i += 64) w[i] = 0u;
-#pragma unroll
-  for (int s = 0; s < E; ++s) {
-    const int i = lane * E + s;
-    if (i <= e) w[e - i] = from_mont(Gm[s], c);
+  for (int i = lane; i <= e + 128; i += 64) {
+    uint32_t g = 0;
+    if (i <= e) {
+      g = mmulc(canon4(sm[i], c.p), inv, c.p, c.pinv);
+      w[e - i] = from_mont(g, c);
+    }
+    N[i] = mneg(g, c.p);
   }
+  wave_sync();
+  uint32_t* H = sm + div_off(E) + 64 * E + 192;
+  uint32_t* R = H + 128;
+  series_inverse(N, H, lane, c);
   uint32_t* u = ws + G.u_off + (int64_t)slot * (G.da + 1);
   uint32_t* v = ws + G.v_off + (int64_t)slot * (G.db + 1);
-  reg_cofactor<E>(X, Gm, e, ra, G.da, u, sm, lane, c);
-  reg_cofactor<E>(X, Gm, e, rb, G.db, v, sm, lane, c);
+  wave_divide(ra, G.da, e, N, H, sm, R, u, lane, c);
+  wave_divide(rb, G.db, e, N, H, sm, R, v, lane, c);
 }
 
 static const int kGcdE[] = {2, 4, 6, 9, 12, 16, 24, 32};
@@ -279,7 +336,7 @@ void launch_gcd_euclid(const GcdDesc* descs, const int32_t* items, int nitems, i
   const dim3 grid(nitems), blk(64);
   switch (slots) {
 #define SNC_GCD_REG(E) \
-    case E: hipLaunchKernelGGL(k_gcd_modp_reg<E>, grid, blk, 2 * 64 * E * 4, s, descs, items, primes, ws); return;
+    case E: hipLaunchKernelGGL(k_gcd_modp_reg<E>, grid, blk, gcd_reg_lds(E) * 4, s, descs, items, primes, ws); return;
     SNC_GCD_REG(2) SNC_GCD_REG(4) SNC_GCD_REG(6) SNC_GCD_REG(9)
     SNC_GCD_REG(12) SNC_GCD_REG(16) SNC_GCD_REG(24) SNC_GCD_REG(32)
 #undef SNC_GCD_REG

@@ -8,6 +8,7 @@
 
 #include "eval_elim.hpp"
 #include "general_elim.hpp"
+#include "toeplitz.hpp"
 
 namespace snc {
 
@@ -223,20 +224,6 @@ __device__ __forceinline__ uint32_t bcast(uint32_t v, int lane) {
   return (uint32_t)__builtin_amdgcn_readlane((int)v, lane);
 }
 
-// s + a 2^-32 mod p for a sum a of sixteen canonical products: a stays below
-// 16 p^2 < 2^64, and a 2^-32 = hi + REDC(lo) mod p splits it without REDC's
-// own sum (which could pass 2^64): hi = a >> 32 < 4p is taken below 2p,
-// REDC(lo) = mulhi(lo pinv, p) + (lo != 0) <= p (lo plus the low word of m p
-// is 0 mod 2^32), so hi + REDC(lo) < 3p and s + it < 4p.
-__device__ __forceinline__ uint32_t fold16(uint32_t s, uint64_t a, const PrimeC& c) {
-  uint32_t hi = (uint32_t)(a >> 32);
-  const uint32_t h2 = hi - 2 * c.p;
-  hi = h2 < hi ? h2 : hi;
-  const uint32_t lo = (uint32_t)a;
-  const uint32_t r = __umulhi(lo * c.pinv, c.p) + (lo != 0u ? 1u : 0u);
-  return canon(s + hi + r, c.p);
-}
-
 // s + sum_{q<64} u_q S[-q] with u_q = lane q of u (broadcast by readlane) and
 // S per lane; s canonical in, out
 __device__ __forceinline__ uint32_t toeplitz64_bc(uint32_t s, uint32_t u, const uint32_t* S, const PrimeC& c) {
@@ -246,24 +233,6 @@ __device__ __forceinline__ uint32_t toeplitz64_bc(uint32_t s, uint32_t u, const 
 #pragma unroll
     for (int q = g; q < g + 8; ++q) acc += (uint64_t)bcast(u, q) * S[-q];  // 8 p^2 < 2^63
     s = canon(s + redc(acc, c.p, c.pinv), c.p);
-  }
-  return s;
-}
-
-// The same with U in LDS (16-byte aligned), read four words at a time at one
-// address for the whole wavefront (no vector-unit instruction per word), and
-// sixteen products per reduction (fold16).
-__device__ __forceinline__ uint32_t toeplitz64(uint32_t s, const uint32_t* U, const uint32_t* S, const PrimeC& c) {
-#pragma unroll
-  for (int g = 0; g < IB; g += 16) {
-    const uint4* U4 = reinterpret_cast<const uint4*>(U + g);
-    const uint4 ua = U4[0], ub = U4[1], uc = U4[2], ud = U4[3];
-    const uint32_t w16[16] = {ua.x, ua.y, ua.z, ua.w, ub.x, ub.y, ub.z, ub.w,
-                              uc.x, uc.y, uc.z, uc.w, ud.x, ud.y, ud.z, ud.w};
-    uint64_t acc = 0;
-#pragma unroll
-    for (int q = 0; q < 16; ++q) acc += (uint64_t)w16[q] * S[-(g + q)];
-    s = fold16(s, acc, c);
   }
   return s;
 }
