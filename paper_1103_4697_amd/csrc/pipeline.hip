@@ -84,7 +84,7 @@ void layout_batch(const std::vector<ResPlan>& plans, BatchLayout& lay) {
   lay.crt_small_on = small_coefs >= CRT_SMALL_MIN_COEFS;
   for (int j = 0; j < NJ; ++j) {
     const int k = plans[lay.dev[j]].k;
-    const int cc = lay.crt_small_on ? crt_small_class(k) : -1;
+    const int cc = lay.crt_small_on && k < CRT_MFMA_MIN ? crt_small_class(k) : -1;
     if (cc >= 0) lay.n_crts_jobs[cc]++;
     else if (k >= CRT_MFMA_MIN) lay.n_crtm_jobs++;
     else lay.n_crtb_jobs++;
@@ -140,7 +140,7 @@ void layout_batch(const std::vector<ResPlan>& plans, BatchLayout& lay) {
     J.acc_off = (int64_t)w;  // unused: the combine step keeps its accumulators in LDS
     lay.nb_red += reduce_blocks(P.k, P.T);
     reduce_again += (double)P.k * ((np - 1) / EE_BLOCK) * ((P.T + 63) / 64) * (3 * P.nl + 8);
-    const int cc = lay.crt_small_on ? crt_small_class(P.k) : -1;
+    const int cc = lay.crt_small_on && P.k < CRT_MFMA_MIN ? crt_small_class(P.k) : -1;
     if (cc >= 0) {
       lay.nb_crts[cc] += (int64_t)((n1 + 63) / 64);
     } else if (P.k >= CRT_MFMA_MIN) {
@@ -282,23 +282,38 @@ void launch_pipeline(const BatchLayout& lay, uint8_t* ws, hipStream_t s, StageTi
   }
   if (part == PIPE_TO_INTERP) return;
   static const char* const kCrtStage[NCRT_SMALL] = {"crt_small_32", "crt_small_64", "crt_small_128"};
-  // The class with the most primes has the fewest, longest workgroups (one
-  // round on the device, each bound by its own latency): on a branch it runs
-  // beside the other classes instead of after them.
+  // The jobs on the matrix cores (or, without any, the small-prime class with
+  // the most primes: few, long workgroups bound by their own latency) run on a
+  // branch beside the other classes instead of after them.
   int nsmall = 0, top = -1;
   for (int c = 0; c < NCRT_SMALL; ++c)
     if (lay.n_crts_jobs[c]) { ++nsmall; top = c; }
-  const bool branch = fk.stream && !tm && nsmall >= 2;
+  const CrtTables tb = global_crt_tables();
+  auto small = [&](int c, hipStream_t st) {
+    launch_crt_small(c, jobs, (const int32_t*)(ws + lay.list_crts[c]), (const int64_t*)(ws + lay.pref_crts[c]),
+                     lay.n_crts_jobs[c], lay.nb_crts[c], wsw, st);
+  };
+  auto mfma = [&](hipStream_t st) {
+    const int32_t* lm = (const int32_t*)(ws + lay.list_crtm);
+    const int64_t* pg = (const int64_t*)(ws + lay.pref_crtm_grp);
+    launch_crt_mfma_digits(tb, jobs, lm, pg, lay.n_crtm_jobs, lay.nb_crtm_grp, lay.max_k_crtm, wsw, st);
+    if (tm) tm->mark("crt_mfma_digits", 1);
+    launch_crt_mfma_product(jobs, lm, (const int64_t*)(ws + lay.pref_crtm_tile), lay.n_crtm_jobs, lay.nb_crtm_tile,
+                            wsw, st);
+    if (tm) tm->mark("crt_mfma_product", 1);
+    launch_crt_mfma_carry(tb, jobs, lm, pg, lay.n_crtm_jobs, lay.nb_crtm_grp, lay.max_k_crtm, wsw, st);
+    if (tm) tm->mark("crt_mfma_carry", 1);
+  };
+  const bool branch = fk.stream && !tm && (lay.n_crtm_jobs ? nsmall >= 1 : nsmall >= 2);
   if (branch) {
     (void)hipEventRecord(fk.fork, s);
     (void)hipStreamWaitEvent(fk.stream, fk.fork, 0);
-    launch_crt_small(top, jobs, (const int32_t*)(ws + lay.list_crts[top]), (const int64_t*)(ws + lay.pref_crts[top]),
-                     lay.n_crts_jobs[top], lay.nb_crts[top], wsw, fk.stream);
+    if (lay.n_crtm_jobs) mfma(fk.stream);
+    else small(top, fk.stream);
   }
   for (int c = 0; c < NCRT_SMALL; ++c) {
-    if (!lay.n_crts_jobs[c] || (branch && c == top)) continue;
-    launch_crt_small(c, jobs, (const int32_t*)(ws + lay.list_crts[c]), (const int64_t*)(ws + lay.pref_crts[c]),
-                     lay.n_crts_jobs[c], lay.nb_crts[c], wsw, s);
+    if (!lay.n_crts_jobs[c] || (branch && !lay.n_crtm_jobs && c == top)) continue;
+    small(c, s);
     if (tm) tm->mark(kCrtStage[c], 1);
   }
   if (branch) {
@@ -306,27 +321,14 @@ void launch_pipeline(const BatchLayout& lay, uint8_t* ws, hipStream_t s, StageTi
     (void)hipStreamWaitEvent(s, fk.join, 0);
   }
   if (lay.n_crtb_jobs) {
-    const CrtTables tb = global_crt_tables();
     const int32_t* lb = (const int32_t*)(ws + lay.list_crtb);
     launch_crt_digits(tb, jobs, lb, (const int64_t*)(ws + lay.pref_crtd), lay.n_crtb_jobs, lay.nb_crtd, wsw, s);
     if (tm) tm->mark("crt_digits", 1);
     launch_crt_combine(tb, jobs, lb, (const int64_t*)(ws + lay.pref_crtc), lay.n_crtb_jobs, lay.nb_crtc,
-                       (int)std::min<int64_t>(lay.max_k, CRT_MFMA_MIN - 1),
-                       wsw, s);
+                       (int)std::min<int64_t>(lay.max_k, CRT_MFMA_MIN - 1), wsw, s);
     if (tm) tm->mark("crt_combine", 1);
   }
-  if (lay.n_crtm_jobs) {
-    const CrtTables tb = global_crt_tables();
-    const int32_t* lm = (const int32_t*)(ws + lay.list_crtm);
-    const int64_t* pg = (const int64_t*)(ws + lay.pref_crtm_grp);
-    launch_crt_mfma_digits(tb, jobs, lm, pg, lay.n_crtm_jobs, lay.nb_crtm_grp, lay.max_k_crtm, wsw, s);
-    if (tm) tm->mark("crt_mfma_digits", 1);
-    launch_crt_mfma_product(jobs, lm, (const int64_t*)(ws + lay.pref_crtm_tile), lay.n_crtm_jobs, lay.nb_crtm_tile,
-                            wsw, s);
-    if (tm) tm->mark("crt_mfma_product", 1);
-    launch_crt_mfma_carry(tb, jobs, lm, pg, lay.n_crtm_jobs, lay.nb_crtm_grp, lay.max_k_crtm, wsw, s);
-    if (tm) tm->mark("crt_mfma_carry", 1);
-  }
+  if (lay.n_crtm_jobs && !branch) mfma(s);
 }
 
 // Essential lane-operations of one evaluation block (64 instances): Horner
@@ -417,7 +419,7 @@ void fill_header(const BatchLayout& lay, const std::vector<ResPlan>& plans, cons
     cw += (size_t)P.T * P.nl;
     const int64_t n1 = P.D + 1;
     pr[j + 1] = pr[j] + reduce_blocks(P.k, P.T);
-    const int cc = lay.crt_small_on ? crt_small_class(P.k) : -1;
+    const int cc = lay.crt_small_on && P.k < CRT_MFMA_MIN ? crt_small_class(P.k) : -1;
     if (cc >= 0) {
       ls[cc][ns[cc]] = j;
       ps[cc][ns[cc] + 1] = ps[cc][ns[cc]] + (n1 + 63) / 64;
