@@ -27,7 +27,7 @@
 namespace snc {
 
 constexpr int NOALLOC_MAX_DEVICES = 64;
-constexpr size_t NOALLOC_HEADER_BYTES = (size_t)9 << 20;  // host upload block
+constexpr size_t NOALLOC_HEADER_BYTES = (size_t)8 << 20;  // host upload block
 
 static __device__ __align__(256) uint8_t scratch[SNC_NOALLOC_SCRATCH_BYTES];
 

@@ -43,6 +43,8 @@ void snc_ctx::release() {
   side_stream = nullptr;
   if (ev_mid) (void)hipEventDestroy(ev_mid);
   ev_mid = nullptr;
+  if (ev_tail) (void)hipEventDestroy(ev_tail);
+  ev_tail = nullptr;
   if (fork_stream) (void)hipStreamDestroy(fork_stream);
   fork_stream = nullptr;
   if (ev_fork) (void)hipEventDestroy(ev_fork);
@@ -61,11 +63,67 @@ namespace snc {
 
 static size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
+// Essential lane-operations of one evaluation block (64 instances): Horner
+// on the powers of one parity (0.75 per coefficient), the fused remainder steps (5 per entry of
+// each remainder), the first remainder's elementary steps and the final
+// powers and inversion.
+static int64_t eval_block_cost(const ResPlan& P) {
+  const int64_t m = P.m, n = P.n;
+  return 3 * (int64_t)P.T / 4 + 5 * n * (n + 1) / 2 + 4 * n * std::max<int64_t>(m - n - 1, 0) + 300;
+}
+
+// Download and collection of a large output block in chunks: the copy of
+// chunk c+1 runs while host threads widen chunk c into the caller's buffers.
+constexpr size_t COLLECT_CHUNKED_WORDS = (size_t)1 << 20;
+constexpr int COLLECT_CHUNKS = 8;
+
+// Remaindering of a job: class of the one-lane-per-coefficient kernel, or
+// CRT_B (lanes over primes), CRT_M (matrix cores)
+constexpr int CRT_B = -1, CRT_M = -2;
+static int crt_kind(const BatchLayout& lay, int k) {
+  if (k >= CRT_MFMA_MIN) return CRT_M;
+  return lay.crt_small_on ? crt_small_class(k) : CRT_B;
+}
+
+// Two tails when the output is large enough to be downloaded in chunks and
+// the classes besides the one with the most output words take at least a
+// tenth of the evaluation: the first tail's download (PCIe) then runs beside
+// their evaluation.  Orders lay.dev so that each tail's jobs are consecutive.
+// Pipelined runs overlap their downloads with the next run instead and take
+// the tail of all jobs (97 pairs pipelined in two tails: 2.17 -> 2.45 ms).
+static void choose_tails(const std::vector<ResPlan>& plans, BatchLayout& lay) {
+  double words[NCLS + 1] = {0}, cost[NCLS + 1] = {0}, all_words = 0, all_cost = 0;
+  for (int i : lay.dev) {
+    const ResPlan& P = plans[i];
+    const int c = P.cls >= 0 ? P.cls : NCLS;
+    const double w = ((double)P.D + 1) * P.L, e = (double)P.k * npts_of(P.D) * (double)eval_block_cost(P);
+    words[c] += w; all_words += w;
+    cost[c] += e; all_cost += e;
+  }
+  int h = 0;
+  for (int c = 1; c <= NCLS; ++c)
+    if (words[c] > words[h]) h = c;
+  lay.ntails = all_words >= (double)COLLECT_CHUNKED_WORDS && all_cost - cost[h] >= 0.1 * all_cost ? 2 : 1;
+  lay.tail[0].j1 = (int)lay.dev.size();
+  lay.tail[0].classes = (1u << NCLS) - 1;
+  lay.tail[0].general = true;
+  if (lay.ntails == 1) return;
+  auto mid = std::stable_partition(lay.dev.begin(), lay.dev.end(),
+                                   [&](int i) { return (plans[i].cls >= 0 ? plans[i].cls : NCLS) == h; });
+  lay.tail[1] = lay.tail[TAIL_WHOLE] = lay.tail[0];
+  lay.tail[0].j1 = lay.tail[1].j0 = (int)(mid - lay.dev.begin());
+  lay.tail[0].classes = h < NCLS ? 1u << h : 0u;
+  lay.tail[0].general = h == NCLS;
+  lay.tail[1].classes &= ~lay.tail[0].classes;
+  lay.tail[1].general = !lay.tail[0].general;
+}
+
 void layout_batch(const std::vector<ResPlan>& plans, BatchLayout& lay) {
   lay = BatchLayout();
   for (int i = 0; i < (int)plans.size(); ++i)
     if (!plans[i].trivial) lay.dev.push_back(i);
   const int NJ = (int)lay.dev.size();
+  choose_tails(plans, lay);
   lay.jobs.resize(NJ);
   size_t off = 0;
   lay.jobs_off = off; off = align256(off + sizeof(ResJob) * NJ);
@@ -74,31 +132,45 @@ void layout_batch(const std::vector<ResPlan>& plans, BatchLayout& lay) {
   lay.n_rows = nrows;
   lay.rows_off = off; off = align256(off + sizeof(RowDesc) * nrows);
   lay.pref_red = off; off = align256(off + 8 * (NJ + 1));
-  lay.pref_interp = off; off = align256(off + 8 * (NJ + 1));
-  lay.start_im = off; off = align256(off + 4 * (NJ + 1));
   // one lane per coefficient pays off only when the batch's few-prime coefficients fill the device
   // (a wavefront per CU); otherwise the lanes go over the primes of each coefficient
   int64_t small_coefs = 0;
   for (int j = 0; j < NJ; ++j)
     if (crt_small_class(plans[lay.dev[j]].k) >= 0) small_coefs += plans[lay.dev[j]].D + 1;
   lay.crt_small_on = small_coefs >= CRT_SMALL_MIN_COEFS;
-  for (int j = 0; j < NJ; ++j) {
-    const int k = plans[lay.dev[j]].k;
-    const int cc = lay.crt_small_on && k < CRT_MFMA_MIN ? crt_small_class(k) : -1;
-    if (cc >= 0) lay.n_crts_jobs[cc]++;
-    else if (k >= CRT_MFMA_MIN) lay.n_crtm_jobs++;
-    else lay.n_crtb_jobs++;
+  for (int x = 0; x < lay.tails(); ++x) {
+    BatchTail& t = lay.tail[x];
+    const size_t n = (size_t)(t.j1 - t.j0);
+    for (int j = t.j0; j < t.j1; ++j) {
+      const ResPlan& P = plans[lay.dev[j]];
+      const int n1 = P.D + 1, kind = crt_kind(lay, P.k);
+      if (kind >= 0) {
+        t.n_crts_jobs[kind]++;
+        t.nb_crts[kind] += (n1 + 63) / 64;
+      } else if (kind == CRT_M) {
+        t.n_crtm_jobs++;
+        t.nb_crtm_grp += crt_mfma_groups(n1);
+        t.nb_crtm_tile += crt_mfma_tiles(n1, P.k);
+        t.max_k_crtm = std::max(t.max_k_crtm, P.k);
+      } else {
+        t.n_crtb_jobs++;
+        t.nb_crtd += (n1 + CRT_COEF_PER_BLOCK - 1) / CRT_COEF_PER_BLOCK;
+        t.nb_crtc += (n1 + CRT_COMB_PER_BLOCK - 1) / CRT_COMB_PER_BLOCK;
+      }
+    }
+    t.list_im = off; off = align256(off + 4 * std::max<size_t>(n, 1));
+    t.start_im = off; off = align256(off + 4 * (n + 1));
+    t.pref_interp = off; off = align256(off + 8 * (n + 1));
+    // one section each for the jobs of both kinds of the other remaindering
+    const size_t nbm = (size_t)t.n_crtb_jobs + t.n_crtm_jobs;
+    t.pref_crtd = off; t.pref_crtm_grp = off + 8 * (t.n_crtb_jobs + 1); off = align256(off + 8 * (nbm + 2));
+    t.pref_crtc = off; t.pref_crtm_tile = off + 8 * (t.n_crtb_jobs + 1); off = align256(off + 8 * (nbm + 2));
+    t.list_crtb = off; t.list_crtm = off + 4 * t.n_crtb_jobs; off = align256(off + 4 * std::max<size_t>(nbm, 1));
+    for (int c = 0; c < NCRT_SMALL; ++c) {
+      t.pref_crts[c] = off; off = align256(off + 8 * (t.n_crts_jobs[c] + 1));
+      t.list_crts[c] = off; off = align256(off + 4 * std::max(t.n_crts_jobs[c], 1));
+    }
   }
-  // one section each for the jobs of both kinds of the other remaindering
-  const size_t nbm = (size_t)lay.n_crtb_jobs + lay.n_crtm_jobs;
-  lay.pref_crtd = off; lay.pref_crtm_grp = off + 8 * (lay.n_crtb_jobs + 1); off = align256(off + 8 * (nbm + 2));
-  lay.pref_crtc = off; lay.pref_crtm_tile = off + 8 * (lay.n_crtb_jobs + 1); off = align256(off + 8 * (nbm + 2));
-  for (int c = 0; c < NCRT_SMALL; ++c) {
-    lay.pref_crts[c] = off; off = align256(off + 8 * (lay.n_crts_jobs[c] + 1));
-    lay.list_crts[c] = off; off = align256(off + 4 * std::max(lay.n_crts_jobs[c], 1));
-  }
-  lay.list_crtb = off; lay.list_crtm = off + 4 * lay.n_crtb_jobs; off = align256(off + 4 * std::max<size_t>(nbm, 1));
-  lay.list_im = off; off = align256(off + 4 * std::max(NJ, 1));
   for (int j = 0; j < NJ; ++j) {
     const ResPlan& P = plans[lay.dev[j]];
     if (P.cls >= 0) lay.n_ee_jobs[P.cls]++; else lay.n_gen_jobs++;
@@ -140,17 +212,6 @@ void layout_batch(const std::vector<ResPlan>& plans, BatchLayout& lay) {
     J.acc_off = (int64_t)w;  // unused: the combine step keeps its accumulators in LDS
     lay.nb_red += reduce_blocks(P.k, P.T);
     reduce_again += (double)P.k * ((np - 1) / EE_BLOCK) * ((P.T + 63) / 64) * (3 * P.nl + 8);
-    const int cc = lay.crt_small_on && P.k < CRT_MFMA_MIN ? crt_small_class(P.k) : -1;
-    if (cc >= 0) {
-      lay.nb_crts[cc] += (int64_t)((n1 + 63) / 64);
-    } else if (P.k >= CRT_MFMA_MIN) {
-      lay.nb_crtm_grp += crt_mfma_groups((int)n1);
-      lay.nb_crtm_tile += crt_mfma_tiles((int)n1, P.k);
-      lay.max_k_crtm = std::max(lay.max_k_crtm, P.k);
-    } else {
-      lay.nb_crtd += (int64_t)((n1 + CRT_COEF_PER_BLOCK - 1) / CRT_COEF_PER_BLOCK);
-      lay.nb_crtc += (int64_t)((n1 + CRT_COMB_PER_BLOCK - 1) / CRT_COMB_PER_BLOCK);
-    }
     lay.max_k = std::max(lay.max_k, P.k);
     if (P.cls >= 0) {
       lay.nb_ee[P.cls] += (int64_t)P.k * ((np + EE_BLOCK - 1) / EE_BLOCK);
@@ -166,25 +227,29 @@ void layout_batch(const std::vector<ResPlan>& plans, BatchLayout& lay) {
   int64_t npairs = 0;
   for (const ResJob& J : lay.jobs) npairs += J.k;
   const int per = (int)std::min<int64_t>(IM_JOBS, std::max<int64_t>(1, npairs / IM_MIN_BLOCKS));
-  lay.im_order.resize(NJ);
-  for (int j = 0; j < NJ; ++j) lay.im_order[j] = j;
-  std::stable_sort(lay.im_order.begin(), lay.im_order.end(),
-                   [&](int x, int y) { return lay.jobs[x].D > lay.jobs[y].D; });
-  lay.im_start.assign(1, 0);
-  for (int t = 0; t < NJ;) {
-    const int top = lay.jobs[lay.im_order[t]].D;
-    int u = t, blocks = 0, kmax = 0;
-    for (; u < NJ && u - t < per; ++u) {
-      const ResJob& J = lay.jobs[lay.im_order[u]];
-      const int nb = blocks + interp_mfma_blocks(J.D);
-      if (u > t && interp_mfma_lds(top, nb) > IM_LDS) break;
-      blocks = nb;
-      kmax = std::max(kmax, (int)J.k);
+  for (int x = 0; x < lay.tails(); ++x) {
+    BatchTail& tl = lay.tail[x];
+    const int n = tl.j1 - tl.j0;
+    tl.im_order.resize(n);
+    for (int j = 0; j < n; ++j) tl.im_order[j] = tl.j0 + j;
+    std::stable_sort(tl.im_order.begin(), tl.im_order.end(),
+                     [&](int a, int b) { return lay.jobs[a].D > lay.jobs[b].D; });
+    tl.im_start.assign(1, 0);
+    for (int t = 0; t < n;) {
+      const int top = lay.jobs[tl.im_order[t]].D;
+      int u = t, blocks = 0, kmax = 0;
+      for (; u < n && u - t < per; ++u) {
+        const ResJob& J = lay.jobs[tl.im_order[u]];
+        const int nb = blocks + interp_mfma_blocks(J.D);
+        if (u > t && interp_mfma_lds(top, nb) > IM_LDS) break;
+        blocks = nb;
+        kmax = std::max(kmax, (int)J.k);
+      }
+      tl.im_lds = std::max(tl.im_lds, interp_mfma_lds(top, blocks));
+      tl.nb_interp += kmax;
+      tl.im_start.push_back(u);
+      t = u;
     }
-    lay.im_lds = std::max(lay.im_lds, interp_mfma_lds(top, blocks));
-    lay.nb_interp += kmax;
-    lay.im_start.push_back(u);
-    t = u;
   }
   // Every job on the evaluation kernel's LDS variant: it can reduce the
   // inputs itself, once per 64-point block of a prime.  With long
@@ -247,38 +312,42 @@ struct StageTimer {
 // Device launch sequence for a laid-out batch (everything after the upload).
 // part: PIPE_ALL, PIPE_TO_INTERP (reduction .. interpolation) or PIPE_CRT
 void launch_pipeline(const BatchLayout& lay, uint8_t* ws, hipStream_t s, StageTimer* tm, int part,
-                     const PipeFork& fk) {
+                     const PipeFork& fk, int tail) {
+  if (tail < 0) tail = lay.whole();
+  const BatchTail& t = lay.tail[tail];
   uint32_t* wsw = (uint32_t*)ws;
   const ResJob* jobs = (const ResJob*)(ws + lay.jobs_off);
   const RowDesc* rows = (const RowDesc*)(ws + lay.rows_off);
-  const int NJ = (int)lay.jobs.size();
   if (part != PIPE_CRT) {
-  if (!lay.reduce_in_eval) launch_reduce(jobs, (const int64_t*)(ws + lay.pref_red), NJ, lay.nb_red, wsw, wsw, s);
-  if (tm) tm->mark("reduce", lay.reduce_in_eval ? 0 : 1);
-  // one stage per register class (names: eval_elim_<width>), then the
-  // jobs above the register classes
-  static const char* const kEEStage[NCLS] = {"eval_elim_8", "eval_elim_16", "eval_elim_32", "eval_elim_40",
-                                             "eval_elim_48", "eval_elim_64"};
-  uint32_t* ee_counters = (uint32_t*)(ws + lay.ee_counter_off);
-  bool persistent = false;
-  for (int c = 0; c < NCLS; ++c) persistent |= lay.n_ee_jobs[c] && lay.ee_var[c].chunk > 0;
-  if (persistent) launch_zero_u32(ee_counters, NCLS, s);  // a kernel, not a memset node
-  for (int c = 0; c < NCLS; ++c) {
-    if (!lay.n_ee_jobs[c]) continue;
-    launch_eval_elim(c, lay.ee_var[c], ee_counters + c, jobs, (const int32_t*)(ws + lay.list_ee[c]),
-                     (const int64_t*)(ws + lay.pref_ee[c]), lay.n_ee_jobs[c], lay.nb_ee[c], lay.max_T_ee[c], rows,
-                     wsw, lay.reduce_in_eval, s);
-    if (tm) tm->mark(kEEStage[c], 1);
-  }
-  if (lay.n_gen_jobs) {
-    launch_elim_general_all(jobs, (const int32_t*)(ws + lay.list_gen), (const int64_t*)(ws + lay.pref_gen),
-                            lay.n_gen_jobs, lay.n_gen_inst, rows, wsw, s);
-    if (tm) tm->mark("eval_elim_general", 1);
-  }
-  launch_interp_mfma(jobs, (const int32_t*)(ws + lay.list_im), (const int32_t*)(ws + lay.start_im),
-                     (const int64_t*)(ws + lay.pref_interp), (int)lay.im_start.size() - 1, lay.nb_interp, lay.im_lds,
-                     rows, wsw, s);
-  if (tm) tm->mark("interp", 1);
+    uint32_t* ee_counters = (uint32_t*)(ws + lay.ee_counter_off);
+    if (tail != 1) {  // before everything
+      if (!lay.reduce_in_eval)
+        launch_reduce(jobs, (const int64_t*)(ws + lay.pref_red), (int)lay.jobs.size(), lay.nb_red, wsw, wsw, s);
+      if (tm) tm->mark("reduce", lay.reduce_in_eval ? 0 : 1);
+      bool persistent = false;
+      for (int c = 0; c < NCLS; ++c) persistent |= lay.n_ee_jobs[c] && lay.ee_var[c].chunk > 0;
+      if (persistent) launch_zero_u32(ee_counters, NCLS, s);  // a kernel, not a memset node
+    }
+    // one stage per register class (names: eval_elim_<width>), then the
+    // jobs above the register classes
+    static const char* const kEEStage[NCLS] = {"eval_elim_8", "eval_elim_16", "eval_elim_32", "eval_elim_40",
+                                               "eval_elim_48", "eval_elim_64"};
+    for (int c = 0; c < NCLS; ++c) {
+      if (!lay.n_ee_jobs[c] || !(t.classes >> c & 1u)) continue;
+      launch_eval_elim(c, lay.ee_var[c], ee_counters + c, jobs, (const int32_t*)(ws + lay.list_ee[c]),
+                       (const int64_t*)(ws + lay.pref_ee[c]), lay.n_ee_jobs[c], lay.nb_ee[c], lay.max_T_ee[c], rows,
+                       wsw, lay.reduce_in_eval, s);
+      if (tm) tm->mark(kEEStage[c], 1);
+    }
+    if (lay.n_gen_jobs && t.general) {
+      launch_elim_general_all(jobs, (const int32_t*)(ws + lay.list_gen), (const int64_t*)(ws + lay.pref_gen),
+                              lay.n_gen_jobs, lay.n_gen_inst, rows, wsw, s);
+      if (tm) tm->mark("eval_elim_general", 1);
+    }
+    launch_interp_mfma(jobs, (const int32_t*)(ws + t.list_im), (const int32_t*)(ws + t.start_im),
+                       (const int64_t*)(ws + t.pref_interp), (int)t.im_start.size() - 1, t.nb_interp, t.im_lds, rows,
+                       wsw, s);
+    if (tm) tm->mark("interp", 1);
   }
   if (part == PIPE_TO_INTERP) return;
   static const char* const kCrtStage[NCRT_SMALL] = {"crt_small_32", "crt_small_64", "crt_small_128"};
@@ -287,32 +356,32 @@ void launch_pipeline(const BatchLayout& lay, uint8_t* ws, hipStream_t s, StageTi
   // branch beside the other classes instead of after them.
   int nsmall = 0, top = -1;
   for (int c = 0; c < NCRT_SMALL; ++c)
-    if (lay.n_crts_jobs[c]) { ++nsmall; top = c; }
+    if (t.n_crts_jobs[c]) { ++nsmall; top = c; }
   const CrtTables tb = global_crt_tables();
   auto small = [&](int c, hipStream_t st) {
-    launch_crt_small(c, jobs, (const int32_t*)(ws + lay.list_crts[c]), (const int64_t*)(ws + lay.pref_crts[c]),
-                     lay.n_crts_jobs[c], lay.nb_crts[c], wsw, st);
+    launch_crt_small(c, jobs, (const int32_t*)(ws + t.list_crts[c]), (const int64_t*)(ws + t.pref_crts[c]),
+                     t.n_crts_jobs[c], t.nb_crts[c], wsw, st);
   };
   auto mfma = [&](hipStream_t st) {
-    const int32_t* lm = (const int32_t*)(ws + lay.list_crtm);
-    const int64_t* pg = (const int64_t*)(ws + lay.pref_crtm_grp);
-    launch_crt_mfma_digits(tb, jobs, lm, pg, lay.n_crtm_jobs, lay.nb_crtm_grp, lay.max_k_crtm, wsw, st);
+    const int32_t* lm = (const int32_t*)(ws + t.list_crtm);
+    const int64_t* pg = (const int64_t*)(ws + t.pref_crtm_grp);
+    launch_crt_mfma_digits(tb, jobs, lm, pg, t.n_crtm_jobs, t.nb_crtm_grp, t.max_k_crtm, wsw, st);
     if (tm) tm->mark("crt_mfma_digits", 1);
-    launch_crt_mfma_product(jobs, lm, (const int64_t*)(ws + lay.pref_crtm_tile), lay.n_crtm_jobs, lay.nb_crtm_tile,
+    launch_crt_mfma_product(jobs, lm, (const int64_t*)(ws + t.pref_crtm_tile), t.n_crtm_jobs, t.nb_crtm_tile,
                             wsw, st);
     if (tm) tm->mark("crt_mfma_product", 1);
-    launch_crt_mfma_carry(tb, jobs, lm, pg, lay.n_crtm_jobs, lay.nb_crtm_grp, lay.max_k_crtm, wsw, st);
+    launch_crt_mfma_carry(tb, jobs, lm, pg, t.n_crtm_jobs, t.nb_crtm_grp, t.max_k_crtm, wsw, st);
     if (tm) tm->mark("crt_mfma_carry", 1);
   };
-  const bool branch = fk.stream && !tm && (lay.n_crtm_jobs ? nsmall >= 1 : nsmall >= 2);
+  const bool branch = fk.stream && !tm && (t.n_crtm_jobs ? nsmall >= 1 : nsmall >= 2);
   if (branch) {
     (void)hipEventRecord(fk.fork, s);
     (void)hipStreamWaitEvent(fk.stream, fk.fork, 0);
-    if (lay.n_crtm_jobs) mfma(fk.stream);
+    if (t.n_crtm_jobs) mfma(fk.stream);
     else small(top, fk.stream);
   }
   for (int c = 0; c < NCRT_SMALL; ++c) {
-    if (!lay.n_crts_jobs[c] || (branch && !lay.n_crtm_jobs && c == top)) continue;
+    if (!t.n_crts_jobs[c] || (branch && !t.n_crtm_jobs && c == top)) continue;
     small(c, s);
     if (tm) tm->mark(kCrtStage[c], 1);
   }
@@ -320,24 +389,15 @@ void launch_pipeline(const BatchLayout& lay, uint8_t* ws, hipStream_t s, StageTi
     (void)hipEventRecord(fk.join, fk.stream);
     (void)hipStreamWaitEvent(s, fk.join, 0);
   }
-  if (lay.n_crtb_jobs) {
-    const int32_t* lb = (const int32_t*)(ws + lay.list_crtb);
-    launch_crt_digits(tb, jobs, lb, (const int64_t*)(ws + lay.pref_crtd), lay.n_crtb_jobs, lay.nb_crtd, wsw, s);
+  if (t.n_crtb_jobs) {
+    const int32_t* lb = (const int32_t*)(ws + t.list_crtb);
+    launch_crt_digits(tb, jobs, lb, (const int64_t*)(ws + t.pref_crtd), t.n_crtb_jobs, t.nb_crtd, wsw, s);
     if (tm) tm->mark("crt_digits", 1);
-    launch_crt_combine(tb, jobs, lb, (const int64_t*)(ws + lay.pref_crtc), lay.n_crtb_jobs, lay.nb_crtc,
+    launch_crt_combine(tb, jobs, lb, (const int64_t*)(ws + t.pref_crtc), t.n_crtb_jobs, t.nb_crtc,
                        (int)std::min<int64_t>(lay.max_k, CRT_MFMA_MIN - 1), wsw, s);
     if (tm) tm->mark("crt_combine", 1);
   }
-  if (lay.n_crtm_jobs && !branch) mfma(s);
-}
-
-// Essential lane-operations of one evaluation block (64 instances): Horner
-// on the powers of one parity (0.75 per coefficient), the fused remainder steps (5 per entry of
-// each remainder), the first remainder's elementary steps and the final
-// powers and inversion.
-static int64_t eval_block_cost(const ResPlan& P) {
-  const int64_t m = P.m, n = P.n;
-  return 3 * (int64_t)P.T / 4 + 5 * n * (n + 1) / 2 + 4 * n * std::max<int64_t>(m - n - 1, 0) + 300;
+  if (t.n_crtm_jobs && !branch) mfma(s);
 }
 
 // Fill the upload block: job descriptors, row descriptors, block prefixes,
@@ -349,8 +409,6 @@ void fill_header(const BatchLayout& lay, const std::vector<ResPlan>& plans, cons
   RowDesc* rows = (RowDesc*)(h + lay.rows_off);
   uint32_t* coef = (uint32_t*)(h + lay.coef_off);
   int64_t* pr = (int64_t*)(h + lay.pref_red);
-  int64_t* pd = (int64_t*)(h + lay.pref_crtd);
-  int64_t* pc = (int64_t*)(h + lay.pref_crtc);
   int64_t* pe[NCLS];
   int32_t* le[NCLS];
   int ne[NCLS] = {0};
@@ -359,27 +417,12 @@ void fill_header(const BatchLayout& lay, const std::vector<ResPlan>& plans, cons
     le[c] = (int32_t*)(h + lay.list_ee[c]);
     pe[c][0] = 0;
   }
-  int64_t* ps[NCRT_SMALL];
-  int32_t* ls[NCRT_SMALL];
-  int ns[NCRT_SMALL] = {0};
-  for (int c = 0; c < NCRT_SMALL; ++c) {
-    ps[c] = (int64_t*)(h + lay.pref_crts[c]);
-    ls[c] = (int32_t*)(h + lay.list_crts[c]);
-    ps[c][0] = 0;
-  }
-  int32_t* lbig = (int32_t*)(h + lay.list_crtb);
-  int nbig = 0;
-  int32_t* lmm = (int32_t*)(h + lay.list_crtm);
-  int64_t* pmg = (int64_t*)(h + lay.pref_crtm_grp);
-  int64_t* pmt = (int64_t*)(h + lay.pref_crtm_tile);
-  int nmm = 0;
-  pmg[0] = pmt[0] = 0;
   std::vector<std::pair<int64_t, int>> by_cost[NCLS];  // (work per block, job) per register class
   int64_t* pg = (int64_t*)(h + lay.pref_gen);
   int32_t* lg = (int32_t*)(h + lay.list_gen);
   int ng = 0;
   pg[0] = 0;
-  pr[0] = pd[0] = pc[0] = 0;
+  pr[0] = 0;
   size_t cw = 0;
   for (int j = 0; j < NJ; ++j) {
     const int idx = lay.dev[j];
@@ -417,24 +460,7 @@ void fill_header(const BatchLayout& lay, const std::vector<ResPlan>& plans, cons
     emit(A, ra, P.m);
     emit(B, ra + P.rstride, P.n);
     cw += (size_t)P.T * P.nl;
-    const int64_t n1 = P.D + 1;
     pr[j + 1] = pr[j] + reduce_blocks(P.k, P.T);
-    const int cc = lay.crt_small_on && P.k < CRT_MFMA_MIN ? crt_small_class(P.k) : -1;
-    if (cc >= 0) {
-      ls[cc][ns[cc]] = j;
-      ps[cc][ns[cc] + 1] = ps[cc][ns[cc]] + (n1 + 63) / 64;
-      ns[cc]++;
-    } else if (P.k >= CRT_MFMA_MIN) {
-      lmm[nmm] = j;
-      pmg[nmm + 1] = pmg[nmm] + crt_mfma_groups((int)n1);
-      pmt[nmm + 1] = pmt[nmm] + crt_mfma_tiles((int)n1, P.k);
-      nmm++;
-    } else {
-      lbig[nbig] = j;
-      pd[nbig + 1] = pd[nbig] + (n1 + CRT_COEF_PER_BLOCK - 1) / CRT_COEF_PER_BLOCK;
-      pc[nbig + 1] = pc[nbig] + (n1 + CRT_COMB_PER_BLOCK - 1) / CRT_COMB_PER_BLOCK;
-      nbig++;
-    }
     if (P.cls >= 0) {
       by_cost[P.cls].push_back({eval_block_cost(P), j});
     } else {
@@ -443,16 +469,50 @@ void fill_header(const BatchLayout& lay, const std::vector<ResPlan>& plans, cons
       ng++;
     }
   }
-  // the interpolation's job order, groups and their prime counts
-  {
-    std::memcpy(h + lay.list_im, lay.im_order.data(), 4 * (size_t)NJ);
-    std::memcpy(h + lay.start_im, lay.im_start.data(), 4 * lay.im_start.size());
-    int64_t* pg2 = (int64_t*)(h + lay.pref_interp);
-    pg2[0] = 0;
-    for (size_t g = 0; g + 1 < lay.im_start.size(); ++g) {
+  for (int x = 0; x < lay.tails(); ++x) {
+    const BatchTail& t = lay.tail[x];
+    // the interpolation's job order, groups and their prime counts
+    std::memcpy(h + t.list_im, t.im_order.data(), 4 * t.im_order.size());
+    std::memcpy(h + t.start_im, t.im_start.data(), 4 * t.im_start.size());
+    int64_t* pi = (int64_t*)(h + t.pref_interp);
+    pi[0] = 0;
+    for (size_t g = 0; g + 1 < t.im_start.size(); ++g) {
       int kmax = 0;
-      for (int t = lay.im_start[g]; t < lay.im_start[g + 1]; ++t) kmax = std::max(kmax, (int)lay.jobs[lay.im_order[t]].k);
-      pg2[g + 1] = pg2[g] + kmax;
+      for (int i = t.im_start[g]; i < t.im_start[g + 1]; ++i) kmax = std::max(kmax, (int)lay.jobs[t.im_order[i]].k);
+      pi[g + 1] = pi[g] + kmax;
+    }
+    // the remaindering's job lists and prefixes
+    int64_t* ps[NCRT_SMALL];
+    int32_t* ls[NCRT_SMALL];
+    int ns[NCRT_SMALL] = {0}, nb = 0, nm = 0;
+    for (int c = 0; c < NCRT_SMALL; ++c) {
+      ps[c] = (int64_t*)(h + t.pref_crts[c]);
+      ls[c] = (int32_t*)(h + t.list_crts[c]);
+      ps[c][0] = 0;
+    }
+    int32_t *lb = (int32_t*)(h + t.list_crtb), *lm = (int32_t*)(h + t.list_crtm);
+    int64_t *pd = (int64_t*)(h + t.pref_crtd), *pc = (int64_t*)(h + t.pref_crtc);
+    int64_t *pmg = (int64_t*)(h + t.pref_crtm_grp), *pmt = (int64_t*)(h + t.pref_crtm_tile);
+    pd[0] = pc[0] = pmg[0] = pmt[0] = 0;
+    for (int j = t.j0; j < t.j1; ++j) {
+      const int k = lay.jobs[j].k;
+      const int64_t n1 = (int64_t)lay.jobs[j].D + 1;
+      const int kind = crt_kind(lay, k);
+      if (kind >= 0) {
+        ls[kind][ns[kind]] = j;
+        ps[kind][ns[kind] + 1] = ps[kind][ns[kind]] + (n1 + 63) / 64;
+        ns[kind]++;
+      } else if (kind == CRT_M) {
+        lm[nm] = j;
+        pmg[nm + 1] = pmg[nm] + crt_mfma_groups((int)n1);
+        pmt[nm + 1] = pmt[nm] + crt_mfma_tiles((int)n1, k);
+        nm++;
+      } else {
+        lb[nb] = j;
+        pd[nb + 1] = pd[nb] + (n1 + CRT_COEF_PER_BLOCK - 1) / CRT_COEF_PER_BLOCK;
+        pc[nb + 1] = pc[nb] + (n1 + CRT_COMB_PER_BLOCK - 1) / CRT_COMB_PER_BLOCK;
+        nb++;
+      }
     }
   }
   // a class's jobs most expensive first: a persistent launch hands out the
@@ -565,18 +625,19 @@ static bool prepared_outputs(snc_prepared* pr, snc_upoly* out) {
   return true;
 }
 
-// the whole pipeline on `stream`, as a HIP graph captured on first use
-static int launch_prepared_all(snc_prepared* pr, hipStream_t stream, StageTimer& tm) {
-  const int part = PIPE_ALL;
+// the pipeline of one tail (-1: of all jobs) on `stream`, as a HIP graph
+// captured on first use
+static int launch_prepared(snc_prepared* pr, hipStream_t stream, StageTimer& tm, int tail) {
   snc_ctx* c = pr->c;
   // with timing on, the same launches go straight to the stream between
   // events (a replayed graph cannot be timed per stage)
   if (!pr->use_graph || tm.on) {
-    launch_pipeline(pr->lay, pr->ws, stream, tm.on ? &tm : nullptr, part);
+    launch_pipeline(pr->lay, pr->ws, stream, tm.on ? &tm : nullptr, PIPE_ALL, PipeFork(), tail);
     HIPCHK(hipGetLastError());
     return SNC_OK;
   }
-  hipGraphExec_t& gx = pr->gexec;
+  const int x = tail < 0 ? pr->lay.whole() : tail;
+  hipGraphExec_t& gx = pr->gexec[x];
   if (!gx) {
     if (!c->cap_stream) HIPCHK(hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
     if (!c->fork_stream) HIPCHK(hipStreamCreateWithFlags(&c->fork_stream, hipStreamNonBlocking));
@@ -588,7 +649,7 @@ static int launch_prepared_all(snc_prepared* pr, hipStream_t stream, StageTimer&
     fk.join = c->ev_join;
     hipGraph_t graph = nullptr;
     HIPCHK(hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
-    launch_pipeline(pr->lay, pr->ws, c->cap_stream, nullptr, part, fk);
+    launch_pipeline(pr->lay, pr->ws, c->cap_stream, nullptr, PIPE_ALL, fk, x);
     HIPCHK(hipStreamEndCapture(c->cap_stream, &graph));
     hipError_t e = hipGraphInstantiate(&gx, graph, nullptr, nullptr, 0);
     (void)hipGraphDestroy(graph);
@@ -630,11 +691,6 @@ static void prepared_collect(snc_prepared* pr, snc_upoly* out) {
   collect_jobs(pr, (const uint32_t*)pr->h_out, out, 0, (int)pr->lay.dev.size(), 0, 1);
 }
 
-// Download and collection of a large output block in chunks: the copy of
-// chunk c+1 runs while host threads widen chunk c into the caller's buffers.
-constexpr size_t COLLECT_CHUNKED_WORDS = (size_t)1 << 20;
-constexpr int COLLECT_CHUNKS = 8;
-
 // job ranges of about equal output words (the jobs' output regions are consecutive)
 static std::vector<int> chunk_bounds(const BatchLayout& lay) {
   const int NJ = (int)lay.dev.size();
@@ -643,17 +699,19 @@ static std::vector<int> chunk_bounds(const BatchLayout& lay) {
   size_t acc = 0;
   for (int j = 0; j < NJ; ++j) {
     acc += (size_t)(lay.jobs[j].D + 1) * lay.jobs[j].L;
-    if (acc >= per * bnd.size() && j + 1 < NJ && (int)bnd.size() < COLLECT_CHUNKS) bnd.push_back(j + 1);
+    const bool border = lay.ntails == 2 && j + 1 == lay.tail[1].j0;  // a chunk belongs to one tail
+    if ((acc >= per * bnd.size() || border) && j + 1 < NJ && ((int)bnd.size() < COLLECT_CHUNKS || border))
+      bnd.push_back(j + 1);
   }
   bnd.push_back(NJ);
   return bnd;
 }
 
 // downloads of the output block from src (device, laid out as the
-// workspace's output region) to dst (pinned host) in the chunks of bnd on
-// stream, one event recorded after each
+// workspace's output region) to dst (pinned host) in the chunks of bnd within
+// jobs j0 .. j1-1 on stream, one event recorded after each
 static int enqueue_chunks(const snc_prepared* pr, const std::vector<int>& bnd, const uint8_t* src, void* dst,
-                          std::vector<hipEvent_t>& ev, hipStream_t stream) {
+                          std::vector<hipEvent_t>& ev, hipStream_t stream, int j0, int j1) {
   snc_ctx* c = pr->c;
   const BatchLayout& lay = pr->lay;
   const int NJ = (int)lay.dev.size();
@@ -665,6 +723,7 @@ static int enqueue_chunks(const snc_prepared* pr, const std::vector<int>& bnd, c
   }
   const size_t base = lay.out_off / 4;
   for (int ch = 0; ch < nch; ++ch) {
+    if (bnd[ch] < j0 || bnd[ch] >= j1) continue;
     const size_t w0 = lay.jobs[bnd[ch]].out_off - base;
     const size_t w1 = bnd[ch + 1] < NJ ? lay.jobs[bnd[ch + 1]].out_off - base : lay.out_words;
     HIPCHK(hipMemcpyAsync((uint32_t*)dst + w0, src + w0 * 4, (w1 - w0) * 4, hipMemcpyDeviceToHost, stream));
@@ -705,10 +764,30 @@ static int widen_chunks(snc_prepared* pr, const std::vector<int>& bnd, const std
   return SNC_OK;
 }
 
-static int download_collect_chunked(snc_prepared* pr, hipStream_t stream, snc_upoly* out) {
-  const std::vector<int> bnd = chunk_bounds(pr->lay);
-  const int st = enqueue_chunks(pr, bnd, pr->ws + pr->lay.out_off, pr->h_out, pr->d2h_ev, stream);
-  if (st) return st;
+// A run with a large output: each tail's results are downloaded as soon as it
+// is done, the first tail's on the side stream beside the second's kernels
+// (512 pairs: 35 of the 50 MB travel beside the evaluation of the smaller
+// classes; 0.9 ms of download after the kernels before, 0.3 ms now).
+static int run_chunked(snc_prepared* pr, hipStream_t stream, snc_upoly* out) {
+  snc_ctx* c = pr->c;
+  const BatchLayout& lay = pr->lay;
+  const std::vector<int> bnd = chunk_bounds(lay);
+  StageTimer tm{c, stream, false};
+  for (int x = 0; x < lay.ntails; ++x) {
+    int st = launch_prepared(pr, stream, tm, x);
+    if (st) return st;
+    hipStream_t down = stream;
+    if (x + 1 < lay.ntails) {
+      if (!c->side_stream) HIPCHK(hipStreamCreateWithFlags(&c->side_stream, hipStreamNonBlocking));
+      // a copy follows: the event releases to the whole system
+      if (!c->ev_tail) HIPCHK(hipEventCreateWithFlags(&c->ev_tail, hipEventDisableTiming));
+      HIPCHK(hipEventRecord(c->ev_tail, stream));
+      HIPCHK(hipStreamWaitEvent(c->side_stream, c->ev_tail, 0));
+      down = c->side_stream;
+    }
+    st = enqueue_chunks(pr, bnd, pr->ws + lay.out_off, pr->h_out, pr->d2h_ev, down, lay.tail[x].j0, lay.tail[x].j1);
+    if (st) return st;
+  }
   return widen_chunks(pr, bnd, pr->d2h_ev, (const uint32_t*)pr->h_out, out);
 }
 
@@ -717,11 +796,11 @@ int run_prepared(snc_prepared* pr, hipStream_t stream, snc_upoly* out) {
   if (!prepared_outputs(pr, out)) return SNC_ERANGE;
   if (pr->lay.dev.empty()) return SNC_OK;
   HIPCHK(hipSetDevice(c->device));
+  if (!c->timing && pr->lay.out_words >= COLLECT_CHUNKED_WORDS) return run_chunked(pr, stream, out);
   StageTimer tm{c, stream, c->timing};
   tm.start();
-  int st = launch_prepared_all(pr, stream, tm);
+  int st = launch_prepared(pr, stream, tm, -1);
   if (st) return st;
-  if (!tm.on && pr->lay.out_words >= COLLECT_CHUNKED_WORDS) return download_collect_chunked(pr, stream, out);
   HIPCHK(hipMemcpyAsync(pr->h_out, pr->ws + pr->lay.out_off, pr->lay.out_words * 4, hipMemcpyDeviceToHost, stream));
   tm.mark("d2h", 1);
   HIPCHK(hipStreamSynchronize(stream));
@@ -758,7 +837,7 @@ int submit_prepared(snc_prepared* pr, void* d_stage, size_t stage_bytes, hipStre
   if (!pr->lay.dev.empty()) {
     uint8_t* slot = (uint8_t*)d_stage + (size_t)s * (need / 2);
     StageTimer tm{c, stream, false};
-    const int st = launch_prepared_all(pr, stream, tm);
+    const int st = launch_prepared(pr, stream, tm, -1);
     if (st) return st;
     // the output region goes to the slot on the device (a short copy on
     // this stream), and from there to the host on the side stream, so the
@@ -766,7 +845,8 @@ int submit_prepared(snc_prepared* pr, void* d_stage, size_t stage_bytes, hipStre
     HIPCHK(hipMemcpyAsync(slot, pr->ws + pr->lay.out_off, bytes, hipMemcpyDeviceToDevice, stream));
     HIPCHK(hipEventRecord(pr->slot_copied[s], stream));
     HIPCHK(hipStreamWaitEvent(c->side_stream, pr->slot_copied[s], 0));
-    const int st2 = enqueue_chunks(pr, chunk_bounds(pr->lay), slot, pr->slot_host[s], pr->slot_ev[s], c->side_stream);
+    const int st2 = enqueue_chunks(pr, chunk_bounds(pr->lay), slot, pr->slot_host[s], pr->slot_ev[s], c->side_stream,
+                                   0, (int)pr->lay.dev.size());
     if (st2) return st2;
   }
   pr->slot_ticket[s] = pr->next_ticket;
@@ -843,7 +923,8 @@ void destroy_prepared(snc_prepared* pr) {
     if (pr->slot_copied[s]) (void)hipEventDestroy(pr->slot_copied[s]);
     for (hipEvent_t e : pr->slot_ev[s]) (void)hipEventDestroy(e);
   }
-  if (pr->gexec) (void)hipGraphExecDestroy(pr->gexec);
+  for (hipGraphExec_t g : pr->gexec)
+    if (g) (void)hipGraphExecDestroy(g);
   if (pr->h_out && pr->own_out) (void)hipHostFree(pr->h_out);
   if (pr->h_ed) (void)hipHostFree(pr->h_ed);
   for (hipEvent_t e : pr->d2h_ev) (void)hipEventDestroy(e);

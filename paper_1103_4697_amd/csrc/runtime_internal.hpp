@@ -47,28 +47,48 @@ struct ResPlan {
 
 inline size_t align_words(size_t w) { return (w + 63) & ~(size_t)63; }  // 256-byte sections
 
+// Interpolation and Chinese remaindering of the jobs j0 .. j1-1 of a batch.
+// Offsets are bytes into the workspace, lists hold job indices, prefixes start
+// at zero.
+struct BatchTail {
+  int j0 = 0, j1 = 0;
+  uint32_t classes = 0;              // register classes evaluated before it (bit per class)
+  bool general = false;              // and the jobs above the register classes
+  // interpolation: jobs by degree bound, largest first, cut into groups that
+  // share a workgroup per prime; list, the groups' first entries and the
+  // prefix of their prime counts
+  std::vector<int32_t> im_order, im_start;
+  size_t list_im = 0, start_im = 0, pref_interp = 0, im_lds = 0;
+  int64_t nb_interp = 0;
+  // the small-prime classes (one lane per coefficient), the jobs on the
+  // lanes-over-primes pair (b) and those on the matrix cores (m)
+  size_t pref_crts[NCRT_SMALL] = {0}, list_crts[NCRT_SMALL] = {0};
+  int64_t nb_crts[NCRT_SMALL] = {0};
+  int n_crts_jobs[NCRT_SMALL] = {0};
+  size_t list_crtb = 0, pref_crtd = 0, pref_crtc = 0;
+  int64_t nb_crtd = 0, nb_crtc = 0;
+  int n_crtb_jobs = 0;
+  size_t list_crtm = 0, pref_crtm_grp = 0, pref_crtm_tile = 0;
+  int64_t nb_crtm_grp = 0, nb_crtm_tile = 0;
+  int n_crtm_jobs = 0, max_k_crtm = 0;
+};
+
+constexpr int TAIL_WHOLE = 2;
+
 struct BatchLayout {
   std::vector<int> dev;              // plan index of each device job
   std::vector<ResJob> jobs;          // device job descriptors (offsets filled)
   size_t jobs_off = 0, rows_off = 0, coef_off = 0;        // bytes
-  size_t pref_red = 0, pref_interp = 0, pref_crtd = 0, pref_crtc = 0, pref_gen = 0;  // bytes
-  // interpolation: jobs by degree bound, largest first, cut into groups that
-  // share a workgroup per prime; bytes of the list, the groups' first entries
-  // and the prefix of their prime counts (pref_interp)
-  std::vector<int32_t> im_order, im_start;
-  size_t list_im = 0, start_im = 0, im_lds = 0;
+  size_t pref_red = 0, pref_gen = 0;  // bytes
+  // one tail, or two for a large output (the class with the most output first,
+  // whose results travel while the other classes are computed) and the one of
+  // all jobs for the runs that do not download by themselves
+  int ntails = 1;
+  BatchTail tail[TAIL_WHOLE + 1];
+  int tails() const { return ntails == 2 ? TAIL_WHOLE + 1 : 1; }
+  int whole() const { return ntails == 2 ? TAIL_WHOLE : 0; }
   bool reduce_in_eval = false;       // the evaluation kernel reduces the inputs (no reduction launch)
   size_t pref_ee[NCLS] = {0}, list_ee[NCLS] = {0}, list_gen = 0;                   // bytes
-  // Chinese remaindering: the small-prime classes (one lane per coefficient)
-  // and the jobs with more primes (pref_crtd / pref_crtc over list_crtb)
-  size_t pref_crts[NCRT_SMALL] = {0}, list_crts[NCRT_SMALL] = {0}, list_crtb = 0;  // bytes
-  int64_t nb_crts[NCRT_SMALL] = {0};
-  int n_crts_jobs[NCRT_SMALL] = {0}, n_crtb_jobs = 0;
-  // those of them that take the matrix cores, listed behind the others: their
-  // list, coefficient groups and product tiles (bytes)
-  size_t list_crtm = 0, pref_crtm_grp = 0, pref_crtm_tile = 0;
-  int64_t nb_crtm_grp = 0, nb_crtm_tile = 0;
-  int n_crtm_jobs = 0, max_k_crtm = 0;
   bool crt_small_on = false;         // the few-prime jobs take k_crt_small (enough coefficients)
   EEVariant ee_var[NCLS];            // launch variant of each register class (autotuner, or the defaults)
   size_t ee_counter_off = 0;         // bytes: the NCLS work counters of persistent evaluation launches
@@ -76,7 +96,7 @@ struct BatchLayout {
   size_t out_off = 0, out_words = 0;                       // bytes / words
   size_t sq_off = 0, sq_words = 0;  // bytes / words: gcd(R, R') descriptors, work items, e and d
   size_t total_bytes = 0;
-  int64_t nb_red = 0, nb_interp = 0, nb_crtd = 0, nb_crtc = 0, n_gen_inst = 0;
+  int64_t nb_red = 0, n_gen_inst = 0;
   int64_t nb_ee[NCLS] = {0};
   int n_ee_jobs[NCLS] = {0}, n_gen_jobs = 0, n_rows = 0, max_D = 0, max_k = 0;
   int max_T_ee[NCLS] = {0};  // largest residue count per prime among a class's jobs
@@ -127,7 +147,7 @@ struct snc_ctx {
   std::vector<int64_t> gkey;
   // second stream (default priority) and event for work beside the pipeline
   hipStream_t side_stream = nullptr;
-  hipEvent_t ev_mid = nullptr;
+  hipEvent_t ev_mid = nullptr, ev_tail = nullptr;
   // branch of the captured pipeline (default priority): the small-prime CRT
   // class with the most primes runs beside the other classes
   hipStream_t fork_stream = nullptr;
@@ -152,7 +172,7 @@ struct snc_prepared {
   uint8_t* ws = nullptr;
   void* h_out = nullptr;             // pinned copy of the output block
   bool own_out = true;               // false: the context's staging buffer (a call that ends with its results)
-  hipGraphExec_t gexec = nullptr;    // whole pipeline
+  hipGraphExec_t gexec[snc::TAIL_WHOLE + 1] = {nullptr, nullptr, nullptr};  // the pipeline of each tail
   std::vector<hipEvent_t> d2h_ev;    // chunks of the result download (large batches)
   // projection step (resultant and gcd(R, R')): the Euclid descriptors are
   // uploaded into the workspace on the first run
@@ -185,8 +205,9 @@ struct PipeFork {
 // device launch sequence of a laid-out batch whose header is in ws (tm may be
 // null); with a branch (fk.stream set, tm null) the small-prime CRT class
 // with the most primes runs on the branch beside the other classes
+// tail: -1 all jobs, else that one with the evaluation before it
 void launch_pipeline(const BatchLayout& lay, uint8_t* ws, hipStream_t s, StageTimer* tm, int part,
-                     const PipeFork& fk = PipeFork());
+                     const PipeFork& fk = PipeFork(), int tail = -1);
 // launch variants of the evaluation kernel for a laid-out batch whose header is on the device:
 // forced variants, then (tune true) measured ones for the classes the cache lacks, else cached
 // choices or the defaults; fills lay.ee_var and the context's report
