@@ -47,8 +47,10 @@ def progress(msg):
 
 def eval_elim_lane_ops(m: int, n: int, T: int) -> int:
     """Essential VALU lane-ops of one (prime, point) instance of the fused
-    evaluate+eliminate kernel: Horner's rule in x^4 costs 6 per 4
-    coefficients (four 64-bit multiply-adds, low multiply, multiply-add);
+    evaluate+eliminate kernel: points come in pairs +-x on two lanes, each of
+    which evaluates the powers of one parity, so Horner's rule in z^4 (z = x^2)
+    costs 6 per 8 coefficients (four 64-bit multiply-adds, low multiply,
+    multiply-add) and each of the m + n + 2 rows 3 for the exchange;
     every normal remainder (the first one when deg A = deg B + 1, and all
     later ones) is one fused update of three products and one REDC, 5 per
     coefficient of the new remainder; a first remainder with another degree
@@ -57,7 +59,7 @@ def eval_elim_lane_ops(m: int, n: int, T: int) -> int:
     entries above them, which are only scaled by lc(B): one coefficient
     enters the updated part per step, scaled by the running power of lc(B)
     (3), and that power takes one more product (3)."""
-    ops = (3 * T) // 2
+    ops = (3 * T) // 4 + 3 * (m + n + 2)
     if m < n:
         m, n = n, m
     if n == 0:
@@ -90,11 +92,10 @@ def gcd_euclid_lane_ops(da: int, db: int) -> int:
 
 
 def interp_lane_ops(D: int) -> int:
-    """Essential lane-ops of the interpolation of one prime from D+1 values:
-    the Newton coefficients are a convolution of (D+1)^2/2 products and the
-    Newton-to-monomial expansion another (D+1)^2/2; each product is one
-    64-bit multiply-add, and every eight share a 3-op reduction."""
-    return (11 * (D + 1) * (D + 1)) // 8
+    """Modular products of the interpolation of one prime: two triangular
+    Toeplitz products for each of the two parities, (D+1)^2/2 in all (on the
+    matrix cores, sixteen byte products each)."""
+    return (D + 1) * (D + 1) // 2
 
 
 def crt_lane_ops(k: int, L: int) -> int:
@@ -149,15 +150,24 @@ def profiled_traffic(kernel: str, source, workload: str):
     return None
 
 
-def roof(kernel, ops, ms, traffic, ceilings, algo_bytes=None):
+PEAK_I8_TOPS = 5000.0  # dense int8 matrix cores
+
+
+def roof(kernel, ops, ms, traffic, ceilings, algo_bytes=None, mfma=False):
+    """Roofline record against the int32 vector units, or (mfma) of modular
+    products on the int8 matrix cores, sixteen byte products (two operations
+    each) per modular product."""
+    ops = 32 * ops if mfma else ops
+    peak = PEAK_I8_TOPS if mfma else PEAK_VALU_TOPS
     achieved = ops / (ms * 1e-3) / 1e12
-    r = {"kernel": kernel, "bound": "alu", "achieved": round(achieved, 4), "peak": round(PEAK_VALU_TOPS, 3),
-         "unit": "TOP/s (int32 VALU lane-ops)", "frac": round(achieved / PEAK_VALU_TOPS, 5), "traffic": traffic,
+    r = {"kernel": kernel, "bound": "mfma" if mfma else "alu", "achieved": round(achieved, 4), "peak": round(peak, 3),
+         "unit": "TOP/s (int8 matrix cores)" if mfma else "TOP/s (int32 VALU lane-ops)",
+         "frac": round(achieved / peak, 5), "traffic": traffic,
          "ops_per_launch": int(ops), "avg_launch_ms": round(ms, 5)}
     if algo_bytes is not None:
         r["algorithmic_bytes"] = int(algo_bytes)
         r["hbm_gbps"] = round(algo_bytes / (ms * 1e-3) / 1e9, 2)
-    if ceilings.get("mad_u64_per_s"):
+    if ceilings.get("mad_u64_per_s") and not mfma:
         r["frac_of_measured_mad_rate"] = round(ops / (ms * 1e-3) / ceilings["mad_u64_per_s"], 5)
     return r
 
@@ -291,7 +301,7 @@ def batch_stage_roofline(snc, pairs, plans, stages, ceilings, workload_tag):
         ip_ops += interp_lane_ops(D) * k
         crt_ops += crt_lane_ops(k, L) * (D + 1)
         ee_bytes += 4 * nl * T + 4 * k * T + 4 * k * (D + 1)      # limbs in, residues kept, values out
-        ip_bytes += 12 * k * (D + 1)                               # values, 1/t! table, coefficients
+        ip_bytes += 12 * k * (D + 1)                               # values, scaling tables, coefficients
         crd_bytes += 4 * k * (D + 1) + 2 * k * k                   # coefficients mod p in, constants P_j mod p_i
         crc_bytes += 4 * (D + 1) * L + 4 * k * L                    # output limbs, prefix products P_j
     ee_ms = sum(v for kk, v in stages.items() if kk.startswith("eval_elim"))
@@ -302,7 +312,8 @@ def batch_stage_roofline(snc, pairs, plans, stages, ceilings, workload_tag):
                           profiled_traffic("eval_elim", "paper_1103_4697_amd/csrc/eval_elim.hpp", workload_tag),
                           ceilings, ee_bytes),
         "interp": roof("interp", ip_ops, stages.get("interp", float("nan")),
-                       profiled_traffic("interp", src_res, workload_tag), ceilings, ip_bytes),
+                       profiled_traffic("interp", "paper_1103_4697_amd/csrc/interp_mfma.hip", workload_tag), ceilings,
+                       ip_bytes, mfma=True),
         "crt": roof("crt (all launches: digits and binary value)", crt_ops, crt_ms,
                     profiled_traffic("crt", src_res, workload_tag), ceilings, crd_bytes + crc_bytes),
     }

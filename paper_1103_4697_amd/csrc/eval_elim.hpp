@@ -144,7 +144,9 @@ __device__ __forceinline__ uint32_t horner_grouped(const uint32_t* r, const RowD
 // its powers times 1 or -x (five multiply-adds, below 8 p^2, reduced below
 // 3p); a length that is 4 mod 8 starts with two powers per parity.  Group
 // lengths are padded at the top with zeros, which keep an accumulator at
-// zero.
+// zero.  Bound by the issue of vector instructions: 512 pairs of degrees
+// 8..40, evaluation and elimination 2.86 -> 2.57 ms against every power on
+// every lane; one pair of degrees 64 and 48, 604 -> 515 us.
 struct alignas(16) HChunk {
   uint4 v[HCHUNK];
 };

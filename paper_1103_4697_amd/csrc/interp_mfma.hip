@@ -32,13 +32,13 @@
 // multiply-adds on the vector unit (one wavefront per (resultant, prime) at
 // 77% of its issue slots, or a workgroup with barriers per block), with the
 // expansion of each Newton block a further sixth.  512 pairs of degrees 8..40
-// (25,000 (resultant, prime) pairs, degree bounds up to 1,600): 1,100 -> 274
-// us, 0.9 P byte products/s, bound by the matrix cores and the LDS reads of
-// the operands about equally.  One pair of degree bound 3,072 with 262 primes:
-// 523 -> 79 us (three row tiles and a sixteenth: a third of the products are
-// on rows that end earlier).  Degree bound 225, 15 pairs, 2,052 primes: 248 ->
-// 116 us; degree bound 552, 35 primes: 13 (two launches) -> 11 us; degree
-// bound 36, 5 primes: 8.4 (two launches) -> 6.7 us, both latency.
+// (25,000 (resultant, prime) pairs, degree bounds up to 1,600): 1,100 -> 222
+// us (274 us with all coefficients in one sequence), bound by the matrix
+// cores and the LDS reads of the operands about equally, and by latency where
+// a job has few blocks.  One pair of degree bound 3,072 with 262 primes: 523
+// -> 53 us.  Degree bound 225, 15 pairs, 2,052 primes: 248 -> 96 us; degree
+// bound 552, 35 primes: 13 (two launches) -> 10.5 us; degree bound 36, 5
+// primes: 8.4 (two launches) -> 5.8 us, both latency.
 #include <hip/hip_runtime.h>
 
 #include "eval_elim.hpp"

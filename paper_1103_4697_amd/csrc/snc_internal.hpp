@@ -204,8 +204,8 @@ void launch_crt_digits(const CrtTables& tb, const ResJob* jobs_d, const int32_t*
                        int njobs, int64_t nblocks, uint32_t* ws, hipStream_t s);
 void launch_crt_combine(const CrtTables& tb, const ResJob* jobs_d, const int32_t* job_list_d, const int64_t* prefix_d,
                         int njobs, int64_t nblocks, int kmax, uint32_t* ws, hipStream_t s);
-// Chinese remaindering of a resultant with at most CRT_SMALL_K[cls] primes of
-// the modulus table: one lane per coefficient (digits and binary value in one
+// Chinese remaindering with at most CRT_SMALL_K[cls] primes of the modulus
+// table (resultants: up to 64, in large batches; images of the bivariate gcd): one lane per coefficient (digits and binary value in one
 // kernel); blocks of 64 coefficients, prefix over the launch's jobs
 constexpr int NCRT_SMALL = 3;
 constexpr int64_t CRT_SMALL_MIN_COEFS = 64 * 256;  // a wavefront per CU
