@@ -165,8 +165,8 @@ int snc_get_tuning(const snc_ctx* ctx, int32_t* info, float* ms, int cap, float*
  * output limbs L = ceil((log2 B + 2)/32), device workspace. */
 int snc_resultant_y_plan(const snc_bipoly* f, const snc_bipoly* g, snc_plan* out);
 
-/* One resultant: reduce mod k primes -> evaluate at D+1 points and eliminate
- * per (prime, point) -> interpolate per prime -> CRT per coefficient.  The
+/* One resultant: reduce mod k primes -> evaluate at D/2+1 pairs of points and
+ * eliminate per (prime, point) -> interpolate per prime -> CRT per coefficient.  The
  * result is exact (not probabilistic).  out: see snc_upoly. */
 int snc_resultant_y(snc_ctx* ctx, const snc_bipoly* f, const snc_bipoly* g, void* d_ws,
                     size_t ws_bytes, void* stream, snc_upoly* out);
