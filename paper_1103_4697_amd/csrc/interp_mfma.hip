@@ -426,14 +426,17 @@ __global__ __launch_bounds__(IM_THREADS) void k_interp_mfma(const PrimeC* primes
         put_u(j, i, ws[sPts[j] + 2 * i], ws[sPts[j] + 2 * i + 1]);
       }
     } else {
+      for (int x = tid; x < 2 * sPair[nj]; x += IM_THREADS) {
+        int j = 0;
+        while (x >= 2 * sPair[j + 1]) ++j;
+        const int i = x - 2 * sPair[j];
+        uint32_t* V = ws + sPts[j];
+        if (i < 2 * sN1[2 * j] && V[i] == ABN_MARK)
+          V[i] = general_instance<MAXY_FAST>(jobs + job_list[s0 + j], primes, rows, ws, g_points, pi, i);
+      }
+      __syncthreads();
       load_pairs(tid);
-      each_pair([&](int j, int i, uint32_t v0, uint32_t v1) {
-        if (v0 != ABN_MARK && v1 != ABN_MARK) return;
-        const ResJob* J = jobs + job_list[s0 + j];
-        if (v0 == ABN_MARK) v0 = general_instance<MAXY_FAST>(J, primes, rows, ws, g_points, pi, 2 * i);
-        if (v1 == ABN_MARK) v1 = general_instance<MAXY_FAST>(J, primes, rows, ws, g_points, pi, 2 * i + 1);
-        put_u(j, i, v0, v1);
-      });
+      each_pair([&](int j, int i, uint32_t v0, uint32_t v1) { put_u(j, i, v0, v1); });
     }
     __syncthreads();
   }
