@@ -121,14 +121,6 @@ __device__ __forceinline__ void reduce_limbs(uint32_t (&out)[NP], const uint32_t
 // point (formal degree not attained, or a remainder of lower degree) is
 // marked for the general elimination; the schedule stays uniform.
 // ---------------------------------------------------------------------------
-// one row q (0..3) of a row group
-__device__ __forceinline__ uint32_t horner_grouped(const uint32_t* r, const RowDesc& d, int q, uint32_t X,
-                                                   const PrimeC& c) {
-  uint32_t acc = 0;
-  for (int i = d.len - 1; i >= 0; --i) acc = mhorner(acc, X, r[d.off + grp_pos(i, d.len) + q], c.p, c.pinv);
-  return acc;
-}
-
 // The N+1 rows of one operand at the lane's point, four rows at a time from
 // the interleaved group layout (instruction-level parallelism for a lone
 // wavefront).  Lanes 2i and 2i+1 hold the points x and -x, and
@@ -157,6 +149,25 @@ struct XPow {
   uint32_t m0, m1, m2, m3, m4;  // 1, z, .., z^4 times 1 (even lane) or -x (odd lane)
   uint32_t flip, add;           // value = own + (other ^ flip) + add: own + 2p - other or own + other
 };
+
+// of point j (lanes 2i and 2i + 1 call with points 2i and 2i + 1 of a pair)
+__device__ __forceinline__ XPow pair_powers(const uint32_t* points, int pi, int j, const PrimeC& c) {
+  const int odd = j & 1;
+  XPow X;
+  const uint32_t xj = point_mont(points, pi, j, c);
+  X.z1 = mmulc(xj, xj, c.p, c.pinv);
+  X.z2 = mmulc(X.z1, X.z1, c.p, c.pinv);
+  X.z3 = mmulc(X.z2, X.z1, c.p, c.pinv);
+  X.z4 = mmulc(X.z2, X.z2, c.p, c.pinv);
+  X.m0 = odd ? xj : c.r1;
+  X.m1 = mmulc(X.z1, X.m0, c.p, c.pinv);
+  X.m2 = mmulc(X.z2, X.m0, c.p, c.pinv);
+  X.m3 = mmulc(X.z3, X.m0, c.p, c.pinv);
+  X.m4 = mmulc(X.z4, X.m0, c.p, c.pinv);
+  X.flip = odd ? 0u : ~0u;
+  X.add = odd ? 0u : 2 * c.p + 1;
+  return X;
+}
 
 __device__ __forceinline__ uint32_t hstep4(uint32_t acc, uint32_t v0, uint32_t v1, uint32_t v2, uint32_t v3,
                                            const XPow& xp, const PrimeC& c) {
@@ -502,19 +513,7 @@ __device__ __forceinline__ void eval_elim_block(int64_t b, const PrimeC* primes,
     }
     r = er;
   }
-  XPow X;
-  const uint32_t xj = point_mont(points, pi, j, c);
-  X.z1 = mmulc(xj, xj, c.p, c.pinv);
-  X.z2 = mmulc(X.z1, X.z1, c.p, c.pinv);
-  X.z3 = mmulc(X.z2, X.z1, c.p, c.pinv);
-  X.z4 = mmulc(X.z2, X.z2, c.p, c.pinv);
-  X.m0 = odd ? xj : c.r1;
-  X.m1 = mmulc(X.z1, X.m0, c.p, c.pinv);
-  X.m2 = mmulc(X.z2, X.m0, c.p, c.pinv);
-  X.m3 = mmulc(X.z3, X.m0, c.p, c.pinv);
-  X.m4 = mmulc(X.z4, X.m0, c.p, c.pinv);
-  X.flip = odd ? 0u : ~0u;
-  X.add = odd ? 0u : 2 * c.p + 1;
+  const XPow X = pair_powers(points, pi, j, c);
   // rows are padded to N+1 per operand (length 0 above the degree): no branches
   const RowDesc* ra = rows + J.rows_off;
   const RowDesc* rb = ra + J.rstride;  // J.rstride == N + 1 on this path

@@ -47,8 +47,16 @@ static __device__ uint32_t res_general(uint32_t* F, int m, uint32_t* G, int n, c
     while (r >= b) {
       const uint32_t q = mmulc(Ap[r], inv, c.p, c.pinv);
       if (q) {
-        for (int i = 0; i < b; ++i)
-          Ap[r - b + i] = msub(Ap[r - b + i], mmulc(q, Bp[i], c.p, c.pinv), c.p);
+        uint32_t* A = Ap + (r - b);
+        int i = 0;
+        for (; i + 8 <= b; i += 8) {  // the two arrays never overlap: all loads of a step are in flight together
+          uint32_t x[8], y[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) { x[u] = A[i + u]; y[u] = Bp[i + u]; }
+#pragma unroll
+          for (int u = 0; u < 8; ++u) A[i + u] = msub(x[u], mmulc(q, y[u], c.p, c.pinv), c.p);
+        }
+        for (; i < b; ++i) A[i] = msub(A[i], mmulc(q, Bp[i], c.p, c.pinv), c.p);
       }
       Ap[r] = 0;
       --r;
@@ -62,8 +70,63 @@ static __device__ uint32_t res_general(uint32_t* F, int m, uint32_t* G, int n, c
   }
 }
 
-// MAXY: the largest y-degree of the instances this variant runs (the size
-// of the per-lane value arrays)
+// z, z^2, z^3, z^4 = x, x^2, x^3, x^4: hstep4 on consecutive powers
+__device__ __forceinline__ XPow point_powers(uint32_t x, const PrimeC& c) {
+  XPow P;
+  P.z1 = x;
+  P.z2 = mmulc(x, x, c.p, c.pinv);
+  P.z3 = mmulc(P.z2, x, c.p, c.pinv);
+  P.z4 = mmulc(P.z2, P.z2, c.p, c.pinv);
+  return P;
+}
+
+// Row q of a group at the point (canonical): the eight coefficients of a pair
+// of chunks are requested together and take two steps of Horner's rule in x^4.
+__device__ __forceinline__ uint32_t eval_row(const uint32_t* g, int len, int q, const XPow& X, const PrimeC& c) {
+  uint32_t a = 0;
+  int k = len & ~7;
+  g += q;
+  if (len & HCHUNK) {
+    const uint32_t* v = g + 4 * k;  // x^k, x^(k+2), x^(k+1), x^(k+3)
+    a = hstep4(0u, v[0], v[8], v[4], v[12], X, c);
+  }
+#pragma unroll 2
+  for (k -= 8; k >= 0; k -= 8) {
+    const uint32_t* e = g + 4 * k;  // four even powers, then four odd ones
+    const uint32_t v0 = e[0], v2 = e[4], v4 = e[8], v6 = e[12], v1 = e[16], v3 = e[20], v5 = e[24], v7 = e[28];
+    a = hstep4(a, v4, v5, v6, v7, X, c);
+    a = hstep4(a, v0, v1, v2, v3, X, c);
+  }
+  return canon4(a, c.p);
+}
+
+// The deg + 1 rows of an operand at the lane's point, F[i] the coefficient of
+// y^i, by the pair of lanes of +-x as in the evaluation kernel.
+__device__ __forceinline__ void eval_operand(uint32_t* F, const uint32_t* r, const RowDesc* rd, int deg, int odd,
+                                             const XPow& X, const PrimeC& c) {
+  for (int t0 = 0; t0 <= deg; t0 += ROWGRP) {
+    const RowDesc d = rd[t0 / ROWGRP];
+    uint32_t a[4] = {0u, 0u, 0u, 0u};
+    if (d.len > 0) {
+      if (deg - t0 >= 2) eval_group<4>(a, r + d.off, d.len, odd, X, c);
+      else eval_group<2>(a, r + d.off, d.len, odd, X, c);
+    }
+#pragma unroll
+    for (int q = 0; q < ROWGRP; ++q)
+      if (t0 + q <= deg) F[deg - t0 - q] = canon4(a[q], c.p);
+  }
+}
+
+// One instance per lane; lanes 2i and 2i + 1 of a wavefront call together, for
+// points j = 2i and 2i + 1 of one prime (both or neither).  MAXY: the largest
+// y-degree of the instances this variant runs (the size of the per-lane value
+// arrays).  Bound by the issue of the 64-bit multiply-adds of a lone wavefront
+// per SIMD: a prime's abnormal instances share the workgroup that interpolates
+// it.  Whole calls, with the pair's evaluation and the loads of eight update
+// steps in flight, against one row after the other with a load and a dependent
+// step per coefficient: even in y of y-degree 4 and x-degree 700 (5,602 points
+// of 5 primes) 17.3 -> 1.8 ms, y- and x-degree 62 (3,700 points) 14.6 -> 5.0 ms;
+// y-degree 70, above the register classes, 1.06 -> 0.57 ms.
 template <int MAXY>
 __device__ __attribute__((noinline)) uint32_t general_instance(const ResJob* job, const PrimeC* primes,
                                                                const RowDesc* rows, const uint32_t* ws,
@@ -71,12 +134,12 @@ __device__ __attribute__((noinline)) uint32_t general_instance(const ResJob* job
   const ResJob& J = *job;
   const PrimeC c = primes[pi];
   const uint32_t* r = ws + J.res_off + (int64_t)pi * J.T;
-  const uint32_t X = point_mont(points, pi, j, c);
+  const XPow X = pair_powers(points, pi, j, c);
   const RowDesc* ra = rows + J.rows_off;
   const RowDesc* rb = ra + J.rstride;
   uint32_t F[MAXY + 1], G[MAXY + 1];
-  for (int t = 0; t <= J.m; ++t) F[J.m - t] = canon(horner_grouped(r, ra[t / ROWGRP], t % ROWGRP, X, c), c.p);
-  for (int t = 0; t <= J.n; ++t) G[J.n - t] = canon(horner_grouped(r, rb[t / ROWGRP], t % ROWGRP, X, c), c.p);
+  eval_operand(F, r, ra, J.m, j & 1, X, c);
+  eval_operand(G, r, rb, J.n, j & 1, X, c);
   uint32_t res = res_general(F, J.m, G, J.n, c);
   if (J.sign) res = mneg(res, c.p);
   return res;
@@ -94,8 +157,8 @@ __device__ __forceinline__ void wave_sync() {
 // elimination, which is division-free (an elementary step replaces A by
 // lc(B) A - lc(A) x^s B; its scale goes to one denominator, inverted at the
 // end).  F, G: MAXY_FAST + 1 words of LDS of the wavefront's own.  A lone
-// abnormal instance costs a lane about 220 us of serial loads and updates
-// (degree 40), a wavefront about a tenth.
+// abnormal instance of degree 40 takes a wavefront 60 us and a lane 250 us; of
+// degree 16, 25 and 88 us; of degree 4, 5 and 14 us.
 __device__ __attribute__((noinline)) uint32_t general_instance_wave(const ResJob* job, const PrimeC* primes,
                                                                     const RowDesc* rows, const uint32_t* ws,
                                                                     const uint32_t* points, int pi, int j,
@@ -103,13 +166,14 @@ __device__ __attribute__((noinline)) uint32_t general_instance_wave(const ResJob
   const int m = job->m, n = job->n;
   const PrimeC c = primes[pi];
   const uint32_t* r = ws + job->res_off + (int64_t)pi * job->T;
-  const uint32_t X = point_mont(points, pi, j, c);
+  const XPow X = point_powers(point_mont(points, pi, j, c), c);
   const RowDesc* ra = rows + job->rows_off;
   const RowDesc* rb = ra + job->rstride;
   for (int x = lane; x < m + n + 2; x += 64) {
     const bool first = x <= m;
     const int t = first ? x : x - m - 1;
-    const uint32_t v = canon(horner_grouped(r, (first ? ra : rb)[t / ROWGRP], t % ROWGRP, X, c), c.p);
+    const RowDesc d = (first ? ra : rb)[t / ROWGRP];
+    const uint32_t v = eval_row(r + d.off, d.len, t % ROWGRP, X, c);
     if (first) F[m - t] = v;
     else G[n - t] = v;
   }

@@ -115,7 +115,7 @@ constexpr int IM_THREADS = 256;
 constexpr int IM_WAVES = IM_THREADS / 64;
 constexpr int IM_MAXROWS = 192;
 constexpr int IM_LOADS = 4;   // pairs of values a thread has in flight
-constexpr int IM_MARKS = 32;  // abnormal instances of a workgroup that take a wavefront each
+constexpr int IM_MARKS = 16;  // abnormal instances of a workgroup that take a wavefront each
 static_assert(2 * (IM_DP / 64) <= IM_MAXROWS, "the rows of one job of the largest degree bound");
 constexpr int IM_SEQ = 2 * IM_JOBS;  // sequences of a group: the even and the odd coefficients of each job
 
@@ -376,7 +376,7 @@ __global__ __launch_bounds__(IM_THREADS) void k_interp_mfma(const PrimeC* primes
   __syncthreads();
   // u of both parities from the pairs of values.  Instances the evaluation
   // marked abnormal are computed here: a wavefront each while there are few (a
-  // lane alone takes up to ten times as long), else a lane each (a pair whose
+  // lane alone takes three to four times as long), else a lane each (a pair whose
   // remainders skip degrees at every point marks all of them).
   auto put_u = [&](int j, int i, uint32_t v0, uint32_t v1) {
     v0 = canon(v0, c.p);
@@ -411,7 +411,8 @@ __global__ __launch_bounds__(IM_THREADS) void k_interp_mfma(const PrimeC* primes
   });
   __syncthreads();
   if (__builtin_expect(nmark != 0, 0)) {
-    // small degrees: a lane needs two to three times a wavefront's time, not ten, so two rounds at most
+    // from y-degree 16 up to four rounds of wavefronts (degree 40, 16 marks: 315 us a call against 348 of a lane
+    // each; 32: 554 against 374), below two (degree 8, 8 marks: 71 against 88; 16: 107 against 88)
     const int most = jobs[job_list[s0 + (mark[0] >> 16)]].m >= 16 ? IM_MARKS : 2 * IM_WAVES;
     if (nmark <= most) {
       for (int x = wave; x < nmark; x += IM_WAVES) {
@@ -426,13 +427,18 @@ __global__ __launch_bounds__(IM_THREADS) void k_interp_mfma(const PrimeC* primes
         put_u(j, i, ws[sPts[j] + 2 * i], ws[sPts[j] + 2 * i + 1]);
       }
     } else {
+      // pairs of lanes take the pairs of points of which at least one is marked
       for (int x = tid; x < 2 * sPair[nj]; x += IM_THREADS) {
         int j = 0;
         while (x >= 2 * sPair[j + 1]) ++j;
         const int i = x - 2 * sPair[j];
         uint32_t* V = ws + sPts[j];
-        if (i < 2 * sN1[2 * j] && V[i] == ABN_MARK)
-          V[i] = general_instance<MAXY_FAST>(jobs + job_list[s0 + j], primes, rows, ws, g_points, pi, i);
+        if (i >= 2 * sN1[2 * j]) continue;
+        const uint32_t v = V[i];
+        if (v == ABN_MARK || V[i ^ 1] == ABN_MARK) {
+          const uint32_t w = general_instance<MAXY_FAST>(jobs + job_list[s0 + j], primes, rows, ws, g_points, pi, i);
+          if (v == ABN_MARK) V[i] = w;
+        }
       }
       __syncthreads();
       load_pairs(tid);
