@@ -110,6 +110,24 @@ def test_some_points(m, marks):
     assert snc.resultant_y(f, h) == want
 
 
+def test_marks_of_jobs_that_share_workgroups():
+    """Pairs with every, with some and without abnormal points, of y-degrees below and above 16, in groups."""
+    rnd = random.Random(77)
+    items = []
+    for i in range(8):
+        items.append(_power_pair(rnd, 2 + i % 3, 3 + i, 2, 500 + 11 * i))
+        items.append(_power_pair(rnd, 17 + i, 1, 1, 60))
+        items.append(_linear_divisor_pair(rnd, 20 if i % 2 else 3, _points(3 + 9 * i), 4))
+        items.append(_power_pair(rnd, 1, 30 + i, 25, 1500 + 37 * i))
+    pairs = [(f, h) for f, h, _ in items]
+    want = [w for _, _, w in items]
+    assert sum(snc.resultant_plan(f, h).nprimes for f, h in pairs) >= 2 * 1024  # jobs share workgroups from here
+    b = snc.ResultantBatch(pairs)
+    for _ in range(3):
+        b.run()
+        assert b.results() == want
+
+
 def _best(f, n=5):
     f()
     t = []
