@@ -413,7 +413,7 @@ __global__ __launch_bounds__(IM_THREADS) void k_interp_mfma(const PrimeC* primes
   if (__builtin_expect(nmark != 0, 0)) {
     // the group decides, not the first mark to arrive.  From y-degree 16 up to four rounds of wavefronts
     // (degree 40, 16 marks: 315 us a call against 348 of a lane each; 32: 554 against 374), below two (degree 8,
-    // 8 marks: 71 against 88; 16: 107 against 88)
+    // 8 marks: 71 against 88, a round of wavefronts 14)
     int mm = 0;
     for (int j = 0; j < nj; ++j) mm = max(mm, (int)jobs[job_list[s0 + j]].m);
     const int most = mm >= 16 ? IM_MARKS : 2 * IM_WAVES;

@@ -539,6 +539,16 @@ void fill_header(const BatchLayout& lay, const std::vector<ResPlan>& plans, cons
     }                                                                                 \
   } while (0)
 
+// Status of a call on `stream`.  A failed one may have copies and kernels in
+// flight on both streams: they end before its buffers can be reused or freed.
+static int end_run(snc_ctx* c, hipStream_t stream, int st) {
+  if (st != SNC_OK) {
+    (void)hipStreamSynchronize(stream);
+    if (c->side_stream) (void)hipStreamSynchronize(c->side_stream);
+  }
+  return st;
+}
+
 int prepare_resultants(snc_ctx* c, int n, const snc_bipoly* f, const snc_bipoly* g, void* d_ws,
                        size_t ws_bytes, hipStream_t stream, bool use_graph, bool one_shot, snc_prepared** outp) {
   *outp = nullptr;
@@ -588,12 +598,17 @@ int prepare_resultants(snc_ctx* c, int n, const snc_bipoly* f, const snc_bipoly*
     if (e == hipSuccess) {
       // launch variants of the evaluation kernel: measured for a batched graph, looked up otherwise
       const int st = choose_eval_variants(c, pr->lay, pr->ws, stream, use_graph);
-      if (st) { destroy_prepared(pr); return st; }
+      if (st) { end_run(c, stream, st); destroy_prepared(pr); return st; }
     }
     // a single call waits once, for its results; the staging buffer is not
     // written again before that
     if (e == hipSuccess && !one_shot) e = hipStreamSynchronize(stream);
-    if (e != hipSuccess) { c->err = std::string("input upload: ") + hipGetErrorString(e); destroy_prepared(pr); return SNC_EDEVICE; }
+    if (e != hipSuccess) {
+      c->err = std::string("input upload: ") + hipGetErrorString(e);
+      end_run(c, stream, SNC_EDEVICE);
+      destroy_prepared(pr);
+      return SNC_EDEVICE;
+    }
   }
   *outp = pr;
   return SNC_OK;
@@ -791,12 +806,8 @@ static int run_chunked(snc_prepared* pr, hipStream_t stream, snc_upoly* out) {
   return widen_chunks(pr, bnd, pr->d2h_ev, (const uint32_t*)pr->h_out, out);
 }
 
-int run_prepared(snc_prepared* pr, hipStream_t stream, snc_upoly* out) {
+static int run_whole(snc_prepared* pr, hipStream_t stream, snc_upoly* out) {
   snc_ctx* c = pr->c;
-  if (!prepared_outputs(pr, out)) return SNC_ERANGE;
-  if (pr->lay.dev.empty()) return SNC_OK;
-  HIPCHK(hipSetDevice(c->device));
-  if (!c->timing && pr->lay.out_words >= COLLECT_CHUNKED_WORDS) return run_chunked(pr, stream, out);
   StageTimer tm{c, stream, c->timing};
   tm.start();
   int st = launch_prepared(pr, stream, tm, -1);
@@ -809,8 +820,32 @@ int run_prepared(snc_prepared* pr, hipStream_t stream, snc_upoly* out) {
   return SNC_OK;
 }
 
+int run_prepared(snc_prepared* pr, hipStream_t stream, snc_upoly* out) {
+  snc_ctx* c = pr->c;
+  if (!prepared_outputs(pr, out)) return SNC_ERANGE;
+  if (pr->lay.dev.empty()) return SNC_OK;
+  HIPCHK(hipSetDevice(c->device));
+  const bool chunked = !c->timing && pr->lay.out_words >= COLLECT_CHUNKED_WORDS;
+  return end_run(c, stream, chunked ? run_chunked(pr, stream, out) : run_whole(pr, stream, out));
+}
+
 size_t prepared_stage_bytes(const snc_prepared* pr) {
   return pr->lay.dev.empty() ? 0 : 2 * align_words(pr->lay.out_words) * 4;
+}
+
+// one run, the copy of its output region to the slot on the device (short, on
+// this stream: the next run's kernels can start right after it) and from there
+// to the host on the side stream
+static int enqueue_run(snc_prepared* pr, uint8_t* slot, int s, hipStream_t stream) {
+  snc_ctx* c = pr->c;
+  StageTimer tm{c, stream, false};
+  const int st = launch_prepared(pr, stream, tm, -1);
+  if (st) return st;
+  HIPCHK(hipMemcpyAsync(slot, pr->ws + pr->lay.out_off, pr->lay.out_words * 4, hipMemcpyDeviceToDevice, stream));
+  HIPCHK(hipEventRecord(pr->slot_copied[s], stream));
+  HIPCHK(hipStreamWaitEvent(c->side_stream, pr->slot_copied[s], 0));
+  return enqueue_chunks(pr, chunk_bounds(pr->lay), slot, pr->slot_host[s], pr->slot_ev[s], c->side_stream, 0,
+                        (int)pr->lay.dev.size());
 }
 
 int submit_prepared(snc_prepared* pr, void* d_stage, size_t stage_bytes, hipStream_t stream, int64_t* ticket) {
@@ -835,19 +870,8 @@ int submit_prepared(snc_prepared* pr, void* d_stage, size_t stage_bytes, hipStre
   }
   if (!c->side_stream) HIPCHK(hipStreamCreateWithFlags(&c->side_stream, hipStreamNonBlocking));
   if (!pr->lay.dev.empty()) {
-    uint8_t* slot = (uint8_t*)d_stage + (size_t)s * (need / 2);
-    StageTimer tm{c, stream, false};
-    const int st = launch_prepared(pr, stream, tm, -1);
+    const int st = end_run(c, stream, enqueue_run(pr, (uint8_t*)d_stage + (size_t)s * (need / 2), s, stream));
     if (st) return st;
-    // the output region goes to the slot on the device (a short copy on
-    // this stream), and from there to the host on the side stream, so the
-    // next run's kernels can start right after this copy
-    HIPCHK(hipMemcpyAsync(slot, pr->ws + pr->lay.out_off, bytes, hipMemcpyDeviceToDevice, stream));
-    HIPCHK(hipEventRecord(pr->slot_copied[s], stream));
-    HIPCHK(hipStreamWaitEvent(c->side_stream, pr->slot_copied[s], 0));
-    const int st2 = enqueue_chunks(pr, chunk_bounds(pr->lay), slot, pr->slot_host[s], pr->slot_ev[s], c->side_stream,
-                                   0, (int)pr->lay.dev.size());
-    if (st2) return st2;
   }
   pr->slot_ticket[s] = pr->next_ticket;
   *ticket = pr->next_ticket++;
@@ -871,12 +895,9 @@ int collect_prepared(snc_prepared* pr, int64_t ticket, snc_upoly* out) {
   return st;
 }
 
-int run_prepared_fork(snc_prepared* pr, hipStream_t stream, const std::function<int(hipStream_t)>& branch,
-                      const std::function<void()>& on_results, snc_upoly* out) {
+static int run_fork(snc_prepared* pr, hipStream_t stream, const std::function<int(hipStream_t)>& branch,
+                    const std::function<void()>& on_results, snc_upoly* out) {
   snc_ctx* c = pr->c;
-  if (!prepared_outputs(pr, out)) return SNC_ERANGE;
-  if (pr->lay.dev.empty()) { on_results(); return SNC_OK; }
-  HIPCHK(hipSetDevice(c->device));
   if (!c->side_stream) HIPCHK(hipStreamCreateWithFlags(&c->side_stream, hipStreamNonBlocking));
   // the side stream runs on this device only: a device-scope release suffices
   if (!c->ev_mid) HIPCHK(hipEventCreateWithFlags(&c->ev_mid, hipEventDisableTiming | hipEventReleaseToDevice));
@@ -902,15 +923,22 @@ int run_prepared_fork(snc_prepared* pr, hipStream_t stream, const std::function<
   return SNC_OK;
 }
 
+int run_prepared_fork(snc_prepared* pr, hipStream_t stream, const std::function<int(hipStream_t)>& branch,
+                      const std::function<void()>& on_results, snc_upoly* out) {
+  if (!prepared_outputs(pr, out)) return SNC_ERANGE;
+  if (pr->lay.dev.empty()) { on_results(); return SNC_OK; }
+  snc_ctx* c = pr->c;
+  HIPCHK(hipSetDevice(c->device));
+  return end_run(c, stream, run_fork(pr, stream, branch, on_results, out));
+}
+
 int run_resultants(snc_ctx* c, int n, const snc_bipoly* f, const snc_bipoly* g, void* d_ws,
                    size_t ws_bytes, hipStream_t stream, snc_upoly* out, bool use_graph) {
   snc_prepared* pr = nullptr;
   int st = prepare_resultants(c, n, f, g, d_ws, ws_bytes, stream, use_graph, true, &pr);
-  if (st == SNC_OK) {
-    st = run_prepared(pr, stream, out);
-    destroy_prepared(pr);
-  }
-  if (st) (void)hipStreamSynchronize(stream);  // nothing in flight reads the staging buffers of a failed call
+  if (st) return st;
+  st = end_run(c, stream, run_prepared(pr, stream, out));  // an output refused after the upload waits for it too
+  destroy_prepared(pr);
   return st;
 }
 

@@ -1,0 +1,136 @@
+"""The library's host code against a HIP runtime without a device
+(stub_hip.cpp): what is launched, copied, waited for and kept, also after a
+call of the runtime fails.  Each scenario runs in a process of its own, with
+the stub loaded before the library.
+"""
+import ctypes as C
+import os
+import random
+import subprocess
+import sys
+import types
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+USER = "0x77000"  # the caller's stream
+
+
+class Host:
+    """The library on the stub, with one context."""
+
+    def __init__(self, stub):
+        sys.path.insert(0, os.path.dirname(HERE))
+        self.stub = C.CDLL(stub, mode=C.RTLD_GLOBAL)
+        self.stub.stub_log.restype = C.c_char_p
+        sys.modules["torch"] = types.ModuleType("torch")  # the binding only has it load the real runtime
+        import paper_1103_4697_amd as snc
+        self.snc, self.L = snc, snc.lib()
+        self.ctx = C.c_void_p()
+        assert self.L.snc_create(0, C.byref(self.ctx)) == 0
+        self.stub.stub_clear()
+        self.ws = C.c_void_p(0x10000000)  # never read on the host
+        self.stream = C.c_void_p(int(USER, 16))
+
+    def log(self):
+        return self.stub.stub_log().decode().splitlines()
+
+    def fail(self, name, nth):
+        self.stub.stub_fail(name.encode(), nth)
+
+    def pairs(self, ps):
+        """Operand arrays, output array and plans of a batch."""
+        snc, n, keep = self.snc, len(ps), []
+        F = (snc.Bipoly * n)(*[snc._as_bipoly(f, keep) for f, g in ps])
+        G = (snc.Bipoly * n)(*[snc._as_bipoly(g, keep) for f, g in ps])
+        plans, total = (snc.Plan * n)(), snc.Plan()
+        assert self.L.snc_resultant_y_batch_plan(n, F, G, plans, C.byref(total)) == 0
+        outs = (snc.Upoly * n)(*[snc._out_upoly(p.deg_bound, p.out_nlimbs, keep)[0] for p in plans])
+        self.keep = keep
+        return F, G, outs, plans, total
+
+    def batch(self, ps):
+        F, G, outs, _, total = self.pairs(ps)
+        return self.L.snc_resultant_y_batch(self.ctx, len(ps), F, G, self.ws, C.c_size_t(total.workspace_bytes),
+                                            self.stream, outs)
+
+    def prepare(self, ps):
+        F, G, outs, _, total = self.pairs(ps)
+        h = C.c_void_p()
+        assert self.L.snc_resultant_y_prepare(self.ctx, len(ps), F, G, self.ws, C.c_size_t(total.workspace_bytes),
+                                              self.stream, C.byref(h)) == 0
+        return h, outs
+
+
+def dense(rnd, m, dx, bits):
+    return [[rnd.randrange(1, 1 << bits) for _ in range(dx + 1)] for _ in range(m + 1)]
+
+
+def two_class_batch():
+    """More than 2^20 output words, of y-degree 1, and enough evaluation in another register class: two tails."""
+    rnd = random.Random(3)
+    return ([(dense(rnd, 1, 900, 1500), dense(rnd, 1, 900, 1500)) for _ in range(7)] +
+            [(dense(rnd, 20, 20, 60), dense(rnd, 19, 20, 60)) for _ in range(9)])
+
+
+# ---------------------------------------------------------------------------
+# Scenarios: print the log of the calls under test
+# ---------------------------------------------------------------------------
+def failed_second_tail_single_call(H):
+    H.fail("graph_launch", 2)
+    assert H.batch(two_class_batch()) == H.snc.SNC_EDEVICE
+    return H.log()
+
+
+def failed_second_tail_handle(H):
+    h, outs = H.prepare(two_class_batch())
+    H.stub.stub_clear()
+    H.fail("graph_launch", 2)
+    assert H.L.snc_prepared_run(h, H.stream, outs) == H.snc.SNC_EDEVICE
+    return H.log()
+
+
+def failed_submit(H):
+    h, outs = H.prepare(two_class_batch())
+    need = H.L.snc_prepared_stage_bytes(h)
+    H.stub.stub_clear()
+    H.fail("event_record", 3)  # the slot's copy, the first chunk, the second
+    t = C.c_int64()
+    assert H.L.snc_prepared_submit(h, C.c_void_p(0x20000000), C.c_size_t(need), H.stream,
+                                   C.byref(t)) == H.snc.SNC_EDEVICE
+    return H.log()
+
+
+# ---------------------------------------------------------------------------
+@pytest.fixture(scope="session")
+def stub(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("stub") / "libstub_hip.so")
+    subprocess.run(["g++", "-shared", "-fPIC", "-O1", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include",
+                    os.path.join(HERE, "stub_hip.cpp"), "-o", so], check=True)
+    return so
+
+
+def run(stub, scenario):
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), stub, scenario], capture_output=True, text=True,
+                       timeout=300)
+    assert r.returncode == 0, r.stderr[-2000:]
+    return [line.split() for line in r.stdout.splitlines()]
+
+
+@pytest.mark.parametrize("scenario", ["failed_second_tail_single_call", "failed_second_tail_handle", "failed_submit"])
+def test_failed_call_leaves_no_copy_in_flight(stub, scenario):
+    log = run(stub, scenario)
+    downs = [i for i, e in enumerate(log) if e[0] == "download"]
+    side = log[downs[-1]][3]
+    assert side != USER and all(log[i][3] == side for i in downs)
+    for stream in (side, USER):
+        waits = [i for i, e in enumerate(log) if e[:2] == ["stream_sync", stream] and i > downs[-1]]
+        assert waits, f"nothing waits for {stream}"
+        freed = [i for i, e in enumerate(log) if e[0] in ("host_free", "graph_destroy") and i > downs[-1]]
+        assert not freed or waits[0] < freed[0]
+
+
+if __name__ == "__main__":
+    print("\n".join(globals()[sys.argv[2]](Host(sys.argv[1]))))
+    sys.stdout.flush()
+    os._exit(0)  # no device to tear down
