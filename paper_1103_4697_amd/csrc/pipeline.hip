@@ -132,11 +132,13 @@ void layout_batch(const std::vector<ResPlan>& plans, BatchLayout& lay) {
   lay.n_rows = nrows;
   lay.rows_off = off; off = align256(off + sizeof(RowDesc) * nrows);
   lay.pref_red = off; off = align256(off + 8 * (NJ + 1));
-  // one lane per coefficient pays off only when the batch's few-prime coefficients fill the device
-  // (a wavefront per CU); otherwise the lanes go over the primes of each coefficient
+  // One lane per coefficient pays off from a wavefront for every fourth CU of the coefficients that would take
+  // it; below, the lanes go over the primes of each coefficient.  Whole runs, lanes over primes / one lane: 4,200
+  // coefficients of 4, 32 and 60 primes 77 / 74, 144 / 129 and 219 / 202 us, 14,000 of them 119 / 84, 302 / 226
+  // and 460 / 332; 2,940 of up to 64 primes beside larger jobs 395 / 395.
   int64_t small_coefs = 0;
   for (int j = 0; j < NJ; ++j)
-    if (crt_small_class(plans[lay.dev[j]].k) >= 0) small_coefs += plans[lay.dev[j]].D + 1;
+    if (plans[lay.dev[j]].k < CRT_MFMA_MIN) small_coefs += plans[lay.dev[j]].D + 1;
   lay.crt_small_on = small_coefs >= CRT_SMALL_MIN_COEFS;
   for (int x = 0; x < lay.tails(); ++x) {
     BatchTail& t = lay.tail[x];
@@ -166,7 +168,7 @@ void layout_batch(const std::vector<ResPlan>& plans, BatchLayout& lay) {
     t.pref_crtd = off; t.pref_crtm_grp = off + 8 * (t.n_crtb_jobs + 1); off = align256(off + 8 * (nbm + 2));
     t.pref_crtc = off; t.pref_crtm_tile = off + 8 * (t.n_crtb_jobs + 1); off = align256(off + 8 * (nbm + 2));
     t.list_crtb = off; t.list_crtm = off + 4 * t.n_crtb_jobs; off = align256(off + 4 * std::max<size_t>(nbm, 1));
-    for (int c = 0; c < NCRT_SMALL; ++c) {
+    for (int c = 0; c < NCRT_RES; ++c) {
       t.pref_crts[c] = off; off = align256(off + 8 * (t.n_crts_jobs[c] + 1));
       t.list_crts[c] = off; off = align256(off + 4 * std::max(t.n_crts_jobs[c], 1));
     }
@@ -350,12 +352,12 @@ void launch_pipeline(const BatchLayout& lay, uint8_t* ws, hipStream_t s, StageTi
     if (tm) tm->mark("interp", 1);
   }
   if (part == PIPE_TO_INTERP) return;
-  static const char* const kCrtStage[NCRT_SMALL] = {"crt_small_32", "crt_small_64", "crt_small_128"};
+  static const char* const kCrtStage[NCRT_RES] = {"crt_small_32", "crt_small_64"};
   // The jobs on the matrix cores (or, without any, the small-prime class with
   // the most primes: few, long workgroups bound by their own latency) run on a
-  // branch beside the other classes instead of after them.
+  // branch beside the other jobs instead of after them.
   int nsmall = 0, top = -1;
-  for (int c = 0; c < NCRT_SMALL; ++c)
+  for (int c = 0; c < NCRT_RES; ++c)
     if (t.n_crts_jobs[c]) { ++nsmall; top = c; }
   const CrtTables tb = global_crt_tables();
   auto small = [&](int c, hipStream_t st) {
@@ -373,21 +375,18 @@ void launch_pipeline(const BatchLayout& lay, uint8_t* ws, hipStream_t s, StageTi
     launch_crt_mfma_carry(tb, jobs, lm, pg, t.n_crtm_jobs, t.nb_crtm_grp, t.max_k_crtm, wsw, st);
     if (tm) tm->mark("crt_mfma_carry", 1);
   };
-  const bool branch = fk.stream && !tm && (t.n_crtm_jobs ? nsmall >= 1 : nsmall >= 2);
+  const bool beside = t.n_crtm_jobs ? nsmall >= 1 || t.n_crtb_jobs : nsmall >= 2;
+  const bool branch = fk.stream && !tm && beside;
   if (branch) {
     (void)hipEventRecord(fk.fork, s);
     (void)hipStreamWaitEvent(fk.stream, fk.fork, 0);
     if (t.n_crtm_jobs) mfma(fk.stream);
     else small(top, fk.stream);
   }
-  for (int c = 0; c < NCRT_SMALL; ++c) {
+  for (int c = 0; c < NCRT_RES; ++c) {
     if (!t.n_crts_jobs[c] || (branch && !t.n_crtm_jobs && c == top)) continue;
     small(c, s);
     if (tm) tm->mark(kCrtStage[c], 1);
-  }
-  if (branch) {
-    (void)hipEventRecord(fk.join, fk.stream);
-    (void)hipStreamWaitEvent(s, fk.join, 0);
   }
   if (t.n_crtb_jobs) {
     const int32_t* lb = (const int32_t*)(ws + t.list_crtb);
@@ -396,6 +395,10 @@ void launch_pipeline(const BatchLayout& lay, uint8_t* ws, hipStream_t s, StageTi
     launch_crt_combine(tb, jobs, lb, (const int64_t*)(ws + t.pref_crtc), t.n_crtb_jobs, t.nb_crtc,
                        (int)std::min<int64_t>(lay.max_k, CRT_MFMA_MIN - 1), wsw, s);
     if (tm) tm->mark("crt_combine", 1);
+  }
+  if (branch) {
+    (void)hipEventRecord(fk.join, fk.stream);
+    (void)hipStreamWaitEvent(s, fk.join, 0);
   }
   if (t.n_crtm_jobs && !branch) mfma(s);
 }
@@ -482,10 +485,10 @@ void fill_header(const BatchLayout& lay, const std::vector<ResPlan>& plans, cons
       pi[g + 1] = pi[g] + kmax;
     }
     // the remaindering's job lists and prefixes
-    int64_t* ps[NCRT_SMALL];
-    int32_t* ls[NCRT_SMALL];
-    int ns[NCRT_SMALL] = {0}, nb = 0, nm = 0;
-    for (int c = 0; c < NCRT_SMALL; ++c) {
+    int64_t* ps[NCRT_RES];
+    int32_t* ls[NCRT_RES];
+    int ns[NCRT_RES] = {0}, nb = 0, nm = 0;
+    for (int c = 0; c < NCRT_RES; ++c) {
       ps[c] = (int64_t*)(h + t.pref_crts[c]);
       ls[c] = (int32_t*)(h + t.list_crts[c]);
       ps[c][0] = 0;

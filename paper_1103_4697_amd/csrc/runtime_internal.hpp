@@ -62,9 +62,9 @@ struct BatchTail {
   int64_t nb_interp = 0;
   // the small-prime classes (one lane per coefficient), the jobs on the
   // lanes-over-primes pair (b) and those on the matrix cores (m)
-  size_t pref_crts[NCRT_SMALL] = {0}, list_crts[NCRT_SMALL] = {0};
-  int64_t nb_crts[NCRT_SMALL] = {0};
-  int n_crts_jobs[NCRT_SMALL] = {0};
+  size_t pref_crts[NCRT_RES] = {0}, list_crts[NCRT_RES] = {0};
+  int64_t nb_crts[NCRT_RES] = {0};
+  int n_crts_jobs[NCRT_RES] = {0};
   size_t list_crtb = 0, pref_crtd = 0, pref_crtc = 0;
   int64_t nb_crtd = 0, nb_crtc = 0;
   int n_crtb_jobs = 0;

@@ -205,10 +205,12 @@ void launch_crt_digits(const CrtTables& tb, const ResJob* jobs_d, const int32_t*
 void launch_crt_combine(const CrtTables& tb, const ResJob* jobs_d, const int32_t* job_list_d, const int64_t* prefix_d,
                         int njobs, int64_t nblocks, int kmax, uint32_t* ws, hipStream_t s);
 // Chinese remaindering with at most CRT_SMALL_K[cls] primes of the modulus
-// table (resultants: up to 64, in large batches; images of the bivariate gcd): one lane per coefficient (digits and binary value in one
-// kernel); blocks of 64 coefficients, prefix over the launch's jobs
-constexpr int NCRT_SMALL = 3;
-constexpr int64_t CRT_SMALL_MIN_COEFS = 64 * 256;  // a wavefront per CU
+// table (images of the bivariate gcd; of resultants the first NCRT_RES
+// classes, up to 64 primes, in large batches): one lane per coefficient
+// (digits and binary value in one kernel); blocks of 64 coefficients, prefix
+// over the launch's jobs
+constexpr int NCRT_SMALL = 3, NCRT_RES = 2;
+constexpr int64_t CRT_SMALL_MIN_COEFS = 64 * 64;  // a wavefront for every fourth CU
 constexpr int CRT_SMALL_K[NCRT_SMALL] = {32, 64, 128};
 inline int crt_small_class(int k) {
   for (int c = 0; c < NCRT_SMALL; ++c)
@@ -223,6 +225,7 @@ void launch_crt_small_init(hipStream_t s);  // transposed table of P_j mod p_i (
 // crt_mfma_groups over the launch's jobs), limb sums over tiles (prefix of
 // crt_mfma_tiles); the limb sums use the points and Newton-block regions
 constexpr int CRT_MFMA_MIN = 65;
+static_assert(CRT_SMALL_K[NCRT_RES - 1] == CRT_MFMA_MIN - 1, "the classes of the resultants end where the matrix cores begin");
 int64_t crt_mfma_groups(int n1);
 int64_t crt_mfma_tiles(int n1, int k);
 hipError_t configure_crt_mfma();

@@ -61,6 +61,11 @@ class Host:
                                               self.stream, C.byref(h)) == 0
         return h, outs
 
+    def prepare_run(self, ps):
+        h, outs = self.prepare(ps)
+        self.stub.stub_clear()
+        assert self.L.snc_prepared_run(h, self.stream, outs) == 0
+
 
 def dense(rnd, m, dx, bits):
     return [[rnd.randrange(1, 1 << bits) for _ in range(dx + 1)] for _ in range(m + 1)]
@@ -101,6 +106,28 @@ def failed_submit(H):
     return H.log()
 
 
+def remaindering_kernels(H, ps):
+    H.prepare_run(ps)
+    return [line for line in H.log() if "k_crt" in line]
+
+
+def few_small_beside_many_large(H):
+    """Twenty thousand coefficients of 65..128 primes and ninety of four: the four-prime ones do not fill the chip."""
+    rnd = random.Random(4)
+    ps = [(dense(rnd, 1, 100, 1200), dense(rnd, 1, 100, 1200)) for _ in range(100)]
+    ps += [(dense(rnd, 1, 15, 40), dense(rnd, 1, 15, 40)) for _ in range(3)]
+    plans = H.pairs(ps)[3]
+    assert {(p.nprimes > 64) for p in plans} == {True, False} and max(p.nprimes for p in plans) <= 128
+    return remaindering_kernels(H, ps)
+
+
+def many_small_beside_few_large(H):
+    rnd = random.Random(5)
+    ps = [(dense(rnd, 1, 100, 40), dense(rnd, 1, 100, 40)) for _ in range(90)]
+    ps += [(dense(rnd, 1, 10, 1200), dense(rnd, 1, 10, 1200))]
+    return remaindering_kernels(H, ps)
+
+
 # ---------------------------------------------------------------------------
 @pytest.fixture(scope="session")
 def stub(tmp_path_factory):
@@ -128,6 +155,15 @@ def test_failed_call_leaves_no_copy_in_flight(stub, scenario):
         assert waits, f"nothing waits for {stream}"
         freed = [i for i, e in enumerate(log) if e[0] in ("host_free", "graph_destroy") and i > downs[-1]]
         assert not freed or waits[0] < freed[0]
+
+
+def test_one_lane_remaindering_counts_its_own_coefficients(stub):
+    few = [e[1] for e in run(stub, "few_small_beside_many_large")]
+    assert sum("k_crt_digits" in k for k in few) == 1 and sum("k_crtm_digits" in k for k in few) == 1
+    assert not any("k_crt_small" in k for k in few)
+    many = [e[1] for e in run(stub, "many_small_beside_few_large")]
+    assert sum("k_crt_small" in k for k in many) == 1 and sum("k_crtm_digits" in k for k in many) == 1
+    assert not any("k_crt_digits" in k for k in many)
 
 
 if __name__ == "__main__":
