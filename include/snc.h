@@ -31,6 +31,10 @@
  * whose size the matching *_plan call reports, and a HIP stream (passed as
  * void*, a hipStream_t; NULL = the default stream).  The library never
  * allocates device memory.  A call returns after its result is on the host.
+ * A context keeps pinned host memory for its calls until it is destroyed: a
+ * block for the inputs, at least as large as the largest call's, and one for
+ * the results, of resultant calls at most 64 MiB (a call with a larger result
+ * allocates and frees its own).
  *
  * Errors.  Every function returns an snc_status; nothing aborts or prints.
  * snc_last_error() gives a message for the last failure on a context.

@@ -28,7 +28,7 @@ int snc_ctx::stage_out(size_t bytes) {
   if (bytes <= h_out_bytes) return SNC_OK;
   if (h_out) (void)hipHostFree(h_out);
   h_out = nullptr;
-  size_t nb = std::max(bytes, h_out_bytes * 2);
+  size_t nb = std::max(bytes, std::min(h_out_bytes * 2, STAGE_KEEP));
   if (hipHostMalloc(&h_out, nb, hipHostMallocDefault) != hipSuccess) { h_out_bytes = 0; h_out = nullptr; return SNC_EDEVICE; }
   h_out_bytes = nb;
   return SNC_OK;
@@ -579,10 +579,11 @@ int prepare_resultants(snc_ctx* c, int n, const snc_bipoly* f, const snc_bipoly*
     pr->ws = (uint8_t*)d_ws;
     if (c->stage_in(lay.header_bytes)) { c->err = "pinned staging allocation failed"; delete pr; return SNC_EDEVICE; }
     // a handle keeps a pinned block of its own; a single call takes the
-    // context's (pinning and unpinning a block cost 200-400 us a call)
-    pr->own_out = !one_shot;
+    // context's (pinning and unpinning a block cost 200-400 us a call) up to
+    // the size a context keeps
+    pr->own_out = !one_shot || lay.out_words * 4 > snc_ctx::STAGE_KEEP;
     bool pinned;
-    if (one_shot) {
+    if (!pr->own_out) {
       pinned = c->stage_out(lay.out_words * 4) == SNC_OK;
       pr->h_out = c->h_out;
     } else {

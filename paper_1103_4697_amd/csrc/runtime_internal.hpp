@@ -136,7 +136,9 @@ struct snc_ctx {
   std::vector<float> stage_ms;
   std::vector<int> stage_launches;
   std::vector<hipEvent_t> events;
-  // pinned host staging
+  // pinned host staging; of outputs a context keeps up to STAGE_KEEP bytes
+  // between calls (the headline batch's 50 MB among them)
+  static constexpr size_t STAGE_KEEP = (size_t)64 << 20;
   void* h_in = nullptr;
   size_t h_in_bytes = 0;
   void* h_out = nullptr;
@@ -171,7 +173,7 @@ struct snc_prepared {
   snc::BatchLayout lay;
   uint8_t* ws = nullptr;
   void* h_out = nullptr;             // pinned copy of the output block
-  bool own_out = true;               // false: the context's staging buffer (a call that ends with its results)
+  bool own_out = true;               // false: the context's staging buffer (a single call, up to STAGE_KEEP)
   hipGraphExec_t gexec[snc::TAIL_WHOLE + 1] = {nullptr, nullptr, nullptr};  // the pipeline of each tail
   std::vector<hipEvent_t> d2h_ev;    // chunks of the result download (large batches)
   // projection step (resultant and gcd(R, R')): the Euclid descriptors are

@@ -128,6 +128,25 @@ def many_small_beside_few_large(H):
     return remaindering_kernels(H, ps)
 
 
+def pinned_blocks_of_single_calls(H):
+    """Single calls with a small output, then 40, 48 and 80 MiB, then small again; the blocks held after each."""
+    rnd = random.Random(6)
+    big = [(dense(rnd, 40, 30, 80), dense(rnd, 40, 30, 80)) for _ in range(42)]
+    out, held = [], {}
+    for n in (0, 21, 25, 42, 0):
+        ps = big[:n] or [(dense(rnd, 1, 3, 30), dense(rnd, 1, 3, 30))]
+        H.stub.stub_clear()
+        assert H.batch(ps) == 0
+        words = sum((p.deg_bound + 1) * p.out_nlimbs for p in H.pairs(ps)[3])
+        for e in map(str.split, H.log()):
+            if e[0] == "host_malloc":
+                held[e[1]] = int(e[2])
+            elif e[0] == "host_free":
+                held.pop(e[1], None)
+        out.append(f"{4 * words} " + " ".join(str(v) for v in held.values()))
+    return out
+
+
 # ---------------------------------------------------------------------------
 @pytest.fixture(scope="session")
 def stub(tmp_path_factory):
@@ -164,6 +183,17 @@ def test_one_lane_remaindering_counts_its_own_coefficients(stub):
     many = [e[1] for e in run(stub, "many_small_beside_few_large")]
     assert sum("k_crt_small" in k for k in many) == 1 and sum("k_crtm_digits" in k for k in many) == 1
     assert not any("k_crt_digits" in k for k in many)
+
+
+def test_pinned_blocks_kept_by_a_context_are_bounded(stub):
+    """The output block a context keeps is at most 64 MiB; a call that needs more returns its own."""
+    bound = 64 << 20
+    calls = [[int(v) for v in e] for e in run(stub, "pinned_blocks_of_single_calls")]
+    assert [c[0] > bound for c in calls] == [False, False, False, True, False]
+    assert calls[1][0] > bound // 2
+    for need, *held in calls:  # the block for the inputs, smaller here, and the one for the results
+        assert max(held) <= bound
+        assert need > bound or any(v >= need for v in held)
 
 
 if __name__ == "__main__":
