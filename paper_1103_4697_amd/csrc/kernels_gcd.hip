@@ -170,10 +170,15 @@ __global__ __launch_bounds__(GCD_THREADS) void k_gcd_modp(const GcdDesc* descs, 
 // of the kernel (degrees 1403 and 1187 with a gcd of degree 37: 1,008 us with it,
 // 422 us now, bound by the Euclid of one wavefront per prime).
 // ---------------------------------------------------------------------------
-// H[64 + i] = h_i for i < 64, zeros below; N[j] = -G_j, zeros above e
-__device__ __forceinline__ void series_inverse(const uint32_t* N, uint32_t* H, int lane, const PrimeC& c) {
+// H[64 + i] = h_i for i < min(terms, 64), zeros below; N[j] = -G_j, zeros above
+// e.  A quotient of at most `terms` coefficients reads no further term, and
+// each is a serial step: all 64 of them and the loads behind them cost a gcd
+// with quotients of 7 coefficients 5 us a call (66.4, now 61.5; one quotient
+// coefficient at a time 61.8), with 41 and 11 coefficients 4 to 5 us.
+__device__ __forceinline__ void series_inverse(const uint32_t* N, uint32_t* H, int terms, int lane, const PrimeC& c) {
   uint32_t acc = lane == 0 ? c.r1 : 0u;
-  for (int l = 0; l < 63; ++l) {
+  const int steps = min(terms, 64) - 1;
+  for (int l = 0; l < steps; ++l) {
     const uint32_t h = (uint32_t)__builtin_amdgcn_readlane((int)acc, l);
     const uint32_t n = lane > l ? N[lane - l] : 0u;
     acc = madd(acc, mmulc(h, n, c.p, c.pinv), c.p);
@@ -183,16 +188,21 @@ __device__ __forceinline__ void series_inverse(const uint32_t* N, uint32_t* H, i
   wave_sync();
 }
 
-// row: residues (Montgomery, canonical), ascending, degree at most deg; q:
+// row: residues (Montgomery, canonical), ascending, degree at most deg; top =
+// row[deg - lane] (zero past the end), requested before H is computed; q:
 // deg + 1 quotient coefficients (plain); N, H in LDS, Q: LDS for the quotient
 // (whole blocks), R: 64 words, both 16-byte aligned
-__device__ __forceinline__ void wave_divide(const uint32_t* row, int deg, int e, const uint32_t* N, const uint32_t* H,
-                                            uint32_t* Q, uint32_t* R, uint32_t* q, int lane, const PrimeC& c) {
-  int d = deg;  // degree mod p (a leading coefficient may vanish)
-  while (d >= e && row[d] == 0) --d;
+__device__ __forceinline__ void wave_divide(const uint32_t* row, uint32_t top, int deg, int e, const uint32_t* N,
+                                            const uint32_t* H, uint32_t* Q, uint32_t* R, uint32_t* q, int lane,
+                                            const PrimeC& c) {
+  int d = deg;
+  uint32_t next = top;
+  if (__builtin_amdgcn_readlane((int)top, 0) == 0) {  // degree mod p (a leading coefficient may vanish)
+    while (d >= e && row[d] == 0) --d;
+    next = d - lane >= 0 ? row[d - lane] : 0u;
+  }
   const int nq = d - e + 1;
   for (int i = nq + lane; i <= deg; i += 64) q[i] = 0u;
-  uint32_t next = d - lane >= 0 ? row[d - lane] : 0u;
   for (int b0 = 0; b0 < nq; b0 += 64) {
     uint32_t s = next;
     next = d - b0 - 64 - lane >= 0 ? row[d - b0 - 64 - lane] : 0u;
@@ -209,7 +219,7 @@ __device__ __forceinline__ void wave_divide(const uint32_t* row, int deg, int e,
     }
     R[lane] = s;
     wave_sync();
-    const uint32_t t = toeplitz64(0u, R, H + 64 + lane, c);
+    const uint32_t t = toeplitz64(0u, R, H + 64 + lane, c, nq - b0);
     Q[b0 + lane] = t;
     if (b0 + lane < nq) q[d - e - b0 - lane] = from_mont(t, c);
     wave_sync();
@@ -263,6 +273,7 @@ __global__ __launch_bounds__(64) void k_gcd_modp_reg(const GcdDesc* descs, const
   const int e = euclid_levels<E>(X, dX, Y, dY, sm, lane, c);
   if (lane == 0) ((int32_t*)(ws + G.e_off))[slot] = e;
   if (e == 0) return;  // a usable prime with a constant gcd ends the problem on the host: no rows needed
+  const uint32_t topa = lane <= G.da ? ra[G.da - lane] : 0u, topb = lane <= G.db ? rb[G.db - lane] : 0u;
   // the gcd made monic, from the top in sm[0..e]
   __syncthreads();
   const uint32_t inv = minv(canon4(sm[0], c.p), c);
@@ -280,11 +291,11 @@ __global__ __launch_bounds__(64) void k_gcd_modp_reg(const GcdDesc* descs, const
   wave_sync();
   uint32_t* H = sm + div_off(E) + 64 * E + 192;
   uint32_t* R = H + 128;
-  series_inverse(N, H, lane, c);
+  series_inverse(N, H, max(G.da, G.db) - e + 1, lane, c);
   uint32_t* u = ws + G.u_off + (int64_t)slot * (G.da + 1);
   uint32_t* v = ws + G.v_off + (int64_t)slot * (G.db + 1);
-  wave_divide(ra, G.da, e, N, H, sm, R, u, lane, c);
-  wave_divide(rb, G.db, e, N, H, sm, R, v, lane, c);
+  wave_divide(ra, topa, G.da, e, N, H, sm, R, u, lane, c);
+  wave_divide(rb, topb, G.db, e, N, H, sm, R, v, lane, c);
 }
 
 static const int kGcdE[] = {2, 4, 6, 9, 12, 16, 24, 32};

@@ -24,10 +24,11 @@ __device__ __forceinline__ uint32_t fold16(uint32_t s, uint64_t a, const PrimeC&
 // s + sum_{q<64} U[q] S[-q] with U in LDS (16-byte aligned), uniform across the
 // wavefront, and S per lane; s canonical in, out.  U is read four words at a time at one
 // address for the whole wavefront (no vector-unit instruction per word), and
-// sixteen products per reduction (fold16).
-__device__ __forceinline__ uint32_t toeplitz64(uint32_t s, const uint32_t* U, const uint32_t* S, const PrimeC& c) {
+// sixteen products per reduction (fold16).  len: products needed, uniform.
+__device__ __forceinline__ uint32_t toeplitz64(uint32_t s, const uint32_t* U, const uint32_t* S, const PrimeC& c,
+                                               int len = 64) {
 #pragma unroll
-  for (int g = 0; g < 64; g += 16) {
+  for (int g = 0; g < 64 && g < len; g += 16) {
     const uint4* U4 = reinterpret_cast<const uint4*>(U + g);
     const uint4 ua = U4[0], ub = U4[1], uc = U4[2], ud = U4[3];
     const uint32_t w16[16] = {ua.x, ua.y, ua.z, ua.w, ub.x, ub.y, ub.z, ub.w,
