@@ -1728,6 +1728,8 @@ static int bivariate_gcd_run(snc_ctx* ctx, const std::vector<UPoly>& A, const st
       J.dig_off = w; w += (int64_t)align_words((size_t)Y.n1 * k);
       J.out_off = w;
     }
+    st = ensure_int_interp(ctx->device, stream, ctx->err);
+    if (st) return st;
     const bool blk = interp_blk_fits(Dx, k);
     std::vector<int64_t> pip(nj + 1, 0), pcr(nj + 1, 0), pcc(nj + 1, 0);
     const int cc = crt_small_class(k);

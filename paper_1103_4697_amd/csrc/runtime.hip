@@ -111,7 +111,7 @@ int ensure_device_tables(int device, std::string& err) {
   e = init_noalloc_scratch(device);
   if (e != hipSuccess) { err = std::string("scratch address: ") + hipGetErrorString(e); return SNC_EDEVICE; }
   upload_tables(T.pc.data(), T.garner.data(), T.wtab.data(), T.ptab.data(), nullptr);
-  launch_ifact_init(nullptr);
+  launch_pow32_init(nullptr);
   launch_crt_small_init(nullptr);
   launch_crt_mfma_init(global_crt_tables(), nullptr);
   launch_points_init(nullptr);

@@ -25,6 +25,8 @@ struct Tables {
 };
 const Tables& tables();
 int ensure_device_tables(int device, std::string& err);
+// tables of the interpolation at the points 0..D (bivariate gcd), filled on first use
+int ensure_int_interp(int device, hipStream_t s, std::string& err);
 // device address of the fixed scratch array of snc_resultant_y_noalloc,
 // looked up once per device with that device current
 hipError_t init_noalloc_scratch(int device);

@@ -122,7 +122,6 @@ __host__ __device__ inline int lx_of(int k) { return (30 * k + 31) / 32 + 2; }
 void upload_tables(const PrimeC* primes, const uint32_t* garner_c, const uint32_t* wtab,
                    const uint32_t* ptab, hipStream_t s);
 hipError_t configure_kernels();
-void launch_ifact_init(hipStream_t s);
 size_t interp_lds_bytes(int max_D);
 // block-parallel interpolation: one workgroup per (resultant, prime, block of 64 coefficients),
 // for degree bounds below 64 IFF_J and the first IFF_K primes (falling-factorial table)
@@ -147,6 +146,7 @@ __device__ __forceinline__ uint32_t point_mont(const uint32_t* points, int pi, i
 // entry l <= 64 = 2^(32 l) 2^64 mod p, entry POW32_STEP = Montgomery form of 2^2048
 constexpr int POW32_ROW = 68, POW32_STEP = 65;
 const uint32_t* pow32_table();           // of the current device
+void launch_pow32_init(hipStream_t s);   // once per device
 // residues: workgroups of 64 coefficients for RED_PRIMES primes
 constexpr int RED_PRIMES = 8;
 inline int64_t reduce_blocks(int k, int T) {
