@@ -150,9 +150,8 @@ struct XPow {
   uint32_t flip, add;           // value = own + (other ^ flip) + add: own + 2p - other or own + other
 };
 
-// of point j (lanes 2i and 2i + 1 call with points 2i and 2i + 1 of a pair)
-__device__ __forceinline__ XPow pair_powers(const uint32_t* points, int pi, int j, const PrimeC& c) {
-  const int odd = j & 1;
+// of point j (lanes 2i and 2i + 1 call with points 2i and 2i + 1 of a pair; odd = j mod 2)
+__device__ __forceinline__ XPow pair_powers(const uint32_t* points, int pi, int j, int odd, const PrimeC& c) {
   XPow X;
   const uint32_t xj = point_mont(points, pi, j, c);
   X.z1 = mmulc(xj, xj, c.p, c.pinv);
@@ -513,7 +512,7 @@ __device__ __forceinline__ void eval_elim_block(int64_t b, const PrimeC* primes,
     }
     r = er;
   }
-  const XPow X = pair_powers(points, pi, j, c);
+  const XPow X = pair_powers(points, pi, j, odd, c);
   // rows are padded to N+1 per operand (length 0 above the degree): no branches
   const RowDesc* ra = rows + J.rows_off;
   const RowDesc* rb = ra + J.rstride;  // J.rstride == N + 1 on this path

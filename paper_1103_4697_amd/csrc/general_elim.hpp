@@ -134,7 +134,7 @@ __device__ __attribute__((noinline)) uint32_t general_instance(const ResJob* job
   const ResJob& J = *job;
   const PrimeC c = primes[pi];
   const uint32_t* r = ws + J.res_off + (int64_t)pi * J.T;
-  const XPow X = pair_powers(points, pi, j, c);
+  const XPow X = pair_powers(points, pi, j, j & 1, c);
   const RowDesc* ra = rows + J.rows_off;
   const RowDesc* rb = ra + J.rstride;
   uint32_t F[MAXY + 1], G[MAXY + 1];
