@@ -53,12 +53,21 @@ constexpr int CM_WAVES = 8;        // wavefronts of a digits workgroup: 4 column
 constexpr int CM_THREADS = 64 * CM_WAVES;
 
 // bytes of V_j mod p_i (Montgomery form, balanced), matrix operand order:
-// [block of i][16 columns of it][block of j][byte][lane][16 rows]
-__device__ __align__(16) int8_t g_vfrag[(size_t)CM_NB * 4 * CM_NB * 4 * 64 * 16];
+// [block of i][16 columns of it][block of j, below i's][byte][lane][16 rows]
+__host__ __device__ constexpr int cm_tile(int ib, int it, int jb) { return 2 * ib * (ib - 1) + it * ib + jb; }
+__device__ __align__(16) int8_t g_vfrag[(size_t)cm_tile(CM_NB, 0, 0) * 4 * 64 * 16];
 __device__ uint32_t g_vinv[KMAX];                       // Montgomery form of V_i^-1 mod p_i
-// balanced bytes (each word four signed bytes, sum b_s 256^s) of V_j and P_j
-__device__ uint32_t g_vbal[(size_t)KMAX * LPS];
-__device__ uint32_t g_pbal[(size_t)KMAX * LPS];
+// Balanced bytes (each word four signed bytes, sum b_s 256^s) of V_j and P_j:
+// both are below 2^(1920 (s + 1) - 29) for j in block s, so 60 (s + 1) words
+// hold them, the top one without a carry out.
+__host__ __device__ constexpr int cm_words(int s) { return 60 * (s + 1); }
+__host__ __device__ constexpr int64_t cm_row(int j) {
+  const int64_t s = j >> 6;
+  return 64 * 30 * s * (s + 1) + (int64_t)(j & 63) * cm_words((int)s);
+}
+static_assert(cm_words(CM_NB - 1) <= LPS, "the rows of the product table are as long");
+__device__ uint32_t g_vbal[(size_t)cm_row(KMAX)];
+__device__ uint32_t g_pbal[(size_t)cm_row(KMAX)];
 
 __global__ __launch_bounds__(64) void k_crtm_vinv(CrtTables tb) {
   const int i = blockIdx.x * 64 + threadIdx.x;
@@ -78,7 +87,7 @@ __global__ __launch_bounds__(64) void k_crtm_frag(CrtTables tb) {
   const PrimeC c = tb.primes[i];
   const int top = 64 * (jb + 1);
   const uint32_t P = top < i ? tb.wtab[(size_t)top * tb.wstride + i] : minv(tb.garner[i], c);
-  int8_t* out = g_vfrag + (size_t)tile * 4096 + lane * 16;
+  int8_t* out = g_vfrag + (size_t)cm_tile(ib, it, jb) * 4096 + lane * 16;
   for (int e = 0; e < 16; ++e) {
     const int j = 64 * jb + 16 * (lane >> 4) + e;
     const uint32_t inv = minv(to_mont(tb.primes[j].p, c), c);
@@ -94,10 +103,10 @@ __global__ __launch_bounds__(64) void k_crtm_balance(CrtTables tb) {
   const uint32_t p = tb.primes[j].p, inv = 0u - tb.primes[j].pinv;
   const uint32_t* A = tb.ptab + (size_t)(64 * (j / 64 + 1)) * tb.pstride;
   const uint32_t* B = tb.ptab + (size_t)j * tb.pstride;
-  uint32_t* V = g_vbal + (size_t)j * LPS;
-  uint32_t* P = g_pbal + (size_t)j * LPS;
+  uint32_t* V = g_vbal + cm_row(j);
+  uint32_t* P = g_pbal + cm_row(j);
   uint32_t borrow = 0, cv = 0, cp = 0;
-  for (int l = 0; l < LPS; ++l) {
+  for (int l = 0; l < cm_words(j / 64); ++l) {
     const uint32_t a = A[l];
     const uint32_t q = (a - borrow) * inv;
     borrow = __umulhi(q, p) + (a < borrow ? 1u : 0u);
@@ -155,7 +164,7 @@ __global__ __launch_bounds__(CM_THREADS) void k_crtm_digits(CrtTables tb, const 
     v4i acc[7];
 #pragma unroll
     for (int d = 0; d < 7; ++d) acc[d] = v4i{0, 0, 0, 0};
-    const v4i* F = reinterpret_cast<const v4i*>(g_vfrag) + ((size_t)(s * 4 + it) * CM_NB) * 256 + lane;
+    const v4i* F = reinterpret_cast<const v4i*>(g_vfrag) + (size_t)cm_tile(s, it, 0) * 256 + lane;
     const v4i* Zr = reinterpret_cast<const v4i*>(Z) + (lane >> 4) * ROWS + (lane & (ROWS - 1));
 #pragma unroll 2
     for (int jb = half; jb < s; jb += 2) {
@@ -268,20 +277,20 @@ __global__ __launch_bounds__(256) void k_crtm_product(const ResJob* jobs, const 
   // (g, coefficient q) of the second
   const int g = tid >> 6, q = tid & 63;
   const int wq = l0 + q;
-  const bool lok = wq < LPS, lokp = wq > 0 && wq <= LPS;
   const bool tok = t0 + q < n1;
   const uint32_t* dg = dig + (size_t)(tok ? t0 + q : 0) * k;
   uint32_t cur[4], prv[4];
   uint4 zw;
   auto fetch = [&](int j0) {
     const int j = j0 + 4 * g;
+    const int s = j0 >> 6, words = cm_words(s);  // a step's primes are of one block
+    const uint32_t* row = (s < nf ? g_vbal : g_pbal) + cm_row(64 * s) + (size_t)(j - 64 * s) * words;
+    const bool lok = wq < words, lokp = wq > 0 && wq <= words;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const bool jok = j + e < k;
-      const int je = jok ? j + e : 0;
-      const uint32_t* row = (je < 64 * nf ? g_vbal : g_pbal) + (size_t)je * LPS;
-      cur[e] = jok && lok ? row[wq] : 0u;
-      prv[e] = jok && lokp ? row[wq - 1] : 0u;
+      cur[e] = jok && lok ? row[e * words + wq] : 0u;
+      prv[e] = jok && lokp ? row[e * words + wq - 1] : 0u;
     }
     if (j + 4 <= k) {
       zw = load_words4(dg + j);

@@ -52,62 +52,90 @@ constexpr int IM_DP = (IM_N + 63) / 64 * 64;           // whole blocks
 constexpr int IM_TROW = IM_DP + 64;                    // bytes of a plane of t per prime (zeros past IM_N)
 
 __device__ uint32_t g_iphi[(size_t)KMAX * IM_N];   // Montgomery form of 1 / phi_m
-__device__ uint32_t g_iphiq[(size_t)KMAX * IM_N];  // Montgomery form of 1 / (phi_m q^m)
 __device__ uint32_t g_psi[(size_t)KMAX * IM_N];    // Montgomery form of psi_m
 __device__ __align__(16) int8_t g_tq[(size_t)KMAX * 4 * IM_TROW];  // bytes of t_m (Montgomery form), four planes
 __device__ uint32_t g_points[(size_t)KMAX * POINT_ROW];
+__device__ uint32_t g_ipoints[(size_t)KMAX * POINT_ROW];  // the same powers of 1/q
 
-// one prime per thread
+// inclusive product over the lanes up to this one (DOWN: from this one up)
+template <bool DOWN>
+__device__ __forceinline__ uint32_t wave_product(uint32_t v, int lane, const PrimeC& c) {
+  for (int d = 1; d < 64; d *= 2) {
+    const uint32_t o = (uint32_t)(DOWN ? __shfl_down((int)v, d) : __shfl_up((int)v, d));
+    if (DOWN ? lane + d < 64 : lane >= d) v = mmulc(v, o, c.p, c.pinv);
+  }
+  return v;
+}
+
+// One prime per wavefront, 64 entries at a time: running products by a scan
+// over the lanes, powers by a step of 64 (0.14 ms for the whole table;
+// a thread per prime, one entry after the other with scattered stores, 3.8).
 __global__ __launch_bounds__(64) void k_points_init(const PrimeC* primes) {
-  const int pi = blockIdx.x * 64 + threadIdx.x;
+  const int pi = blockIdx.x, lane = threadIdx.x;
   const PrimeC c = primes[pi];
   uint32_t* ip = g_iphi + (size_t)pi * IM_N;
-  uint32_t* iq = g_iphiq + (size_t)pi * IM_N;
   uint32_t* ps = g_psi + (size_t)pi * IM_N;
   int8_t* tq = g_tq + (size_t)pi * 4 * IM_TROW;
-  uint32_t* pt = g_points + (size_t)pi * POINT_ROW;
-  // the least q >= 2 with q^2 of order above IM_N - 1; phi_m in psi's row
-  uint32_t q = 0, phi = c.r1, Qm = c.r1;
+  auto mul = [&](uint32_t a, uint32_t b) { return mmulc(a, b, c.p, c.pinv); };
+  constexpr int NB = (IM_N + 63) / 64;
+  // the least q >= 2 with Q = q^2 of order above IM_N - 1
+  uint32_t q = 0, Q = 0;
   for (uint32_t g = 2; q == 0; ++g) {
-    const uint32_t gm = to_mont(g, c), Q = mmulc(gm, gm, c.p, c.pinv);
-    phi = c.r1;
-    Qm = c.r1;
-    ps[0] = phi;
-    bool ok = true;
-    for (int m = 1; m < IM_N && ok; ++m) {
-      Qm = mmulc(Qm, Q, c.p, c.pinv);
-      ok = Qm != c.r1;
-      phi = mmulc(phi, msub(Qm, c.r1, c.p), c.p, c.pinv);
-      ps[m] = phi;
+    const uint32_t gm = to_mont(g, c);
+    Q = mul(gm, gm);
+    const uint32_t step = mpow(Q, 64, c);
+    uint32_t v = mpow(Q, (uint32_t)lane, c);
+    bool one = false;
+    for (int b = 0; b < NB; ++b) {
+      const int m = 64 * b + lane;
+      one |= m >= 1 && m < IM_N && v == c.r1;
+      v = mul(v, step);
     }
-    if (ok) q = gm;
+    if (!__any(one)) q = gm;
   }
-  const uint32_t Q = mmulc(q, q, c.p, c.pinv), qi = minv(q, c), Qi = mmulc(qi, qi, c.p, c.pinv);
-  uint32_t inv = minv(phi, c);  // 1 / phi_m, and Qm = Q^m, from the top down
-  for (int m = IM_N - 1; m >= 0; --m) {
-    ip[m] = inv;
-    inv = mmulc(inv, msub(Qm, c.r1, c.p), c.p, c.pinv);
-    Qm = mmulc(Qm, Qi, c.p, c.pinv);
+  const uint32_t qi = minv(q, c), Qi = mul(qi, qi);
+  // factors Q^m - 1 (1 at m = 0 and past the end) and phi_m, their products, into psi's row
+  auto factor = [&](int m, uint32_t Qm) { return m >= 1 && m < IM_N ? msub(Qm, c.r1, c.p) : c.r1; };
+  const uint32_t Q64 = mpow(Q, 64, c), Qi64 = mpow(Qi, 64, c);
+  uint32_t Qm = mpow(Q, (uint32_t)lane, c), carry = c.r1;
+  for (int b = 0; b < NB; ++b) {
+    const int m = 64 * b + lane;
+    const uint32_t f = mul(carry, wave_product<false>(factor(m, Qm), lane, c));
+    if (m < IM_N) ps[m] = f;
+    carry = (uint32_t)__shfl((int)f, 63);
+    Qm = mul(Qm, Q64);
   }
-  uint32_t qp = c.r1, qip = c.r1;    // q^m, q^-m
-  uint32_t Qp = c.r1, Qip = c.r1;    // Q^m, Q^-m
-  uint32_t Qc = c.r1;                // Q^C(m,2)
-  uint32_t hc = to_mont((c.p + 1) / 2, c);  // Q^-C(m,2) / 2
-  for (int m = 0; m < IM_N; ++m) {
-    uint32_t t = mmulc(Qc, ip[m], c.p, c.pinv);
+  // 1 / phi_m from the top down
+  carry = minv(carry, c);
+  for (int b = NB - 1; b >= 0; --b) {
+    const int m = 64 * b + lane;
+    Qm = mul(Qm, Qi64);
+    const uint32_t f = wave_product<true>(factor(m, Qm), lane, c);
+    const uint32_t above = (uint32_t)__shfl_down((int)f, 1);
+    if (m < IM_N) ip[m] = lane < 63 ? mul(carry, above) : carry;
+    carry = mul(carry, (uint32_t)__shfl((int)f, 0));
+  }
+  // t_m and psi_m: Q^C(m,2) and its inverse by C(m + 64, 2) = C(m, 2) + 64 m + C(64, 2)
+  const uint32_t c0 = (uint32_t)(lane * (lane - 1) / 2);
+  uint32_t Qc = mpow(Q, c0, c), Qr = mul(mpow(Q64, (uint32_t)lane, c), mpow(Q, 2016, c));
+  uint32_t hc = mul(mpow(Qi, c0, c), to_mont((c.p + 1) / 2, c));
+  uint32_t Hr = mul(mpow(Qi64, (uint32_t)lane, c), mpow(Qi, 2016, c));
+  const uint32_t Q4096 = mpow(Q64, 64, c), Qi4096 = mpow(Qi64, 64, c);
+  for (int m = lane; m < IM_N; m += 64) {
+    uint32_t t = mul(Qc, ip[m]);
     if (m & 1) t = mneg(t, c.p);
     const uint32_t w = balance4(t);
     for (int b = 0; b < 4; ++b) tq[(size_t)b * IM_TROW + m] = (int8_t)(w >> (8 * b));
-    ps[m] = mmulc(ps[m], hc, c.p, c.pinv);
-    iq[m] = mmulc(ip[m], qip, c.p, c.pinv);
-    if (m < 32) pt[m] = qp;
-    if (m % 32 == 0) pt[32 + m / 32] = qp;
-    Qc = mmulc(Qc, Qp, c.p, c.pinv);
-    hc = mmulc(hc, Qip, c.p, c.pinv);
-    Qp = mmulc(Qp, Q, c.p, c.pinv);
-    Qip = mmulc(Qip, Qi, c.p, c.pinv);
-    qp = mmulc(qp, q, c.p, c.pinv);
-    qip = mmulc(qip, qi, c.p, c.pinv);
+    ps[m] = mul(ps[m], hc);
+    Qc = mul(Qc, Qr);
+    hc = mul(hc, Hr);
+    Qr = mul(Qr, Q4096);
+    Hr = mul(Hr, Qi4096);
+  }
+  for (int x = lane; x < POINT_ROW; x += 64) {
+    const uint32_t e = x < 32 ? (uint32_t)x : 32u * (uint32_t)(x - 32);
+    g_points[(size_t)pi * POINT_ROW + x] = mpow(q, e, c);
+    g_ipoints[(size_t)pi * POINT_ROW + x] = mpow(qi, e, c);
   }
 }
 
@@ -327,9 +355,12 @@ __global__ __launch_bounds__(IM_THREADS) void k_interp_mfma(const PrimeC* primes
     sPair[tid] = off;
   }
   __syncthreads();
-  // The pairs of values of all jobs, IM_LOADS at a time per thread; the first
-  // are requested before t is staged.
+  const uint32_t* ip = g_iphi + (size_t)pi * IM_N;
+  const uint32_t* iq = g_ipoints + (size_t)pi * POINT_ROW;  // q^-i = iq[32 + i / 32] iq[i mod 32]
+  // The pairs of values of all jobs and their factors, IM_LOADS at a time per
+  // thread; the first are requested before t is staged.
   uint2 vv[IM_LOADS];
+  uint32_t vp[IM_LOADS], va[IM_LOADS], vb[IM_LOADS];
   int vj[IM_LOADS], vi[IM_LOADS];
   auto load_pairs = [&](int x0) {
     int j = 0;
@@ -343,12 +374,13 @@ __global__ __launch_bounds__(IM_THREADS) void k_interp_mfma(const PrimeC* primes
         vi[u] = x - sPair[j];
         vv[u] = make_uint2(0u, 0u);
         if (vi[u] < sN1[2 * j]) vv[u] = *reinterpret_cast<const uint2*>(ws + sPts[j] + 2 * vi[u]);
+        vp[u] = ip[min(vi[u], IM_N - 1)];
+        va[u] = iq[32 + (vi[u] >> 5)];
+        vb[u] = iq[vi[u] & 31];
       }
     }
   };
   load_pairs(tid);
-  const uint32_t* ip = g_iphi + (size_t)pi * IM_N;
-  const uint32_t* iq = g_iphiq + (size_t)pi * IM_N;
   const uint32_t* ps = g_psi + (size_t)pi * IM_N;
   const int8_t* tq = g_tq + (size_t)pi * 4 * IM_TROW;
   // t reversed: the word at byte y holds t at Dp + 67 - y and the three below
@@ -378,15 +410,17 @@ __global__ __launch_bounds__(IM_THREADS) void k_interp_mfma(const PrimeC* primes
   // marked abnormal are computed here: a wavefront each while there are few (a
   // lane alone takes three to four times as long), else a lane each (a pair whose
   // remainders skip degrees at every point marks all of them).
-  auto put_u = [&](int j, int i, uint32_t v0, uint32_t v1) {
+  // p = 1 / phi_i, r = q^-i below 2p
+  auto put_u = [&](int j, int i, uint32_t v0, uint32_t v1, uint32_t p, uint32_t r) {
     v0 = canon(v0, c.p);
     v1 = canon(v1, c.p);
 #pragma unroll
     for (int odd = 0; odd < 2; ++odd) {
       const int s = 2 * j + odd;
       if (i >= 64 * sBlk[s]) continue;
-      const uint32_t v = odd ? v0 + c.p - v1 : v0 + v1;  // < 2p
-      const uint32_t w = i < sN1[s] ? balance4(mmulc(v, (odd ? iq : ip)[i], c.p, c.pinv)) : 0u;
+      uint32_t v = odd ? v0 + c.p - v1 : v0 + v1;  // < 2p
+      if (odd) v = mmul(v, r, c.p, c.pinv);
+      const uint32_t w = i < sN1[s] ? balance4(mmulc(v, p, c.p, c.pinv)) : 0u;
 #pragma unroll
       for (int q = 0; q < 4; ++q) sm[sU[s] + q * 64 * sBlk[s] + i] = (uint8_t)(w >> (8 * q));
     }
@@ -396,10 +430,10 @@ __global__ __launch_bounds__(IM_THREADS) void k_interp_mfma(const PrimeC* primes
       if (x0 != tid) load_pairs(x0);
 #pragma unroll
       for (int u = 0; u < IM_LOADS; ++u)
-        if (vj[u] >= 0) f(vj[u], vi[u], vv[u].x, vv[u].y);
+        if (vj[u] >= 0) f(vj[u], vi[u], vv[u].x, vv[u].y, vp[u], mmul(va[u], vb[u], c.p, c.pinv));
     }
   };
-  each_pair([&](int j, int i, uint32_t v0, uint32_t v1) {
+  each_pair([&](int j, int i, uint32_t v0, uint32_t v1, uint32_t p, uint32_t r) {
     if (__builtin_expect(v0 == ABN_MARK || v1 == ABN_MARK, 0)) {
       for (int e = 0; e < 2; ++e)
         if ((e ? v1 : v0) == ABN_MARK) {
@@ -407,7 +441,7 @@ __global__ __launch_bounds__(IM_THREADS) void k_interp_mfma(const PrimeC* primes
           if (x < IM_MARKS) mark[x] = j << 16 | (2 * i + e);
         }
     }
-    put_u(j, i, v0, v1);
+    put_u(j, i, v0, v1, p, r);
   });
   __syncthreads();
   if (__builtin_expect(nmark != 0, 0)) {
@@ -427,7 +461,8 @@ __global__ __launch_bounds__(IM_THREADS) void k_interp_mfma(const PrimeC* primes
       __syncthreads();
       if (tid < nmark) {
         const int j = mark[tid] >> 16, i = (mark[tid] & 0xffff) >> 1;
-        put_u(j, i, ws[sPts[j] + 2 * i], ws[sPts[j] + 2 * i + 1]);
+        put_u(j, i, ws[sPts[j] + 2 * i], ws[sPts[j] + 2 * i + 1], ip[i],
+              mmul(iq[32 + (i >> 5)], iq[i & 31], c.p, c.pinv));
       }
     } else {
       // pairs of lanes take the pairs of points of which at least one is marked
@@ -445,7 +480,7 @@ __global__ __launch_bounds__(IM_THREADS) void k_interp_mfma(const PrimeC* primes
       }
       __syncthreads();
       load_pairs(tid);
-      each_pair([&](int j, int i, uint32_t v0, uint32_t v1) { put_u(j, i, v0, v1); });
+      each_pair([&](int j, int i, uint32_t v0, uint32_t v1, uint32_t p, uint32_t r) { put_u(j, i, v0, v1, p, r); });
     }
     __syncthreads();
   }
@@ -474,7 +509,7 @@ hipError_t configure_interp_mfma() {
 }
 
 void launch_points_init(hipStream_t s) {
-  hipLaunchKernelGGL(k_points_init, dim3(KMAX / 64), dim3(64), 0, s, global_crt_tables().primes);
+  hipLaunchKernelGGL(k_points_init, dim3(KMAX), dim3(64), 0, s, global_crt_tables().primes);
 }
 
 const uint32_t* points_table() {

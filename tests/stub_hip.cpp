@@ -16,9 +16,20 @@ std::mutex mu;
 std::string text, fail_name;
 int fail_at = 0;
 uintptr_t next_handle = 0x1000;
-std::map<const void*, std::string>& kernels() {
-  static std::map<const void*, std::string> k;
+struct Symbol { std::string name; int module; };
+std::map<const void*, Symbol>& symbols() {  // kernels and device variables
+  static std::map<const void*, Symbol> k;
   return k;
+}
+// code objects: bytes of static device memory, and whether anything of it was used (loaded)
+struct Module { size_t bytes; bool used; } modules[256];
+void* handles[256];
+int nmodules = 0;
+int module_of(void** m) { return (int)(m - handles); }
+const char* use(const void* f) {
+  Symbol& s = symbols()[f];
+  modules[s.module].used = true;
+  return s.name.c_str();
 }
 
 hipError_t note(const char* name, const char* fmt = "", ...) {
@@ -44,11 +55,22 @@ void stub_clear() { text.clear(); }
 // the nth call of `name` from now on fails
 void stub_fail(const char* name, int nth) { fail_name = name; fail_at = nth; }
 
-void** __hipRegisterFatBinary(const void*) { static void* m; return &m; }
+// static device memory of the code objects used so far
+size_t stub_loaded_bytes() {
+  size_t n = 0;
+  for (int i = 0; i < nmodules; ++i) n += modules[i].used ? modules[i].bytes : 0;
+  return n;
+}
+
+void** __hipRegisterFatBinary(const void*) { return &handles[nmodules++]; }
 void __hipUnregisterFatBinary(void**) {}
-void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
-void __hipRegisterFunction(void**, const void* f, char*, const char* name, unsigned, void*, void*, void*, void*, int*) {
-  kernels()[f] = name;
+void __hipRegisterVar(void** m, void* v, char*, char* name, int, size_t bytes, int, int) {
+  symbols()[v] = {name, module_of(m)};
+  modules[module_of(m)].bytes += bytes;
+}
+void __hipRegisterFunction(void** m, const void* f, char*, const char* name, unsigned, void*, void*, void*, void*,
+                           int*) {
+  symbols()[f] = {name, module_of(m)};
 }
 hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t s, hipStream_t st) {
   config = {g, b, s, st};
@@ -59,7 +81,7 @@ hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* s, hipStream_t* s
   return hipSuccess;
 }
 hipError_t hipLaunchKernel(const void* f, dim3 g, dim3, void**, size_t, hipStream_t s) {
-  return note("kernel", "%s %u %p", kernels()[f].c_str(), g.x, (void*)s);
+  return note("kernel", "%s %u %p", use(f), g.x, (void*)s);
 }
 hipError_t hipGetDeviceCount(int* n) { *n = 1; return hipSuccess; }
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
@@ -72,11 +94,14 @@ hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600* p, int) {
   p->multiProcessorCount = 256;
   return hipSuccess;
 }
-hipError_t hipFuncGetAttributes(hipFuncAttributes* a, const void*) { memset(a, 0, sizeof *a); return hipSuccess; }
-hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
+hipError_t hipFuncGetAttributes(hipFuncAttributes* a, const void* f) { use(f); memset(a, 0, sizeof *a); return hipSuccess; }
+hipError_t hipFuncSetAttribute(const void* f, hipFuncAttribute, int) { use(f); return hipSuccess; }
 hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void*, int, size_t) { *n = 8; return hipSuccess; }
-hipError_t hipGetSymbolAddress(void** p, const void*) { handle(p); return hipSuccess; }
-hipError_t hipMemcpyToSymbolAsync(const void*, const void*, size_t, size_t, hipMemcpyKind, hipStream_t) { return hipSuccess; }
+hipError_t hipGetSymbolAddress(void** p, const void* v) { use(v); handle(p); return hipSuccess; }
+hipError_t hipMemcpyToSymbolAsync(const void* v, const void*, size_t, size_t, hipMemcpyKind, hipStream_t) {
+  use(v);
+  return hipSuccess;
+}
 const char* hipGetErrorString(hipError_t) { return "stub"; }
 hipError_t hipGetLastError() { return hipSuccess; }
 hipError_t hipEventCreate(hipEvent_t* e) { handle(e); return hipSuccess; }
