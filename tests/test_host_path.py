@@ -149,6 +149,37 @@ def pinned_blocks_of_single_calls(H):
     return out
 
 
+def general_first_batch(rnd):
+    """Two tails whose first is the pairs above the register classes."""
+    return ([(dense(rnd, 70, 8, 64), dense(rnd, 69, 8, 64)) for _ in range(4)] +
+            [(dense(rnd, 60, 20, 24), dense(rnd, 59, 20, 24)) for _ in range(4)] +
+            [(dense(rnd, 4, 4, 12), dense(rnd, 3, 4, 12))])
+
+
+def two_tails_class_first(H):
+    H.prepare_run(two_class_batch())
+    return H.log()
+
+
+def two_tails_general_first(H):
+    H.prepare_run(general_first_batch(random.Random(8)))
+    return H.log()
+
+
+def one_tail_of_one_class(H):
+    rnd = random.Random(9)
+    H.prepare_run([(dense(rnd, 1, 900, 1500), dense(rnd, 1, 900, 1500)) for _ in range(7)])
+    return H.log()
+
+
+def one_tail_of_a_submitted_run(H):
+    h, _ = H.prepare(two_class_batch())
+    need = H.L.snc_prepared_stage_bytes(h)
+    H.stub.stub_clear()
+    assert H.L.snc_prepared_submit(h, C.c_void_p(0x20000000), C.c_size_t(need), H.stream, C.byref(C.c_int64())) == 0
+    return H.log()
+
+
 def static_memory(H):
     H.batch(two_class_batch())
     return [f"{H.loaded} {H.stub.stub_loaded_bytes()}"]
@@ -201,6 +232,37 @@ def test_pinned_blocks_kept_by_a_context_are_bounded(stub):
     for need, *held in calls:  # the block for the inputs, smaller here, and the one for the results
         assert max(held) <= bound
         assert need > bound or any(v >= need for v in held)
+
+
+@pytest.mark.parametrize("scenario,first,second", [
+    ("two_tails_class_first", "k_eval_elimILi8", "k_eval_elimILi32"),
+    ("two_tails_general_first", "k_elim_general_all", "k_eval_elim"),
+])
+def test_first_tail_travels_beside_the_second(stub, scenario, first, second):
+    log = run(stub, scenario)
+    text = [" ".join(e) for e in log]
+    launches = [i for i, e in enumerate(log) if e[0] == "graph_launch"]
+    downs = [i for i, e in enumerate(log) if e[0] == "download"]
+    assert len(launches) == 2
+    capture = [i for i, e in enumerate(log) if e[0] == "capture"]
+    assert any(first in t for t in text[capture[0]:launches[0]])
+    assert not any(second in t for t in text[capture[0]:launches[0]])
+    assert any(second in t for t in text[capture[1]:launches[1]])
+    assert not any(first in t for t in text[capture[1]:launches[1]])
+    early = [i for i in downs if i < launches[1]]
+    assert early and len(early) < len(downs)
+    side = {log[i][3] for i in early}
+    assert len(side) == 1 and USER not in side
+    # an event on the caller's stream lies between the tail and its download on the other stream
+    assert any(log[i] == ["event_record", USER] for i in range(launches[0], early[0]))
+    assert all(log[i][3] == USER for i in downs if i > launches[1])
+
+
+@pytest.mark.parametrize("scenario", ["one_tail_of_one_class", "one_tail_of_a_submitted_run"])
+def test_one_tail(stub, scenario):
+    log = run(stub, scenario)
+    assert sum(e[0] == "graph_launch" for e in log) == 1
+    assert len({e[3] for e in log if e[0] == "download"}) == 1
 
 
 def test_static_memory_loaded_with_a_context(stub):
