@@ -107,6 +107,16 @@ def crt_lane_ops(k: int, L: int) -> int:
     return (k * (k - 1) // 2) * 19 // 16 + k * L
 
 
+# More primes than this are remaindered on the matrix cores.
+CRT_VALU_PRIMES = 64
+
+
+def crt_mfma_products(k: int, L: int) -> int:
+    """Products of the same on the matrix cores, sixteen byte products each:
+    k(k-1)/2 modular ones for the digits, k L / 2 of a digit and a limb."""
+    return (k * (k - 1) + k * L) // 2
+
+
 def pair_shape(f, g):
     """(m, n, T) of a pair: y-degrees over Z[x] and stored coefficients."""
     def rows(F):
@@ -289,8 +299,8 @@ def measure_ceilings(ctx):
 
 def batch_stage_roofline(snc, pairs, plans, stages, ceilings, workload_tag):
     """Roofline records of the batch's stages from their device times."""
-    ee_ops, ip_ops, crt_ops = 0, 0, 0
-    ee_bytes = ip_bytes = crd_bytes = crc_bytes = 0
+    ee_ops, ip_ops, crt_ops, crtm_ops = 0, 0, 0, 0
+    ee_bytes = ip_bytes = crt_bytes = crtm_bytes = 0
     for (f, g), p in zip(pairs, plans):
         if p.nprimes == 0:
             continue
@@ -299,13 +309,19 @@ def batch_stage_roofline(snc, pairs, plans, stages, ceilings, workload_tag):
         nl = snc.bivariate_limbs(f)[3]
         ee_ops += eval_elim_lane_ops(m, n, T) * k * (D + 1)
         ip_ops += interp_lane_ops(D) * k
-        crt_ops += crt_lane_ops(k, L) * (D + 1)
+        # coefficients mod p in, constants P_j mod p_i, output limbs, prefix products P_j
+        rem_bytes = 4 * k * (D + 1) + 2 * k * k + 4 * (D + 1) * L + 4 * k * L
+        if k > CRT_VALU_PRIMES:
+            crtm_ops += crt_mfma_products(k, L) * (D + 1)
+            crtm_bytes += rem_bytes
+        else:
+            crt_ops += crt_lane_ops(k, L) * (D + 1)
+            crt_bytes += rem_bytes
         ee_bytes += 4 * nl * T + 4 * k * T + 4 * k * (D + 1)      # limbs in, residues kept, values out
         ip_bytes += 12 * k * (D + 1)                               # values, scaling tables, coefficients
-        crd_bytes += 4 * k * (D + 1) + 2 * k * k                   # coefficients mod p in, constants P_j mod p_i
-        crc_bytes += 4 * (D + 1) * L + 4 * k * L                    # output limbs, prefix products P_j
     ee_ms = sum(v for kk, v in stages.items() if kk.startswith("eval_elim"))
-    crt_ms = sum(v for kk, v in stages.items() if kk.startswith("crt"))
+    crtm_ms = sum(v for kk, v in stages.items() if kk.startswith("crt_mfma"))
+    crt_ms = sum(v for kk, v in stages.items() if kk.startswith("crt")) - crtm_ms
     src_res = "paper_1103_4697_amd/csrc/kernels_res.hip"
     recs = {
         "eval_elim": roof("eval_elim (all register classes)", ee_ops, ee_ms,
@@ -314,11 +330,16 @@ def batch_stage_roofline(snc, pairs, plans, stages, ceilings, workload_tag):
         "interp": roof("interp", ip_ops, stages.get("interp", float("nan")),
                        profiled_traffic("interp", "paper_1103_4697_amd/csrc/interp_mfma.hip", workload_tag), ceilings,
                        ip_bytes, mfma=True),
-        "crt": roof("crt (all launches: digits and binary value)", crt_ops, crt_ms,
-                    profiled_traffic("crt", src_res, workload_tag), ceilings, crd_bytes + crc_bytes),
     }
-    hbm = {"eval_elim": recs["eval_elim"]["hbm_gbps"], "interp": recs["interp"]["hbm_gbps"],
-           "crt": recs["crt"]["hbm_gbps"], "peak": PEAK_HBM_GBPS}
+    if crt_ops:
+        recs["crt"] = roof(f"crt (up to {CRT_VALU_PRIMES} primes: digits and binary value)", crt_ops, crt_ms,
+                           profiled_traffic("crt", src_res, workload_tag), ceilings, crt_bytes)
+    if crtm_ops:
+        recs["crt_mfma"] = roof(f"crt (more than {CRT_VALU_PRIMES} primes: digits, product and carry)", crtm_ops, crtm_ms,
+                                profiled_traffic("crt_mfma", "paper_1103_4697_amd/csrc/crt_mfma.hip", workload_tag),
+                                ceilings, crtm_bytes, mfma=True)
+    hbm = {kk: r["hbm_gbps"] for kk, r in recs.items()}
+    hbm["peak"] = PEAK_HBM_GBPS
     return recs, hbm, ee_ms
 
 

@@ -615,7 +615,6 @@ static BigInt stage_crt(GcdProb& p, const std::vector<int32_t>& sel, int emin, c
     jb[t].L = p.lg;
     jb[t].val_off = (int64_t)vals[t];
     jb[t].dig_off = (int64_t)(p.dig + t * p.nmax * ks);
-    jb[t].acc_off = 0;
     jb[t].pts_off = 0;
     jb[t].nq_off = 0;
     jb[t].out_off = (int64_t)(p.outw + t * p.nmax * p.lg);

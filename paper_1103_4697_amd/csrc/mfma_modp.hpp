@@ -23,9 +23,10 @@ __device__ __forceinline__ uint32_t fold_const(const PrimeC& c) {
 }
 
 // sum_d acc[d] 256^d 2^-32 mod p, canonical.  A contraction of n residue
-// pairs leaves |acc[d]| <= 4 n 2^14; n <= 10048 (the largest degree bound,
-// whole blocks) keeps them below 2^29.4.  The sum is split at 2^24: the lower part is
-// below 2^45.5 in magnitude, the upper below 2^53.5, and with p > 2^29.9 both
+// pairs leaves |acc[d]| <= 4 n 2^14; n <= 5056 (one parity of the largest degree
+// bound in whole blocks; the remaindering sums at most 1536) keeps them below
+// 2^28.4.  The sum is split at 2^24: the lower part is
+// below 2^44.5 in magnitude, the upper below 2^52.5, and with p > 2^29.9 both
 // turn positive by p 2^17 and p 2^24; the upper one comes back by k56 =
 // fold_const.
 __device__ __forceinline__ uint32_t fold_bytes(int a0, int a1, int a2, int a3, int a4, int a5, int a6, uint32_t k56,

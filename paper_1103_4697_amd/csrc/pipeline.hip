@@ -209,9 +209,8 @@ void layout_batch(const std::vector<ResPlan>& plans, BatchLayout& lay) {
     J.val_off = (int64_t)w; w += align_words((size_t)P.k * n1);
     const size_t np = (size_t)npts_of(P.D);
     J.pts_off = (int64_t)w; w += align_words((size_t)P.k * np);
-    J.nq_off = (int64_t)w; w += align_words((size_t)P.k * ((n1 + 63) / 64) * 64);
+    J.nq_off = (int64_t)w; w += align_words((size_t)P.k * ((n1 + 63) / 64) * 64);  // adjacent: one buffer of limb sums
     J.dig_off = (int64_t)w; w += align_words(n1 * P.k);
-    J.acc_off = (int64_t)w;  // unused: the combine step keeps its accumulators in LDS
     lay.nb_red += reduce_blocks(P.k, P.T);
     reduce_again += (double)P.k * ((np - 1) / EE_BLOCK) * ((P.T + 63) / 64) * (3 * P.nl + 8);
     lay.max_k = std::max(lay.max_k, P.k);

@@ -106,7 +106,6 @@ struct BatchLayout {
 };
 
 void layout_batch(const std::vector<ResPlan>& plans, BatchLayout& lay);
-size_t job_region_words(const ResPlan& P);
 int parse_bipoly(const snc_bipoly* f, Operand& op, std::string& err);
 int plan_resultant(const Operand& F, const Operand& G, ResPlan& P, std::string& err);
 
@@ -152,8 +151,9 @@ struct snc_ctx {
   // second stream (default priority) and event for work beside the pipeline
   hipStream_t side_stream = nullptr;
   hipEvent_t ev_mid = nullptr, ev_tail = nullptr;
-  // branch of the captured pipeline (default priority): the small-prime CRT
-  // class with the most primes runs beside the other classes
+  // branch of the captured pipeline (default priority): the remaindering on
+  // the matrix cores, or without any the small-prime class with the most
+  // primes, runs beside the other jobs'
   hipStream_t fork_stream = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
 
@@ -207,8 +207,8 @@ struct PipeFork {
   hipEvent_t fork = nullptr, join = nullptr;
 };
 // device launch sequence of a laid-out batch whose header is in ws (tm may be
-// null); with a branch (fk.stream set, tm null) the small-prime CRT class
-// with the most primes runs on the branch beside the other classes
+// null); with a branch (fk.stream set, tm null) part of the remaindering runs
+// on it beside the rest (snc_ctx::fork_stream)
 // tail: -1 all jobs, else that one with the evaluation before it
 void launch_pipeline(const BatchLayout& lay, uint8_t* ws, hipStream_t s, StageTimer* tm, int part,
                      const PipeFork& fk = PipeFork(), int tail = -1);

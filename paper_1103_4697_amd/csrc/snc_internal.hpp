@@ -14,7 +14,7 @@ constexpr int MAXY_GEN = 255;     // largest y-degree handled at all
 constexpr int EE_WAVES = 1;       // wavefronts per eval_elim workgroup
 constexpr int EE_BLOCK = 64 * EE_WAVES;
 constexpr int INTERP_THREADS = 1024;
-constexpr int MAX_D = 10000;     // largest degree bound: interpolation keeps 4(D+1)+O(1) words in LDS
+constexpr int MAX_D = 10000;     // largest degree bound: the interpolations keep a prime's values and tables in LDS
 constexpr int CRT_COEF_PER_BLOCK = 4;   // one wavefront per coefficient (digits)
 constexpr int CRT_COMB_PER_BLOCK = 2;   // coefficients per combination workgroup (four wavefronts over limbs)
 constexpr int GCD_THREADS = 256;
@@ -35,10 +35,10 @@ struct ResJob {
   int64_t coef_off;    // input limbs, limb-major [nl][T] (uint32 index)
   int64_t res_off;     // residues [k][T] (uint32 index)
   int64_t val_off;     // coefficients mod p: [k][D+1]
-  int64_t pts_off;     // values at the points: [k][npts_of(D)]
-  int64_t nq_off;      // Newton blocks Q_j of the block-parallel interpolation: [k][64 ceil((D+1)/64)]
+  int64_t pts_off;     // values at the points: [k][npts_of(D)] (bivariate gcd: [k][D+1])
+  int64_t nq_off;      // right behind them, [k][64 ceil((D+1)/64)]: Newton blocks of the bivariate gcd's interpolation;
+                       // of resultants the rest of the limb sums that start at pts_off (crt_mfma.hip)
   int64_t dig_off;     // mixed-radix digits [D+1][k]
-  int64_t acc_off;     // CRT accumulator [D+1][LX] with LX = lx_of(k)
   int64_t out_off;     // output limbs [D+1][L]
 };
 
@@ -116,7 +116,7 @@ constexpr int32_t GCD_SLOT_UNUSABLE = -2;
 // computes it by the general elimination (no residue is >= 2^30)
 constexpr uint32_t ABN_MARK = 0xffffffffu;
 
-__host__ __device__ inline int lx_of(int k) { return (30 * k + 31) / 32 + 2; }
+__host__ __device__ constexpr int lx_of(int k) { return (30 * k + 31) / 32 + 2; }
 
 // launchers (kernels_res.hip)
 void upload_tables(const PrimeC* primes, const uint32_t* garner_c, const uint32_t* wtab,
@@ -223,8 +223,11 @@ void launch_crt_small_init(hipStream_t s);  // transposed table of P_j mod p_i (
 // Chinese remaindering on the matrix cores (more than CRT_MFMA_MIN - 1
 // primes): digits and carry over groups of 16 coefficients (prefix of
 // crt_mfma_groups over the launch's jobs), limb sums over tiles (prefix of
-// crt_mfma_tiles); the limb sums use the points and Newton-block regions
+// crt_mfma_tiles).  The limb sums, [lx_of(k)][D+1] of 64 bits, take the points
+// region and the one behind it: two words a sum, where the two regions hold
+// at least 2 k (D + 1).
 constexpr int CRT_MFMA_MIN = 65;
+static_assert(lx_of(CRT_MFMA_MIN) <= CRT_MFMA_MIN && lx_of(KMAX) <= KMAX, "the limb sums fit the two regions");
 static_assert(CRT_SMALL_K[NCRT_RES - 1] == CRT_MFMA_MIN - 1, "the classes of the resultants end where the matrix cores begin");
 int64_t crt_mfma_groups(int n1);
 int64_t crt_mfma_tiles(int n1, int k);
