@@ -28,15 +28,16 @@
 // 2048-bit coefficients: 2052 primes, 3,300 coefficients of 1,923 limbs, about
 // 1.1e11 byte products in each half).  The lanes-over-primes kernels issued a
 // 64-bit multiply-add per (digit, prime) and per (digit, limb) and were bound
-// by them: digits 2610 us, binary value 3113 us.  Here: digits 170 us, bound
-// by the stream of the operand table through L2 (each workgroup of 16
-// coefficients reads its triangle once, 8.4 MB) and one barrier pair per
-// block; product 371 us (0.3 P byte products/s), bound by LDS (operands are
-// permuted into it and read back for one 32-wide tile each); carry 42 us, the
-// 52 MB of limb sums.  With 412 primes (degree 12, 512 bits): 150 + 204 us
-// before, 24 + 34 + 11 us now; with 262 primes and 3,073 coefficients: 99 +
-// 134 us before, 15 + 21 + 10 us now; with 79 primes: 17 + 24 us before, 8 +
-// 8 + 7 us now.  Up to 64 primes there is no earlier block to contract with
+// by them: digits 2610 us, binary value 3113 us.  Here: digits 171 us, a chain
+// of 33 blocks with a barrier pair each in 220 workgroups, fewer than CUs
+// (counters: matrix cores busy 28%, vector unit 23% of its issue slots, LDS
+// 9%); product 354 us (0.3 P byte products/s), a barrier and a round trip to
+// L2 for every 16 primes with four workgroups a CU (matrix cores 15%, LDS 19%,
+// vector unit 18%, 2.7 TB/s of HBM); carry 42 us, the 51 MB of limb sums, of
+// which a workgroup reads 64 bytes of each line (143 MB fetched, 3.4 TB/s).
+// With 412 primes (degree 12, 512 bits): 150 + 204 us before, 24 + 34 + 11 us
+// now; with 262 primes and 3,073 coefficients: 99 + 134 us before, 15 + 19 + 9
+// us now; with 79 primes: 17 + 24 us before, 8 + 8 + 8 us now.  Up to 64 primes there is no earlier block to contract with
 // and the lanes-over-primes pair serves (33..64 primes here: 26 us a call
 // against 21).  In a large batch with 65..128 primes (30,000 coefficients): 48
 // + 27 + 24 us against 158 of one lane per coefficient.

@@ -32,13 +32,15 @@
 // multiply-adds on the vector unit (one wavefront per (resultant, prime) at
 // 77% of its issue slots, or a workgroup with barriers per block), with the
 // expansion of each Newton block a further sixth.  512 pairs of degrees 8..40
-// (25,000 (resultant, prime) pairs, degree bounds up to 1,600): 1,100 -> 222
-// us (274 us with all coefficients in one sequence), bound by the matrix
-// cores and the LDS reads of the operands about equally, and by latency where
-// a job has few blocks.  One pair of degree bound 3,072 with 262 primes: 523
-// -> 53 us.  Degree bound 225, 15 pairs, 2,052 primes: 248 -> 96 us; degree
-// bound 552, 35 primes: 13 (two launches) -> 10.5 us; degree bound 36, 5
-// primes: 8.4 (two launches) -> 5.8 us, both latency.
+// (25,000 (resultant, prime) pairs, degree bounds up to 1,600): 1,100 -> 240
+// us.  No unit is at its limit there: counters show 47% of the vector unit's
+// issue slots, 32% of LDS cycles (almost half of them bank conflicts) and the
+// matrix cores busy 24% of theirs; the rest is the latency of the phases
+// between the barriers.  One pair of degree bound 3,072 with 262 primes: 523
+// -> 51 us.  Degree bound 225, 15 pairs, 2,052 primes: 248 -> 94 us (52%, 28%
+// and 11%: staging and folding weigh more in short sums); degree bound 552, 35
+// primes: 13 (two launches) -> 10.3 us; degree bound 36, 5 primes: 8.4 (two
+// launches) -> 7.1 us, both latency.
 #include <hip/hip_runtime.h>
 
 #include "eval_elim.hpp"

@@ -168,7 +168,7 @@ __global__ __launch_bounds__(GCD_THREADS) void k_gcd_modp(const GcdDesc* descs, 
 // Per block e + 64 multiply-adds per lane; one quotient coefficient at a time
 // over the whole dividend took (deg + 1) / 64 updates a coefficient and half
 // of the kernel (degrees 1403 and 1187 with a gcd of degree 37: 1,008 us with it,
-// 422 us now, bound by the Euclid of one wavefront per prime).
+// 414 us now, bound by the Euclid of one wavefront per prime).
 // ---------------------------------------------------------------------------
 // H[64 + i] = h_i for i < min(terms, 64), zeros below; N[j] = -G_j, zeros above
 // e.  A quotient of at most `terms` coefficients reads no further term, and
@@ -294,8 +294,9 @@ __global__ __launch_bounds__(64) void k_gcd_modp_reg(const GcdDesc* descs, const
   series_inverse(N, H, max(G.da, G.db) - e + 1, lane, c);
   uint32_t* u = ws + G.u_off + (int64_t)slot * (G.da + 1);
   uint32_t* v = ws + G.v_off + (int64_t)slot * (G.db + 1);
-  wave_divide(ra, topa, G.da, e, N, H, sm, R, u, lane, c);
-  wave_divide(rb, topb, G.db, e, N, H, sm, R, v, lane, c);
+#pragma unroll 1
+  for (int o = 0; o < 2; ++o)  // one copy of the code, which each wavefront fetches cold
+    wave_divide(o ? rb : ra, o ? topb : topa, o ? G.db : G.da, e, N, H, sm, R, o ? v : u, lane, c);
 }
 
 static const int kGcdE[] = {2, 4, 6, 9, 12, 16, 24, 32};
