@@ -1,7 +1,7 @@
 // HIP kernels of the multi-modular resultant res_y(f, g) (Section 4,
-// "Symbolic Speedups": modular and evaluation homomorphisms, one problem per
-// (prime, point) over Z_p, interpolation and Chinese remaindering), written
-// for gfx950: 64-wide wavefronts, full-rate 32-bit multiplies, LDS staging.
+// "Symbolic Speedups"): reduction of the inputs, elimination above the register
+// classes and Chinese remaindering up to 64 primes, written for gfx950: 64-wide
+// wavefronts, full-rate 32-bit multiplies, LDS staging.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

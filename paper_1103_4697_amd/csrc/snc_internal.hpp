@@ -122,8 +122,9 @@ __host__ __device__ constexpr int lx_of(int k) { return (30 * k + 31) / 32 + 2; 
 void upload_tables(const PrimeC* primes, const uint32_t* garner_c, const uint32_t* wtab,
                    const uint32_t* ptab, hipStream_t s);
 hipError_t configure_kernels();
+// Interpolation at the points 0..D of the bivariate gcd (interp_int.hip).
 size_t interp_lds_bytes(int max_D);
-// block-parallel interpolation: one workgroup per (resultant, prime, block of 64 coefficients),
+// block-parallel: one workgroup per (resultant, prime, block of 64 coefficients),
 // for degree bounds below 64 IFF_J and the first IFF_K primes (falling-factorial table)
 constexpr int IFF_J = 16;
 constexpr int IFF_K = 256;
